@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libbcg.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["hop.hip", "hop_f64.hip", "hop_f32.hip", "hop_h16.hip", "hop_b16.hip", "hop_x16.hip",
+SOURCES = ["hop.hip", "hop_f64.hip", "hop_f32.hip", "hop_h16.hip", "hop_b16.hip", "hop_x16.hip", "hop_rows.hip", "blas_rows.hip",
            "blas.hip", "small.hip", "force.hip", "pseudo.hip", "bcg_api.cpp"]
 CFLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -71,6 +71,9 @@ struct bcg_ctx {
     int qr_passes = 1;        // 1: CholQR, 2: CholQR2 in the initial and reliable-update QR
     bool links = false;
     void* W64[2] = {nullptr, nullptr};
+    bool planes = false;                 // W64 holds the loaded links
+    void* W64r[2] = {nullptr, nullptr};  // the FP64 links in the row layout (rows.h); W64 is
+                                         // made from them by the first call that needs it
     void* Wsl[2] = {nullptr, nullptr};
     Prec wsl_prec = Prec::FP64;
     // device state
@@ -264,6 +267,15 @@ long nvec(bcg_ctx* ctx, int N) { return (long)N * 3 * ctx->Vh; }
 
 bool gram_mfma(bcg_ctx* ctx) { return ctx->opt[BCG_OPT_GRAM_KERNEL] != 2; }
 
+// The row layout (rows.h) for N columns, unless an option asks for one of the plane
+// kernels (its launch shapes and variants are theirs).
+bool use_rows(bcg_ctx* ctx, int N) {
+    for (int o : {BCG_OPT_HOP_TR, BCG_OPT_HOP_TPB, BCG_OPT_HOP_PIPELINE, BCG_OPT_PASS_CPT, BCG_OPT_FUSE_GRAM,
+                  BCG_OPT_HOP_KERNEL, BCG_OPT_GRAM_KERNEL, BCG_OPT_SITE_ORDER, BCG_OPT_PASS_KERNEL, BCG_OPT_HOP_SCHED})
+        if (ctx->opt[o]) return false;
+    return rows_fit(N, ctx->Vh);
+}
+
 // 64-site blocks per time slice for the XCD order of the streaming passes
 int bps64(bcg_ctx* ctx) { return blocks_per_slice(ctx->g, 64); }
 
@@ -284,8 +296,41 @@ int dot_parts(bcg_ctx* ctx, Prec p) {
     return (int)((ctx->Vh + sites - 1) / sites);
 }
 
+// a lattice so large that no block of more than 4 columns fits the row layout keeps its
+// links in the plane layout only
+bool rows_ever(bcg_ctx* ctx) { return rows_fit(5, ctx->Vh); }
+
+// the largest half-volume of bcg_apply_noalloc (one column): these contexts own the
+// memory of both link layouts from bcg_load_links on, as that call may not allocate
+constexpr long NOALLOC_SITES = (long)(SCRATCH_REGION / 48);
+
+// FP64 links of both parities, in one allocation that w[0] owns
+int alloc_links(bcg_ctx* ctx, void** w) {
+    if (w[0]) return BCG_OK;
+    const size_t bytes = (size_t)ctx->nl * 9 * ctx->Vh * 16;
+    if (hipMalloc(&w[0], 2 * bytes) != hipSuccess) {
+        w[0] = nullptr;
+        return fail(ctx, BCG_ERR_NOMEM, "link allocation failed");
+    }
+    w[1] = (char*)w[0] + bytes;
+    return BCG_OK;
+}
+
+// FP64 links in the plane layout, made from the row layout on first use.  Under stream
+// capture the conversion becomes part of the graph and is not taken as done.
+int ensure_plane_links(bcg_ctx* ctx) {
+    if (ctx->planes) return BCG_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIPCK(hipStreamIsCapturing(ctx->stream, &cap));
+    RETCK(alloc_links(ctx, ctx->W64));
+    for (int p = 0; p < 2; ++p) HIPCK(row_links_to_planes(ctx->W64r[p], ctx->W64[p], ctx->nl, ctx->Vh, ctx->stream));
+    ctx->planes = cap == hipStreamCaptureStatusNone;
+    return BCG_OK;
+}
+
 int hop(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const void* ctr, int N,
         int epi, const int* halt, double* dot = nullptr, double2* partials = nullptr) {
+    if (p == Prec::FP64) RETCK(ensure_plane_links(ctx));
     const void* Wp = (p == Prec::FP64) ? ctx->W64[out_parity] : ctx->Wsl[out_parity];
     HopShape h = shape(ctx, p, N, partials != nullptr);
     if (epi == EPI_MASS_DOT_) h = dot_shape(ctx, p);
@@ -293,6 +338,22 @@ int hop(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const v
     HIPCK(launch_hop(p, ctx->nl, Wp, in, out, ctr, 4.0 * ctx->mass * ctx->mass, N, ctx->g,
                      out_parity, epi, h, halt, dot, partials, ctx->hopq, ctx->stream));
     return BCG_OK;
+}
+
+// the hop in the row layout (ctr as launch_hop_rows)
+int hop_rows(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const void* ctr, int N,
+             const int* halt) {
+    const void* Wp = ctx->W64r[out_parity];
+    Prof pr(ctx, out_parity == 1 ? BCG_K_HOP_OE : BCG_K_HOP_EO, true);
+    HIPCK(launch_hop_rows(p, ctx->nl, Wp, in, out, ctr, 4.0 * ctx->mass * ctx->mass, N, ctx->g, row_order(ctx->g, N),
+                          out_parity, halt, ctx->stream));
+    return BCG_OK;
+}
+
+// out = A in, FP64, row layout; tmp: odd-parity scratch
+int apply64_rows(bcg_ctx* ctx, const void* in, void* out, void* tmp, int N, const int* halt) {
+    RETCK(hop_rows(ctx, Prec::FP64, 1, in, tmp, nullptr, N, halt));
+    return hop_rows(ctx, Prec::FP64, 0, tmp, out, in, N, halt);
 }
 
 // the fused Gram epilogues fit in LDS for this precision and block size
@@ -355,6 +416,7 @@ int read_state(bcg_ctx* ctx) {
 }
 
 int alloc_solve(bcg_ctx* ctx, int N, Prec ps) {
+    RETCK(ensure_plane_links(ctx));  // before any capture of the iteration
     const size_t n64 = (size_t)nvec(ctx, N) * 16, nsl = store_bytes(ps, N, 3, ctx->Vh);
     for (int s : {WB_B64, WB_Y, WB_X, WB_R64, WB_T64}) RETCK(ensure(ctx, s, n64));
     for (int s : {WB_P0, WB_P1, WB_Q0, WB_Q1, WB_AP, WB_T}) RETCK(ensure(ctx, s, nsl));
@@ -364,6 +426,7 @@ int alloc_solve(bcg_ctx* ctx, int N, Prec ps) {
 int ensure_sloppy_links(bcg_ctx* ctx, Prec ps) {
     if (ps == Prec::FP64) return BCG_OK;
     if (ctx->Wsl[0] && ctx->wsl_prec == ps) return BCG_OK;
+    RETCK(ensure_plane_links(ctx));
     for (int p = 0; p < 2; ++p) {
         if (ctx->Wsl[p]) {
             HIPCK(hipStreamSynchronize(ctx->stream));
@@ -598,8 +661,9 @@ int bcg_destroy(bcg_ctx* ctx) {
     for (auto e : ctx->pool) (void)hipEventDestroy(e);
     for (auto& b : ctx->work)
         if (b.p) (void)hipFree(b.p);
+    if (ctx->W64[0]) (void)hipFree(ctx->W64[0]);
+    if (ctx->W64r[0]) (void)hipFree(ctx->W64r[0]);
     for (int p = 0; p < 2; ++p) {
-        if (ctx->W64[p]) (void)hipFree(ctx->W64[p]);
         if (ctx->Wsl[p]) (void)hipFree(ctx->Wsl[p]);
     }
     if (ctx->d_state) (void)hipFree(ctx->d_state);
@@ -640,14 +704,18 @@ int bcg_load_links(bcg_ctx* ctx, const void* fat, const void* lng, int on_device
             dlng = (char*)tmp + bytes;
         }
     }
-    const size_t wbytes = (size_t)ctx->nl * 9 * ctx->Vh * 16;
-    for (int p = 0; p < 2; ++p) {
-        if (!ctx->W64[p] && hipMalloc(&ctx->W64[p], wbytes) != hipSuccess) {
-            if (tmp) (void)hipFree(tmp);
-            return fail(ctx, BCG_ERR_NOMEM, "link allocation failed");
-        }
-        HIPCK(pack_links(dfat, dlng, ctx->W64[p], ctx->g, p, ctx->nl, ctx->stream));
+    const bool rows = rows_ever(ctx);
+    int rc = alloc_links(ctx, rows ? ctx->W64r : ctx->W64);
+    if (rc == BCG_OK && rows && ctx->Vh <= NOALLOC_SITES) rc = alloc_links(ctx, ctx->W64);
+    if (rc != BCG_OK) {
+        if (tmp) (void)hipFree(tmp);
+        return rc;
     }
+    for (int p = 0; p < 2; ++p) {
+        if (rows) HIPCK(pack_links_rows(dfat, dlng, ctx->W64r[p], ctx->g, p, ctx->nl, ctx->stream));
+        else HIPCK(pack_links(dfat, dlng, ctx->W64[p], ctx->g, p, ctx->nl, ctx->stream));
+    }
+    ctx->planes = !rows;
     ctx->wsl_prec = Prec::FP64;   // sloppy copies are rebuilt from the new links on demand
     if (ctx->Wsl[0]) {
         (void)hipFree(ctx->Wsl[0]);
@@ -689,6 +757,16 @@ int bcg_apply(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
     RETCK(ensure(ctx, WB_A0, b));
     RETCK(ensure(ctx, WB_A1, b));
     RETCK(ensure(ctx, WB_A2, b));
+    if (use_rows(ctx, nrhs)) {
+        {
+            Prof pr(ctx, BCG_K_CONVERT);
+            HIPCK(launch_canon_to_rows((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
+        }
+        RETCK(apply64_rows(ctx, W(ctx, WB_A0), W(ctx, WB_A1), W(ctx, WB_A2), nrhs, nullptr));
+        Prof pr(ctx, BCG_K_CONVERT);
+        HIPCK(launch_rows_to_canon(Wd(ctx, WB_A1), (double2*)out, nrhs, (int)ctx->Vh, ctx->stream));
+        return BCG_OK;
+    }
     {
         Prof pr(ctx, BCG_K_CONVERT);
         HIPCK(launch_canon_to_int((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
@@ -718,10 +796,15 @@ int bcg_apply_noalloc(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
     const unsigned mask = ctx->prof_mask;
     ctx->prof_mask = 0;
     int rc = BCG_OK;
-    hipError_t e = launch_canon_to_int((const double2*)in, A0, nrhs, (int)ctx->Vh, ctx->stream);
+    const int Vh = (int)ctx->Vh;
+    const bool rows = use_rows(ctx, nrhs);
+    hipError_t e = rows ? launch_canon_to_rows((const double2*)in, A0, nrhs, Vh, ctx->stream)
+                        : launch_canon_to_int((const double2*)in, A0, nrhs, Vh, ctx->stream);
     if (e == hipSuccess) {
-        rc = apply64(ctx, A0, A1, A2, nrhs, nullptr);
-        if (rc == BCG_OK) e = launch_int_to_canon(A1, (double2*)out, nrhs, (int)ctx->Vh, ctx->stream);
+        rc = rows ? apply64_rows(ctx, A0, A1, A2, nrhs, nullptr) : apply64(ctx, A0, A1, A2, nrhs, nullptr);
+        if (rc == BCG_OK)
+            e = rows ? launch_rows_to_canon(A1, (double2*)out, nrhs, Vh, ctx->stream)
+                     : launch_int_to_canon(A1, (double2*)out, nrhs, Vh, ctx->stream);
     }
     ctx->prof_mask = mask;
     if (rc != BCG_OK) return rc;
@@ -766,6 +849,16 @@ int bcg_hop(bcg_ctx* ctx, int out_parity, const void* in, void* out, int nrhs) {
     const size_t b = (size_t)nvec(ctx, nrhs) * 16;
     RETCK(ensure(ctx, WB_A0, b));
     RETCK(ensure(ctx, WB_A1, b));
+    if (use_rows(ctx, nrhs)) {
+        {
+            Prof pr(ctx, BCG_K_CONVERT);
+            HIPCK(launch_canon_to_rows((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
+        }
+        RETCK(hop_rows(ctx, Prec::FP64, out_parity, W(ctx, WB_A0), W(ctx, WB_A1), nullptr, nrhs, nullptr));
+        Prof pr(ctx, BCG_K_CONVERT);
+        HIPCK(launch_rows_to_canon(Wd(ctx, WB_A1), (double2*)out, nrhs, (int)ctx->Vh, ctx->stream));
+        return BCG_OK;
+    }
     {
         Prof pr(ctx, BCG_K_CONVERT);
         HIPCK(launch_canon_to_int((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));

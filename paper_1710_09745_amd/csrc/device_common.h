@@ -140,8 +140,8 @@ __device__ __forceinline__ int eta_sign(const int x[4], int mu) {
 // (+3), 3 long backward (-3).  Naive (NL = 8): k = 2 mu + j, j = 0 forward,
 // 1 backward.  W_k(x) already carries eta_mu(x), the sign of the backward hop
 // and the Hermitian conjugate, so (D psi)(x) = sum_k W_k(x) psi(x + d_k).
-template <int NL> __device__ __forceinline__ int hop_mu(int k) { return NL == 16 ? (k >> 2) : (k >> 1); }
-template <int NL> __device__ __forceinline__ int hop_d(int k) {
+template <int NL> __host__ __device__ constexpr int hop_mu(int k) { return NL == 16 ? (k >> 2) : (k >> 1); }
+template <int NL> __host__ __device__ constexpr int hop_d(int k) {
     const int j = NL == 16 ? (k & 3) : (k & 1);
     return ((j & 2) ? 3 : 1) * ((j & 1) ? -1 : 1);
 }

@@ -53,6 +53,12 @@ struct HopQueue {
     int bpc;
 };
 
+// Walk of the site blocks in the row layout (rows.h): cells of by blocks of a plane, bz
+// planes and bt time slices; on = 0: lexicographic
+struct RowOrder {
+    int on, nb, bpp, by, bz, bt, lz;
+};
+
 // bytes per stored complex number, and bytes of a [cols][K][Vh] allocation
 // including the per-group FP32 scales of the 16-bit formats
 inline int pd_bytes(Prec p) {
@@ -100,6 +106,27 @@ HopQueue hop_queue_layout(const Geom& g, int spb, int* ctr);
 size_t hop_tile_bytes(Prec prec, int N, const HopShape& h);
 int hop_grid(const Geom& g, const HopShape& h, bool fused);
 enum { EPI_PLAIN_ = 0, EPI_MASS_ = 1, EPI_MASS_DOT_ = 2 };
+
+// hop_rows.hip ----------------------------------------------------------------------------------
+// whether N columns on Vh sites can use the row layout: more than 4 columns (below, a
+// row of lanes would be mostly idle and the links, which a plane layout streams just as
+// well, are most of the bytes) and FP64 vectors within 32-bit byte offsets
+bool rows_fit(int N, long Vh);
+RowOrder row_order(const Geom& g, int N);
+// FP64 row-layout links of one parity from the canonical ones; from those the FP64 plane
+// layout, and other storages
+hipError_t pack_links_rows(const void* fat, const void* lng, void* W, const Geom& g, int parity, int nl,
+                           hipStream_t s);
+hipError_t row_links_to_planes(const void* Wr, void* Wp, int nl, long Vh, hipStream_t s);
+hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh, hipStream_t s);
+// out = D_{p,1-p} in, or with ctr: out = m2 ctr - D_{p,1-p} in
+hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
+                           int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s);
+
+// blas_rows.hip ---------------------------------------------------------------------------------
+// canonical [N][Vh][3] complex128 <-> FP64 row layout
+hipError_t launch_canon_to_rows(const double2* src, double2* dst, int N, int Vh, hipStream_t s);
+hipError_t launch_rows_to_canon(const double2* src, double2* dst, int N, int Vh, hipStream_t s);
 
 // blas.hip --------------------------------------------------------------------------------------
 // partials[b][i*NB + j] = sum over the rows of workgroup b of conj(A[row,i]) B[row,j]

@@ -1,0 +1,159 @@
+// Row layout of block vectors and links, and the wave mapping its kernels share.
+//
+// The three colours of a site hold their N columns next to each other:
+//   vectors  FP64, FP32  [V/2][3][N] pairs
+//            16-bit      [V/2][N] of {c0, c1, c2, scale}: the three packed colour
+//                        pairs of a (site, column) and their FP32 scale in 16 bytes
+//   links    FP64, FP32  [V/2][9][NL] pairs: entry e = 3 a + b of the NL folded
+//                        matrices of a site side by side
+//            16-bit      [V/2][10][NL] words: the nine packed entries, then the scale
+//
+// A row of 16 lanes takes one site and 16 of its columns (so a wave takes 4 sites),
+// or, with at most 8 columns (half rows), two sites of 8 columns each.  Every load of
+// a vector is then a contiguous, aligned run of columns whatever neighbour it belongs
+// to, and a number that all columns of a site need (an entry of a folded matrix, or
+// the value of another column in a product with an N x N matrix) sits in one lane of
+// the row and reaches the others through the DPP row broadcast inside the multiply-add
+// itself: it costs no load, no LDS access and no extra instruction.
+#pragma once
+#include <type_traits>
+#include <utility>
+
+#include "device_common.h"
+#include "internal.h"
+#include "storage.h"
+
+namespace bcg {
+
+// acc[i] += w_i(lane K of the row) * v for the three complex numbers w_i, on the lanes
+// whose bank (group of four lanes of a row) is set in BM.  The leading s_nop covers
+// the two wait states between a vector write of w and its use as a DPP operand.
+#define BCG_MAC3(T, BM)                                                                     \
+    asm("s_nop 1\n\t"                                                                       \
+        "v_fmac_" T "_dpp %0, %6, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
+        "v_fmac_" T "_dpp %2, %8, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
+        "v_fmac_" T "_dpp %4, %10, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"  \
+        "v_fmac_" T "_dpp %1, %6, %13 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
+        "v_fmac_" T "_dpp %3, %8, %13 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
+        "v_fmac_" T "_dpp %5, %10, %13 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"  \
+        "v_fmac_" T "_dpp %0, -%7, %13 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"  \
+        "v_fmac_" T "_dpp %2, -%9, %13 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"  \
+        "v_fmac_" T "_dpp %4, -%11, %13 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %7, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
+        "v_fmac_" T "_dpp %3, %9, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
+        "v_fmac_" T "_dpp %5, %11, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM         \
+        : "+v"(acc[0].re), "+v"(acc[0].im), "+v"(acc[1].re), "+v"(acc[1].im), "+v"(acc[2].re), "+v"(acc[2].im) \
+        : "v"(w0.re), "v"(w0.im), "v"(w1.re), "v"(w1.im), "v"(w2.re), "v"(w2.im), "v"(v.re), "v"(v.im), "n"(K))
+template <int K, int BM>
+__device__ __forceinline__ void mac3(C2<double> acc[3], C2<double> w0, C2<double> w1, C2<double> w2, C2<double> v) {
+    if constexpr (BM == 0xf) BCG_MAC3("f64", "0xf");
+    else if constexpr (BM == 0x3) BCG_MAC3("f64", "0x3");
+    else BCG_MAC3("f64", "0xc");
+}
+template <int K, int BM>
+__device__ __forceinline__ void mac3(C2<float> acc[3], C2<float> w0, C2<float> w1, C2<float> w2, C2<float> v) {
+    if constexpr (BM == 0xf) BCG_MAC3("f32", "0xf");
+    else if constexpr (BM == 0x3) BCG_MAC3("f32", "0x3");
+    else BCG_MAC3("f32", "0xc");
+}
+#undef BCG_MAC3
+
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, M - 1>)
+template <int... I, typename F> __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int M, typename F> __device__ __forceinline__ void static_for(F&& f) {
+    static_for_(std::make_integer_sequence<int, M>{}, f);
+}
+
+// The three colours of one (site, column): as loaded, and decoded to the arithmetic
+// type.  off: byte offset of (site, column, colour 0), cs: bytes between colours.
+template <typename S> struct RowRaw {
+    C2<typename S::real> v[3];
+    __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned cs) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] = buf_pair<AUX_NONE>(r, off, c * cs, (typename S::real)0);
+    }
+    __device__ __forceinline__ void get(C2<typename S::real> o[3]) const {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = v[c];
+    }
+};
+template <typename S> struct RowRaw16 {
+    uint4 u;
+    __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned) {
+        u = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX_NONE));
+    }
+    __device__ __forceinline__ void get(C2<float> o[3]) const {
+        const float s = __builtin_bit_cast(float, u.w);
+        const unsigned p[3] = {u.x, u.y, u.z};
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            o[c] = C2<float>{S::dec((unsigned short)(p[c] & 0xffffu)) * s, S::dec((unsigned short)(p[c] >> 16)) * s};
+    }
+};
+template <> struct RowRaw<H16> : RowRaw16<H16> {};
+template <> struct RowRaw<B16> : RowRaw16<B16> {};
+template <> struct RowRaw<X16> : RowRaw16<X16> {};
+
+// bytes between the columns of a site, between its colours, and between sites
+template <typename S> __device__ __forceinline__ constexpr unsigned row_col_bytes() { return S::scaled ? 16u : (unsigned)S::bytes; }
+template <typename S> __device__ __forceinline__ unsigned row_cs(int N) { return S::scaled ? 0u : (unsigned)N * S::bytes; }
+template <typename S> __device__ __forceinline__ unsigned row_ss(int N) { return S::scaled ? (unsigned)N * 16u : 3u * (unsigned)N * S::bytes; }
+
+// Store the three colours of a (site, column) in storage S if `st`; v becomes the
+// values as stored, so that a fused product sees what later kernels will load.
+template <typename S, typename R>
+__device__ __forceinline__ void row_store_rt(void* base, size_t off, unsigned cs, C2<R> v[3], bool st) {
+    char* p = reinterpret_cast<char*>(base) + off;
+    if constexpr (!S::scaled) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            typename S::pair w;
+            w.x = (typename S::real)v[c].re;
+            w.y = (typename S::real)v[c].im;
+            if (st) *reinterpret_cast<typename S::pair*>(p + c * cs) = w;
+            v[c] = C2<R>{(R)w.x, (R)w.y};
+        }
+    } else {
+        float m = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m = fmaxf(m, fmaxf(fabsf((float)v[c].re), fabsf((float)v[c].im)));
+        const float inv = m > 0.0f ? 1.0f / m : 0.0f;
+        unsigned u[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const unsigned short lo = S::enc((float)v[c].re * inv), hi = S::enc((float)v[c].im * inv);
+            u[c] = (unsigned)lo | ((unsigned)hi << 16);
+            v[c] = C2<R>{(R)(S::dec(lo) * m), (R)(S::dec(hi) * m)};
+        }
+        if (st) *reinterpret_cast<uint4*>(p) = make_uint4(u[0], u[1], u[2], __builtin_bit_cast(unsigned, m));
+    }
+}
+template <typename S, typename R>
+__device__ __forceinline__ void row_store(void* base, size_t off, unsigned cs, const C2<R> v[3]) {
+    C2<R> w[3] = {v[0], v[1], v[2]};
+    row_store_rt<S, R>(base, off, cs, w, true);
+}
+
+// Site of a lane: blocks of 16 sites (half rows: 32), four waves of 4 (8) sites.
+template <bool HR> __device__ __forceinline__ constexpr int row_block_sites() { return HR ? 32 : 16; }
+template <bool HR> __device__ __forceinline__ int row_lane_site(int lane) { return HR ? lane >> 3 : lane >> 4; }
+template <bool HR> __device__ __forceinline__ int row_lane_col(int lane) { return HR ? lane & 7 : lane & 15; }
+
+// Site block of workgroup (or task) b of nb.  Workgroup b runs on XCD b mod 8; with an
+// order given, XCD x takes the x-th eighth of a walk through four-dimensional cells of
+// (planes of by blocks) x bz x bt, so that the sites one L2 serves at a time are near
+// each other in all four directions.
+__device__ __forceinline__ int row_block(int b, const RowOrder& o) {
+    if (!o.on) return b;
+    const int lin = (b & 7) * (o.nb >> 3) + (b >> 3);
+    const int cell = o.by * o.bz * o.bt;
+    const int k = lin / cell, r = lin - k * cell;
+    const int ny = o.bpp / o.by, nz = o.lz / o.bz;
+    const int y0 = k % ny, z0 = (k / ny) % nz, t0 = k / (ny * nz);
+    const int y = r % o.by, z = (r / o.by) % o.bz, t = r / (o.by * o.bz);
+    return (y0 * o.by + y) + o.bpp * ((z0 * o.bz + z) + o.lz * (t0 * o.bt + t));
+}
+
+}  // namespace bcg
