@@ -76,6 +76,8 @@ struct bcg_ctx {
                                          // made from them by the first call that needs it
     void* Wsl[2] = {nullptr, nullptr};
     Prec wsl_prec = Prec::FP64;
+    void* Wslr[2] = {nullptr, nullptr};  // sloppy links in the row layout
+    Prec wslr_prec = Prec::FP64;
     // device state
     SolveState* d_state = nullptr;
     SolveState* h_state = nullptr;  // pinned
@@ -343,7 +345,7 @@ int hop(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const v
 // the hop in the row layout (ctr as launch_hop_rows)
 int hop_rows(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const void* ctr, int N,
              const int* halt) {
-    const void* Wp = ctx->W64r[out_parity];
+    const void* Wp = p == Prec::FP64 ? ctx->W64r[out_parity] : ctx->Wslr[out_parity];
     Prof pr(ctx, out_parity == 1 ? BCG_K_HOP_OE : BCG_K_HOP_EO, true);
     HIPCK(launch_hop_rows(p, ctx->nl, Wp, in, out, ctr, 4.0 * ctx->mass * ctx->mass, N, ctx->g, row_order(ctx->g, N),
                           out_parity, halt, ctx->stream));
@@ -402,9 +404,52 @@ int gram_general(bcg_ctx* ctx, Prec p, const void* A, const void* B, int N, doub
     return reduce(ctx, ctx->partials, gram_parts(N, (int)ctx->Vh, false), nullptr, 0, 0.0, N, out, nullptr);
 }
 
-int colnorms(bcg_ctx* ctx, const double2* V, int N, double* out) {
+// The operations of the block solver on its layout (rows: rows.h, else planes).
+struct BlockOps {
+    bcg_ctx* ctx;
+    int N;
+    bool rows;
+    RowOrder ord;
+    BlockOps(bcg_ctx* c, int n) : ctx(c), N(n), rows(use_rows(c, n)), ord(row_order(c->g, n)) {}
+    int Vh() const { return (int)ctx->Vh; }
+    int from_canon(const void* src, double2* dst) const {
+        HIPCK(rows ? launch_canon_to_rows((const double2*)src, dst, N, Vh(), ctx->stream)
+                   : launch_canon_to_int((const double2*)src, dst, N, Vh(), ctx->stream));
+        return BCG_OK;
+    }
+    int to_canon(const double2* src, void* dst) const {
+        Prof pr(ctx, BCG_K_CONVERT);
+        HIPCK(rows ? launch_rows_to_canon(src, (double2*)dst, N, Vh(), ctx->stream)
+                   : launch_int_to_canon(src, (double2*)dst, N, Vh(), ctx->stream));
+        return BCG_OK;
+    }
+    // out = D in, or with ctr: out = 4 m^2 ctr - D in
+    int hop1(Prec p, int out_parity, const void* in, void* out, const void* ctr, const int* halt) const {
+        return rows ? hop_rows(ctx, p, out_parity, in, out, ctr, N, halt)
+                    : hop(ctx, p, out_parity, in, out, ctr, N, ctr ? EPI_MASS_ : EPI_PLAIN_, halt);
+    }
+    int apply(const void* in, void* out, void* tmp) const {
+        return rows ? apply64_rows(ctx, in, out, tmp, N, nullptr) : apply64(ctx, in, out, tmp, N, nullptr);
+    }
+    int gram_of(Prec p, const void* A, const void* B, double2* out, const int* halt) const {
+        if (!rows) return gram(ctx, p, A, B, N, out, halt);
+        {
+            Prof pr(ctx, BCG_K_GRAM);
+            HIPCK(launch_gram_rows(p, A, B, N, Vh(), ord, ctx->partials, halt, ctx->stream));
+        }
+        return reduce(ctx, ctx->partials, gram_rows_parts(N, Vh(), ord), nullptr, 0, 0.0, N, out, halt);
+    }
+    int bmul(Prec px, const void* X, Prec py, const void* Z, void* Y, const double2* M, const int* skip) const {
+        HIPCK(rows ? launch_bmul_rows(px, X, py, Z, Y, M, N, Vh(), ord, skip, ctx->stream)
+                   : launch_bmul(px, X, py, Z, Y, M, N, Vh(), skip, ctx->stream));
+        return BCG_OK;
+    }
+};
+
+int colnorms(bcg_ctx* ctx, const double2* V, int N, double* out, bool rows = false) {
     Prof pr(ctx, BCG_K_OTHER);
-    HIPCK(launch_colnorm2(V, N, (int)ctx->Vh, ctx->nparts, ctx->stream));
+    if (rows) HIPCK(launch_colnorm2_rows(V, N, (int)ctx->Vh, ctx->nparts, ctx->stream));
+    else HIPCK(launch_colnorm2(V, N, (int)ctx->Vh, ctx->nparts, ctx->stream));
     HIPCK(launch_colnorm_reduce(ctx->nparts, N, (int)ctx->Vh, out, 1, ctx->stream));
     return BCG_OK;
 }
@@ -415,32 +460,37 @@ int read_state(bcg_ctx* ctx) {
     return sync(ctx);
 }
 
-int alloc_solve(bcg_ctx* ctx, int N, Prec ps) {
-    RETCK(ensure_plane_links(ctx));  // before any capture of the iteration
+// work vectors of a solve; rows: in the row layout (else the plane links too, before any
+// capture of the iteration)
+int alloc_solve(bcg_ctx* ctx, int N, Prec ps, bool rows = false) {
+    if (!rows) RETCK(ensure_plane_links(ctx));
     const size_t n64 = (size_t)nvec(ctx, N) * 16, nsl = store_bytes(ps, N, 3, ctx->Vh);
     for (int s : {WB_B64, WB_Y, WB_X, WB_R64, WB_T64}) RETCK(ensure(ctx, s, n64));
     for (int s : {WB_P0, WB_P1, WB_Q0, WB_Q1, WB_AP, WB_T}) RETCK(ensure(ctx, s, nsl));
     return BCG_OK;
 }
 
-int ensure_sloppy_links(bcg_ctx* ctx, Prec ps) {
+int ensure_sloppy_links(bcg_ctx* ctx, Prec ps, bool rows = false) {
     if (ps == Prec::FP64) return BCG_OK;
-    if (ctx->Wsl[0] && ctx->wsl_prec == ps) return BCG_OK;
-    RETCK(ensure_plane_links(ctx));
+    void** W = rows ? ctx->Wslr : ctx->Wsl;
+    Prec& have = rows ? ctx->wslr_prec : ctx->wsl_prec;
+    if (W[0] && have == ps) return BCG_OK;
+    if (!rows) RETCK(ensure_plane_links(ctx));
     for (int p = 0; p < 2; ++p) {
-        if (ctx->Wsl[p]) {
+        if (W[p]) {
             HIPCK(hipStreamSynchronize(ctx->stream));
-            HIPCK(hipFree(ctx->Wsl[p]));
-            ctx->Wsl[p] = nullptr;
+            HIPCK(hipFree(W[p]));
+            W[p] = nullptr;
         }
-        if (hipMalloc(&ctx->Wsl[p], store_bytes(ps, ctx->nl, 9, ctx->Vh)) != hipSuccess) {
-            ctx->Wsl[p] = nullptr;
+        if (hipMalloc(&W[p], store_bytes(ps, ctx->nl, 9, ctx->Vh)) != hipSuccess) {
+            W[p] = nullptr;
             return fail(ctx, BCG_ERR_NOMEM, "sloppy link allocation failed");
         }
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(links_from64(ps, ctx->W64[p], ctx->Wsl[p], ctx->nl, ctx->Vh, ctx->stream));
+        if (rows) HIPCK(row_links_from64(ps, ctx->W64r[p], W[p], ctx->nl, ctx->Vh, ctx->stream));
+        else HIPCK(links_from64(ps, ctx->W64[p], W[p], ctx->nl, ctx->Vh, ctx->stream));
     }
-    ctx->wsl_prec = ps;
+    have = ps;
     return BCG_OK;
 }
 
@@ -603,7 +653,8 @@ int bcg_create(bcg_ctx** out, const int dims[4], int improved, void* hip_stream)
         // kernel attributes (dynamic LDS above the default limit), once per device
         static bool setup[SCRATCH_MAX_DEVICES] = {};
         if (!setup[dev]) {
-            if ((e = small_setup()) != hipSuccess || (e = blas_setup()) != hipSuccess)
+            if ((e = small_setup()) != hipSuccess || (e = blas_setup()) != hipSuccess ||
+                (e = blas_rows_setup()) != hipSuccess)
                 return fail(nullptr, BCG_ERR_HIP, std::string("kernel setup: ") + hipGetErrorString(e));
             setup[dev] = true;
         }
@@ -665,6 +716,7 @@ int bcg_destroy(bcg_ctx* ctx) {
     if (ctx->W64r[0]) (void)hipFree(ctx->W64r[0]);
     for (int p = 0; p < 2; ++p) {
         if (ctx->Wsl[p]) (void)hipFree(ctx->Wsl[p]);
+        if (ctx->Wslr[p]) (void)hipFree(ctx->Wslr[p]);
     }
     if (ctx->d_state) (void)hipFree(ctx->d_state);
     if (ctx->h_state) (void)hipHostFree(ctx->h_state);
@@ -716,12 +768,12 @@ int bcg_load_links(bcg_ctx* ctx, const void* fat, const void* lng, int on_device
         else HIPCK(pack_links(dfat, dlng, ctx->W64[p], ctx->g, p, ctx->nl, ctx->stream));
     }
     ctx->planes = !rows;
-    ctx->wsl_prec = Prec::FP64;   // sloppy copies are rebuilt from the new links on demand
-    if (ctx->Wsl[0]) {
-        (void)hipFree(ctx->Wsl[0]);
-        (void)hipFree(ctx->Wsl[1]);
-        ctx->Wsl[0] = ctx->Wsl[1] = nullptr;
-    }
+    ctx->wsl_prec = ctx->wslr_prec = Prec::FP64;   // sloppy copies are rebuilt from the new links on demand
+    for (void** w : {ctx->Wsl, ctx->Wslr})
+        for (int p = 0; p < 2; ++p) {
+            if (w[p]) (void)hipFree(w[p]);
+            w[p] = nullptr;
+        }
     HIPCK(hipStreamSynchronize(ctx->stream));
     if (tmp) (void)hipFree(tmp);
     ctx->links = true;
@@ -757,24 +809,13 @@ int bcg_apply(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
     RETCK(ensure(ctx, WB_A0, b));
     RETCK(ensure(ctx, WB_A1, b));
     RETCK(ensure(ctx, WB_A2, b));
-    if (use_rows(ctx, nrhs)) {
-        {
-            Prof pr(ctx, BCG_K_CONVERT);
-            HIPCK(launch_canon_to_rows((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
-        }
-        RETCK(apply64_rows(ctx, W(ctx, WB_A0), W(ctx, WB_A1), W(ctx, WB_A2), nrhs, nullptr));
-        Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_rows_to_canon(Wd(ctx, WB_A1), (double2*)out, nrhs, (int)ctx->Vh, ctx->stream));
-        return BCG_OK;
-    }
+    const BlockOps ops(ctx, nrhs);
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_canon_to_int((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
+        RETCK(ops.from_canon(in, Wd(ctx, WB_A0)));
     }
-    RETCK(apply64(ctx, W(ctx, WB_A0), W(ctx, WB_A1), W(ctx, WB_A2), nrhs, nullptr));
-    Prof pr(ctx, BCG_K_CONVERT);
-    HIPCK(launch_int_to_canon(Wd(ctx, WB_A1), (double2*)out, nrhs, (int)ctx->Vh, ctx->stream));
-    return BCG_OK;
+    RETCK(ops.apply(W(ctx, WB_A0), W(ctx, WB_A1), W(ctx, WB_A2)));
+    return ops.to_canon(Wd(ctx, WB_A1), out);
 }
 
 int bcg_apply_noalloc(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
@@ -795,21 +836,12 @@ int bcg_apply_noalloc(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
     // no kernel timing here: its events would be created on demand
     const unsigned mask = ctx->prof_mask;
     ctx->prof_mask = 0;
-    int rc = BCG_OK;
-    const int Vh = (int)ctx->Vh;
-    const bool rows = use_rows(ctx, nrhs);
-    hipError_t e = rows ? launch_canon_to_rows((const double2*)in, A0, nrhs, Vh, ctx->stream)
-                        : launch_canon_to_int((const double2*)in, A0, nrhs, Vh, ctx->stream);
-    if (e == hipSuccess) {
-        rc = rows ? apply64_rows(ctx, A0, A1, A2, nrhs, nullptr) : apply64(ctx, A0, A1, A2, nrhs, nullptr);
-        if (rc == BCG_OK)
-            e = rows ? launch_rows_to_canon(A1, (double2*)out, nrhs, Vh, ctx->stream)
-                     : launch_int_to_canon(A1, (double2*)out, nrhs, Vh, ctx->stream);
-    }
+    const BlockOps ops(ctx, nrhs);
+    int rc = ops.from_canon(in, A0);
+    if (rc == BCG_OK) rc = ops.apply(A0, A1, A2);
+    if (rc == BCG_OK) rc = ops.to_canon(A1, out);
     ctx->prof_mask = mask;
-    if (rc != BCG_OK) return rc;
-    if (e != hipSuccess) return fail(ctx, BCG_ERR_HIP, std::string("bcg_apply_noalloc: ") + hipGetErrorString(e));
-    return BCG_OK;
+    return rc;
 }
 
 int bcg_apply_prec(bcg_ctx* ctx, int prec, const void* in, void* out, int nrhs) {
@@ -820,24 +852,24 @@ int bcg_apply_prec(bcg_ctx* ctx, int prec, const void* in, void* out, int nrhs) 
     RETCK(check_ready(ctx));
     const Prec ps = (Prec)prec;
     if (ps == Prec::FP64) return bcg_apply(ctx, in, out, nrhs);
-    RETCK(alloc_solve(ctx, nrhs, ps));
-    RETCK(ensure_sloppy_links(ctx, ps));
-    const int Vh = (int)ctx->Vh;
-    hipStream_t s = ctx->stream;
+    const BlockOps ops(ctx, nrhs);
+    RETCK(alloc_solve(ctx, nrhs, ps, ops.rows));
+    RETCK(ensure_sloppy_links(ctx, ps, ops.rows));
     double2* I64 = Wd(ctx, WB_B64);
     void *P = W(ctx, WB_P0), *T = W(ctx, WB_T), *AP = W(ctx, WB_AP);
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_canon_to_int((const double2*)in, I64, nrhs, Vh, s));
-        HIPCK(launch_identity(M(ctx, M_ID), nrhs, s));
-        HIPCK(launch_bmul(Prec::FP64, I64, ps, nullptr, P, M(ctx, M_ID), nrhs, Vh, nullptr, s));
+        RETCK(ops.from_canon(in, I64));
+        HIPCK(launch_identity(M(ctx, M_ID), nrhs, ctx->stream));
+        RETCK(ops.bmul(Prec::FP64, I64, ps, nullptr, P, M(ctx, M_ID), nullptr));
     }
-    RETCK(hop(ctx, ps, 1, P, T, nullptr, nrhs, EPI_PLAIN_, nullptr));
-    RETCK(hop(ctx, ps, 0, T, AP, P, nrhs, EPI_MASS_, nullptr));
-    Prof pr(ctx, BCG_K_CONVERT);
-    HIPCK(launch_bmul(ps, AP, Prec::FP64, nullptr, I64, M(ctx, M_ID), nrhs, Vh, nullptr, s));
-    HIPCK(launch_int_to_canon(I64, (double2*)out, nrhs, Vh, s));
-    return BCG_OK;
+    RETCK(ops.hop1(ps, 1, P, T, nullptr, nullptr));
+    RETCK(ops.hop1(ps, 0, T, AP, P, nullptr));
+    {
+        Prof pr(ctx, BCG_K_CONVERT);
+        RETCK(ops.bmul(ps, AP, Prec::FP64, nullptr, I64, M(ctx, M_ID), nullptr));
+    }
+    return ops.to_canon(I64, out);
 }
 
 int bcg_hop(bcg_ctx* ctx, int out_parity, const void* in, void* out, int nrhs) {
@@ -849,24 +881,13 @@ int bcg_hop(bcg_ctx* ctx, int out_parity, const void* in, void* out, int nrhs) {
     const size_t b = (size_t)nvec(ctx, nrhs) * 16;
     RETCK(ensure(ctx, WB_A0, b));
     RETCK(ensure(ctx, WB_A1, b));
-    if (use_rows(ctx, nrhs)) {
-        {
-            Prof pr(ctx, BCG_K_CONVERT);
-            HIPCK(launch_canon_to_rows((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
-        }
-        RETCK(hop_rows(ctx, Prec::FP64, out_parity, W(ctx, WB_A0), W(ctx, WB_A1), nullptr, nrhs, nullptr));
-        Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_rows_to_canon(Wd(ctx, WB_A1), (double2*)out, nrhs, (int)ctx->Vh, ctx->stream));
-        return BCG_OK;
-    }
+    const BlockOps ops(ctx, nrhs);
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_canon_to_int((const double2*)in, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
+        RETCK(ops.from_canon(in, Wd(ctx, WB_A0)));
     }
-    RETCK(hop(ctx, Prec::FP64, out_parity, W(ctx, WB_A0), W(ctx, WB_A1), nullptr, nrhs, EPI_PLAIN_, nullptr));
-    Prof pr(ctx, BCG_K_CONVERT);
-    HIPCK(launch_int_to_canon(Wd(ctx, WB_A1), (double2*)out, nrhs, (int)ctx->Vh, ctx->stream));
-    return BCG_OK;
+    RETCK(ops.hop1(Prec::FP64, out_parity, W(ctx, WB_A0), W(ctx, WB_A1), nullptr, nullptr));
+    return ops.to_canon(Wd(ctx, WB_A1), out);
 }
 
 int bcg_link_force(bcg_ctx* ctx, const void* X, const void* Lam, int nrhs, void* grad_fat,
@@ -903,9 +924,10 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     const auto t0 = std::chrono::steady_clock::now();
     const int N = nrhs;
     const Prec ps = ctx->sloppy;
-    RETCK(alloc_solve(ctx, N, ps));
+    const BlockOps ops(ctx, N);
+    RETCK(alloc_solve(ctx, N, ps, ops.rows));
     if (ctx->stall_limit > 0) RETCK(ensure(ctx, WB_YBEST, (size_t)nvec(ctx, N) * 16));
-    RETCK(ensure_sloppy_links(ctx, ps));
+    RETCK(ensure_sloppy_links(ctx, ps, ops.rows));
     const int Vh = (int)ctx->Vh;
     const long n = nvec(ctx, N);
     hipStream_t s = ctx->stream;
@@ -922,9 +944,9 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
 
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_canon_to_int((const double2*)B, B64, N, Vh, s));
+        RETCK(ops.from_canon(B, B64));
     }
-    RETCK(colnorms(ctx, B64, N, d_bnorm));
+    RETCK(colnorms(ctx, B64, N, d_bnorm, ops.rows));
     HIPCK(hipMemcpyAsync(ctx->h_vec, d_bnorm, sizeof(double) * N, hipMemcpyDeviceToHost, s));
     RETCK(sync(ctx));
     for (int i = 0; i < N; ++i)
@@ -933,8 +955,8 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
 
     HIPCK(launch_zero(X, n * 16, s));
     if (use_guess) {
-        HIPCK(launch_canon_to_int((const double2*)Xout, Y, N, Vh, s));
-        RETCK(apply64(ctx, Y, R64, T64, N, nullptr));
+        RETCK(ops.from_canon(Xout, Y));
+        RETCK(ops.apply(Y, R64, T64));
         HIPCK(launch_residual(B64, R64, n, s));
     } else {
         HIPCK(launch_zero(Y, n * 16, s));
@@ -945,7 +967,7 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     double2* Ybest = ctx->stall_limit > 0 ? Wd(ctx, WB_YBEST) : nullptr;
     if (Ybest) HIPCK(launch_copy(Y, Ybest, n * 16, s));
     // thin QR of the initial residual (Alg. 2), Q = R C^{-1}, P = Q (S = I, P_0 = 0)
-    RETCK(gram(ctx, Prec::FP64, R64, R64, N, M(ctx, M_H), nullptr));
+    RETCK(ops.gram_of(Prec::FP64, R64, R64, M(ctx, M_H), nullptr));
     {
         Prof pr(ctx, BCG_K_SMALL);
         HIPCK(launch_small_init(M(ctx, M_H), M(ctx, M_C), M(ctx, M_CINV), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], s));
@@ -955,20 +977,20 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         // CholQR2: Q1 = R C1^{-1} in FP64, Q1^H Q1 = C2^H C2, Q = Q1 C2^{-1}, C = C2 C1
         {
             Prof pr(ctx, BCG_K_OTHER);
-            HIPCK(launch_bmul(Prec::FP64, R64, Prec::FP64, nullptr, T64, M(ctx, M_CINV), N, Vh, halt, s));
+            RETCK(ops.bmul(Prec::FP64, R64, Prec::FP64, nullptr, T64, M(ctx, M_CINV), halt));
         }
-        RETCK(gram(ctx, Prec::FP64, T64, T64, N, M(ctx, M_H), halt));
+        RETCK(ops.gram_of(Prec::FP64, T64, T64, M(ctx, M_H), halt));
         {
             Prof pr(ctx, BCG_K_SMALL);
             HIPCK(launch_small_qr2(M(ctx, M_H), M(ctx, M_C), M(ctx, M_CINV), M(ctx, M_C2I), M(ctx, M_C), st,
                                    (int*)&st->halt, 0, N, ctx->opt[BCG_OPT_SMALL_THREADS], s));
         }
         Prof pr(ctx, BCG_K_OTHER);
-        HIPCK(launch_bmul(Prec::FP64, T64, ps, nullptr, Qb[cur], M(ctx, M_C2I), N, Vh, halt, s));
+        RETCK(ops.bmul(Prec::FP64, T64, ps, nullptr, Qb[cur], M(ctx, M_C2I), halt));
         HIPCK(launch_copy(Qb[cur], Pb[cur], (long)store_bytes(ps, N, 3, ctx->Vh), s));
     } else {
         Prof pr(ctx, BCG_K_OTHER);
-        HIPCK(launch_bmul(Prec::FP64, R64, ps, nullptr, Qb[cur], M(ctx, M_CINV), N, Vh, halt, s));
+        RETCK(ops.bmul(Prec::FP64, R64, ps, nullptr, Qb[cur], M(ctx, M_CINV), halt));
         HIPCK(launch_copy(Qb[cur], Pb[cur], (long)store_bytes(ps, N, 3, ctx->Vh), s));
     }
     // fused path: G = 4 m^2 P^H P + T^H T, with P^H P kept as partials from the
@@ -1011,15 +1033,24 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
             RETCK(hop(ctx, ps, 0, T, AP, P, N, EPI_MASS_, halt));
             RETCK(reduce(ctx, ctx->part_tt, n_tt, ctx->part_pp, n_pp, m2, N, M(ctx, M_G), halt));
         } else {
-            RETCK(hop(ctx, ps, 1, P, T, nullptr, N, EPI_PLAIN_, halt));
-            RETCK(hop(ctx, ps, 0, T, AP, P, N, EPI_MASS_, halt));
-            RETCK(gram(ctx, ps, P, AP, N, M(ctx, M_G), halt));
+            RETCK(ops.hop1(ps, 1, P, T, nullptr, halt));
+            RETCK(ops.hop1(ps, 0, T, AP, P, halt));
+            RETCK(ops.gram_of(ps, P, AP, M(ctx, M_G), halt));
         }
         {
             Prof pr(ctx, BCG_K_SMALL);
             HIPCK(launch_small1(M(ctx, M_G), M(ctx, M_C), M(ctx, M_BETA), M(ctx, M_BETAC), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], s));
         }
-        if (fuse) {
+        if (ops.rows) {
+            {
+                Prof pr(ctx, BCG_K_PASS_A);
+                HIPCK(launch_pass_a_rows(ps, Q, AP, M(ctx, M_BETA), N, Vh, ops.ord, ctx->partials, halt, s));
+            }
+            if (pass_a_rows_gram(N))
+                RETCK(reduce(ctx, ctx->partials, gram_rows_parts(N, Vh, ops.ord), nullptr, 0, 0.0, N, M(ctx, M_H), halt));
+            else
+                RETCK(ops.gram_of(ps, Q, Q, M(ctx, M_H), halt));
+        } else if (fuse) {
             {
                 Prof pr(ctx, BCG_K_PASS_A);
                 HIPCK(launch_pass_a(ps, Q, AP, M(ctx, M_BETA), N, Vh, halt, ctx->partials, ctx->opt[BCG_OPT_PASS_CPT], bps64(ctx),
@@ -1040,9 +1071,13 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         }
         {
             Prof pr(ctx, BCG_K_PASS_B);
-            HIPCK(launch_pass_b(ps, X, Q, P, Qn, Pn, M(ctx, M_BETAC), M(ctx, M_SINV), M(ctx, M_SH),
-                                N, Vh, st, fuse ? ctx->part_pp : nullptr, ctx->opt[BCG_OPT_PASS_CPT], bps64(ctx),
-                                ctx->opt[BCG_OPT_PASS_KERNEL], s));
+            if (ops.rows)
+                HIPCK(launch_pass_b_rows(ps, X, Q, P, Qn, Pn, M(ctx, M_BETAC), M(ctx, M_SINV), M(ctx, M_SH), N, Vh,
+                                         ops.ord, st, s));
+            else
+                HIPCK(launch_pass_b(ps, X, Q, P, Qn, Pn, M(ctx, M_BETAC), M(ctx, M_SINV), M(ctx, M_SH),
+                                    N, Vh, st, fuse ? ctx->part_pp : nullptr, ctx->opt[BCG_OPT_PASS_CPT],
+                                    bps64(ctx), ctx->opt[BCG_OPT_PASS_KERNEL], s));
         }
         return BCG_OK;
     };
@@ -1139,9 +1174,9 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         }
         // reliable update (Alg. 3), also the convergence check on the true residual
         HIPCK(launch_fold_x(Y, X, n, s));
-        RETCK(apply64(ctx, Y, R64, T64, N, nullptr));
+        RETCK(ops.apply(Y, R64, T64));
         HIPCK(launch_residual(B64, R64, n, s));
-        RETCK(gram(ctx, Prec::FP64, R64, R64, N, M(ctx, M_HR), nullptr));
+        RETCK(ops.gram_of(Prec::FP64, R64, R64, M(ctx, M_HR), nullptr));
         const bool qr2 = ctx->qr_passes == 2;
         {
             Prof pr(ctx, BCG_K_SMALL);
@@ -1153,9 +1188,9 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
             // second CholQR pass on Q1 = R C^_1^{-1} (FP64), then S^ = C^ C_k^{-1}
             {
                 Prof pr(ctx, BCG_K_OTHER);
-                HIPCK(launch_bmul(Prec::FP64, R64, Prec::FP64, nullptr, T64, M(ctx, M_CINV), N, Vh, ru_skip, s));
+                RETCK(ops.bmul(Prec::FP64, R64, Prec::FP64, nullptr, T64, M(ctx, M_CINV), ru_skip));
             }
-            RETCK(gram(ctx, Prec::FP64, T64, T64, N, M(ctx, M_HR), ru_skip));
+            RETCK(ops.gram_of(Prec::FP64, T64, T64, M(ctx, M_HR), ru_skip));
             {
                 Prof pr(ctx, BCG_K_SMALL);
                 HIPCK(launch_small_qr2(M(ctx, M_HR), M(ctx, M_SH), M(ctx, M_CINV), M(ctx, M_C2I), M(ctx, M_C), st,
@@ -1164,9 +1199,9 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         }
         {
             Prof pr(ctx, BCG_K_OTHER);
-            if (qr2) HIPCK(launch_bmul(Prec::FP64, T64, ps, nullptr, Qb[1 - cur], M(ctx, M_C2I), N, Vh, ru_skip, s));
-            else HIPCK(launch_bmul(Prec::FP64, R64, ps, nullptr, Qb[1 - cur], M(ctx, M_CINV), N, Vh, ru_skip, s));
-            HIPCK(launch_bmul(ps, Pb[cur], ps, Qb[1 - cur], Pb[1 - cur], M(ctx, M_SH), N, Vh, ru_skip, s));
+            if (qr2) RETCK(ops.bmul(Prec::FP64, T64, ps, nullptr, Qb[1 - cur], M(ctx, M_C2I), ru_skip));
+            else RETCK(ops.bmul(Prec::FP64, R64, ps, nullptr, Qb[1 - cur], M(ctx, M_CINV), ru_skip));
+            RETCK(ops.bmul(ps, Pb[cur], ps, Qb[1 - cur], Pb[1 - cur], M(ctx, M_SH), ru_skip));
         }
         if (fuse) {
             RETCK(gram_partials(ctx, ps, Pb[1 - cur], Pb[1 - cur], N, ctx->part_pp, ru_skip));
@@ -1212,15 +1247,12 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     // the solution: Y (+ X if the loop ended without folding it)
     if (status != BCG_OK || need_final_check) {
         HIPCK(launch_fold_x(Y, X, n, s));
-        RETCK(apply64(ctx, Y, R64, T64, N, nullptr));
+        RETCK(ops.apply(Y, R64, T64));
         HIPCK(launch_residual(B64, R64, n, s));
-        RETCK(colnorms(ctx, R64, N, d_true));
+        RETCK(colnorms(ctx, R64, N, d_true, ops.rows));
         // relative: divide on the host below
     }
-    {
-        Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_int_to_canon(Y, (double2*)Xout, N, Vh, s));
-    }
+    RETCK(ops.to_canon(Y, Xout));
     HIPCK(hipMemcpyAsync(ctx->h_vec, d_true, sizeof(double) * N, hipMemcpyDeviceToHost, s));
     HIPCK(hipMemcpyAsync(ctx->h_vec + MAXN, d_bnorm, sizeof(double) * N, hipMemcpyDeviceToHost, s));
     RETCK(sync(ctx));
@@ -1234,13 +1266,10 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     if (want_best && Ybest && !(tr_max <= best_true)) {
         // a failed solve returns the iterate with the smallest true residual seen
         HIPCK(launch_copy(Ybest, Y, n * 16, s));
-        RETCK(apply64(ctx, Y, R64, T64, N, nullptr));
+        RETCK(ops.apply(Y, R64, T64));
         HIPCK(launch_residual(B64, R64, n, s));
-        RETCK(colnorms(ctx, R64, N, d_true));
-        {
-            Prof pr(ctx, BCG_K_CONVERT);
-            HIPCK(launch_int_to_canon(Y, (double2*)Xout, N, Vh, s));
-        }
+        RETCK(colnorms(ctx, R64, N, d_true, ops.rows));
+        RETCK(ops.to_canon(Y, Xout));
         HIPCK(hipMemcpyAsync(ctx->h_vec, d_true, sizeof(double) * N, hipMemcpyDeviceToHost, s));
         RETCK(sync(ctx));
         for (int i = 0; i < N; ++i) tr[i] = ctx->h_vec[i] / ctx->h_vec[MAXN + i];

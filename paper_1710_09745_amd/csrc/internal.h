@@ -127,6 +127,23 @@ hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, voi
 // canonical [N][Vh][3] complex128 <-> FP64 row layout
 hipError_t launch_canon_to_rows(const double2* src, double2* dst, int N, int Vh, hipStream_t s);
 hipError_t launch_rows_to_canon(const double2* src, double2* dst, int N, int Vh, hipStream_t s);
+// The streaming kernels below are those of blas.hip on row-layout blocks (o: row_order
+// of N).  Gram products give partials as launch_gram, gram_rows_parts of them.
+int gram_rows_parts(int N, int Vh, const RowOrder& o);
+hipError_t launch_gram_rows(Prec prec, const void* A, const void* B, int N, int Vh, const RowOrder& o, double2* part,
+                            const int* halt, hipStream_t s);
+// also writes the gram_rows_parts partials of Qt^H Qt if pass_a_rows_gram(N)
+bool pass_a_rows_gram(int N);
+hipError_t launch_pass_a_rows(Prec prec, void* Q, const void* AP, const double2* beta, int N, int Vh,
+                              const RowOrder& o, double2* part, const int* halt, hipStream_t s);
+hipError_t launch_pass_b_rows(Prec prec, double2* X, const void* Qt, const void* P, void* Qn, void* Pn,
+                              const double2* betaC, const double2* Sinv, const double2* SH, int N, int Vh,
+                              const RowOrder& o, const SolveState* st, hipStream_t s);
+// px, py: FP64, or one lower precision
+hipError_t launch_bmul_rows(Prec px, const void* X, Prec py, const void* Z, void* Y, const double2* M, int N, int Vh,
+                            const RowOrder& o, const int* skip, hipStream_t s);
+hipError_t launch_colnorm2_rows(const double2* V, int N, int Vh, double* partials, hipStream_t s);
+hipError_t blas_rows_setup();
 
 // blas.hip --------------------------------------------------------------------------------------
 // partials[b][i*NB + j] = sum over the rows of workgroup b of conj(A[row,i]) B[row,j]

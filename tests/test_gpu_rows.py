@@ -2,12 +2,14 @@
 their tiles: half rows (5 to 8 columns), one to four 16-column tiles with and without a
 remainder, site counts that leave ragged 16- and 32-site blocks, extents of 2 and 4
 (neighbours that wrap twice), and lattices that take the per-XCD cell walk."""
-import numpy as np
 import pytest
 
 import oracle
+from paper_1710_09745_amd import bcg
 
-from gpu_util import col_rel_err, context, elem_rel_err, inputs, to_dev
+from gpu_util import (col_rel_err, context, elem_rel_err, emulated_sloppy_apply, inputs, site_scaled_err, to_dev,
+                      true_rel_res)
+from test_gpu_operator import SLOPPY_TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +43,39 @@ def test_reloaded_links_reach_both_layouts(n):
             ctx.load_links(fat, lng)
         ref = oracle.Operator(dims, fat, lng, 0.07).apply(B)
         assert elem_rel_err(ctx.apply(to_dev(B)).cpu().numpy(), ref).max() <= 1e-12
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16", "fix16"])
+@pytest.mark.parametrize("n", [7, 16, 40])
+def test_row_sloppy_apply_matches_emulation(prec, n):
+    dims = (6, 6, 4, 6)
+    fat, lng, B = inputs(dims, True, n, 12000 + n)
+    ctx = context(dims, True, fat, lng, 0.05)
+    ref = emulated_sloppy_apply(oracle.Operator(dims, fat, lng, 0.05), prec, B)
+    # the storage roundings of the plane kernels' test
+    assert site_scaled_err(ctx.apply_prec(prec, to_dev(B)).cpu().numpy(), ref) <= SLOPPY_TOL[prec]
+
+
+@pytest.mark.parametrize("n", [5, 8, 9, 16, 24, 32, 40, 64])
+def test_row_iterates_match_oracle(n):
+    """Three iterations with a reliable update forced in (Gram, passes A and B, block
+    multiply and column norms at every tile count), FP64 storage and CholQR2."""
+    dims = (6, 6, 6, 10)  # 1080 sites: ragged 16- and 32-site blocks
+    fat, lng, B = inputs(dims, True, n, 13000 + n)
+    ctx = context(dims, True, fat, lng, 0.1, tol=1e-14, ru_delta=0.9, max_iter=3)
+    ctx.set_stability(qr_passes=2)
+    X, info = ctx.solve(to_dev(B), raise_on_error=False)
+    assert info["rc"] == bcg.ERR_NOT_CONVERGED and info["iters"] == 3
+    ref, _ = oracle.block_cg_rq(oracle.Operator(dims, fat, lng, 0.1).apply, B, 1e-14, max_iter=3)
+    assert col_rel_err(X.cpu().numpy(), ref).max() <= 1e-10
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fix16"])
+@pytest.mark.parametrize("n", [6, 20, 50])
+def test_row_mixed_solve_meets_tolerance(prec, n):
+    dims = (8, 8, 8, 6)
+    fat, lng, B = inputs(dims, True, n, 14000 + n)
+    ctx = context(dims, True, fat, lng, 0.15, tol=1e-9, prec=prec)
+    X, _ = ctx.solve(to_dev(B))
+    op = oracle.Operator(dims, fat, lng, 0.15)
+    assert true_rel_res(op, B, X.cpu().numpy()).max() <= 1e-9
