@@ -899,17 +899,22 @@ int bcg_link_force(bcg_ctx* ctx, const void* X, const void* Lam, int nrhs, void*
     RETCK(check_ready(ctx));
     const size_t b = (size_t)nvec(ctx, nrhs) * 16;
     for (int s : {WB_A0, WB_A1, WB_A2, WB_A3}) RETCK(ensure(ctx, s, b));
+    const BlockOps ops(ctx, nrhs);
+    double2 *X0 = Wd(ctx, WB_A0), *L0 = Wd(ctx, WB_A1), *YX = Wd(ctx, WB_A2), *YL = Wd(ctx, WB_A3);
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_canon_to_int((const double2*)X, Wd(ctx, WB_A0), nrhs, (int)ctx->Vh, ctx->stream));
-        HIPCK(launch_canon_to_int((const double2*)Lam, Wd(ctx, WB_A1), nrhs, (int)ctx->Vh, ctx->stream));
+        RETCK(ops.from_canon(X, X0));
+        RETCK(ops.from_canon(Lam, L0));
     }
-    RETCK(hop(ctx, Prec::FP64, 1, W(ctx, WB_A0), W(ctx, WB_A2), nullptr, nrhs, EPI_PLAIN_, nullptr));
-    RETCK(hop(ctx, Prec::FP64, 1, W(ctx, WB_A1), W(ctx, WB_A3), nullptr, nrhs, EPI_PLAIN_, nullptr));
+    RETCK(ops.hop1(Prec::FP64, 1, X0, YX, nullptr, nullptr));
+    RETCK(ops.hop1(Prec::FP64, 1, L0, YL, nullptr, nullptr));
     Prof pr(ctx, BCG_K_OTHER);
-    HIPCK(launch_link_force(Wd(ctx, WB_A0), Wd(ctx, WB_A1), Wd(ctx, WB_A2), Wd(ctx, WB_A3), nrhs,
-                            ctx->g, ctx->improved, (double2*)grad_fat, (double2*)grad_long,
-                            ctx->stream));
+    if (ops.rows)
+        HIPCK(launch_link_force_rows(X0, L0, YX, YL, nrhs, ctx->g, ops.ord, ctx->improved, (double2*)grad_fat,
+                                     (double2*)grad_long, ctx->stream));
+    else
+        HIPCK(launch_link_force(X0, L0, YX, YL, nrhs, ctx->g, ctx->improved, (double2*)grad_fat, (double2*)grad_long,
+                                ctx->stream));
     return BCG_OK;
 }
 

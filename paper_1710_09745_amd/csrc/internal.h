@@ -296,6 +296,10 @@ hipError_t launch_state_init(SolveState* st, double tol, double ru_delta, int ru
 hipError_t launch_identity(double2* M, int N, hipStream_t s);
 
 // force.hip -------------------------------------------------------------------------------------
+// X, Lam, YX, YL in the row layout
+hipError_t launch_link_force_rows(const double2* X, const double2* Lam, const double2* YX, const double2* YL, int N,
+                                  const Geom& g, const RowOrder& ord, int improved, double2* gfat, double2* glong,
+                                  hipStream_t s);
 hipError_t launch_link_force(const double2* X, const double2* Lam, const double2* YX,
                              const double2* YL, int N, const Geom& g, int improved,
                              double2* gfat, double2* glong, hipStream_t s);

@@ -2,10 +2,11 @@
 their tiles: half rows (5 to 8 columns), one to four 16-column tiles with and without a
 remainder, site counts that leave ragged 16- and 32-site blocks, extents of 2 and 4
 (neighbours that wrap twice), and lattices that take the per-XCD cell walk."""
+import numpy as np
 import pytest
 
 import oracle
-from paper_1710_09745_amd import bcg
+from paper_1710_09745_amd import bcg, synth
 
 from gpu_util import (col_rel_err, context, elem_rel_err, emulated_sloppy_apply, inputs, site_scaled_err, to_dev,
                       true_rel_res)
@@ -79,3 +80,16 @@ def test_row_mixed_solve_meets_tolerance(prec, n):
     X, _ = ctx.solve(to_dev(B))
     op = oracle.Operator(dims, fat, lng, 0.15)
     assert true_rel_res(op, B, X.cpu().numpy()).max() <= 1e-9
+
+
+@pytest.mark.parametrize("n", [5, 8, 13, 16, 40, 64])
+@pytest.mark.parametrize("dims,improved", LATTICES)
+def test_row_link_force_matches_oracle(dims, improved, n):
+    fat, lng, X = inputs(dims, improved, n, 15000 + n)
+    Lam = synth.rhs(synth.make_rng(15100 + n), n, dims)
+    ctx = context(dims, improved, fat, lng, 0.1)
+    gf, gl = ctx.link_force(to_dev(X), to_dev(Lam))
+    rf, rl = oracle.Operator(dims, fat, lng, 0.1).link_force(X, Lam)
+    assert np.abs(gf.cpu().numpy() - rf).max() <= 1e-12 * np.abs(rf).max()
+    if improved:
+        assert np.abs(gl.cpu().numpy() - rl).max() <= 1e-12 * np.abs(rl).max()
