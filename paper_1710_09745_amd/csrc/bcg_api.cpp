@@ -1421,7 +1421,8 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
     const int Vh = (int)ctx->Vh;
     const long n = nvec(ctx, N);
     hipStream_t s = ctx->stream;
-    RETCK(alloc_solve(ctx, N, Prec::FP64));
+    const BlockOps ops(ctx, N);
+    RETCK(alloc_solve(ctx, N, Prec::FP64, ops.rows));
     double2 *B64 = Wd(ctx, WB_B64), *X = Wd(ctx, WB_Y), *R = Wd(ctx, WB_R64), *T64 = Wd(ctx, WB_T64),
             *Rt = Wd(ctx, WB_X);
     double2 *P = Wd(ctx, WB_P0), *AP = Wd(ctx, WB_AP), *T = Wd(ctx, WB_T);
@@ -1431,9 +1432,9 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
     double* d_true = ctx->d_vec + MAXN;
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_canon_to_int((const double2*)B, B64, N, Vh, s));
+        RETCK(ops.from_canon(B, B64));
     }
-    RETCK(colnorms(ctx, B64, N, ctx->d_vec));
+    RETCK(colnorms(ctx, B64, N, ctx->d_vec, ops.rows));
     HIPCK(hipMemcpyAsync(ctx->h_vec, ctx->d_vec, sizeof(double) * N, hipMemcpyDeviceToHost, s));
     RETCK(sync(ctx));
     double bn[MAXN];
@@ -1445,7 +1446,7 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
     HIPCK(launch_zero(X, n * 16, s));
     HIPCK(launch_copy(B64, R, n * 16, s));
     HIPCK(launch_copy(B64, P, n * 16, s));
-    HIPCK(launch_colnorm2(R, N, Vh, ctx->nparts, s));
+    HIPCK(ops.rows ? launch_colnorm2_rows(R, N, Vh, ctx->nparts, s) : launch_colnorm2(R, N, Vh, ctx->nparts, s));
     HIPCK(launch_pb_start(ctx->nparts, N, Vh, st, d_restart, ctx->tol, 1, s));
     int status = BCG_OK, restarts = 0;
     double tr[MAXN];
@@ -1465,9 +1466,9 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
         }
         if (hp.halt) {
             // every column met tol on its iterated residual: check the true residuals
-            RETCK(apply64(ctx, X, Rt, T64, N, nullptr));
+            RETCK(ops.apply(X, Rt, T64));
             HIPCK(launch_residual(B64, Rt, n, s));
-            RETCK(colnorms(ctx, Rt, N, d_true));
+            RETCK(colnorms(ctx, Rt, N, d_true, ops.rows));
             HIPCK(hipMemcpyAsync(ctx->h_vec, d_true, sizeof(double) * N, hipMemcpyDeviceToHost, s));
             RETCK(sync(ctx));
             bool all = true;
@@ -1483,13 +1484,14 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
                 break;
             }
             // restart the columns that missed from their true residual
-            for (int i = 0; i < N; ++i)
+            for (int i = 0; i < N && !ops.rows; ++i)
                 if (ctx->h_flags[i]) {
                     HIPCK(launch_copy(Rt + (long)i * 3 * Vh, R + (long)i * 3 * Vh, 3L * Vh * 16, s));
                     HIPCK(launch_copy(Rt + (long)i * 3 * Vh, P + (long)i * 3 * Vh, 3L * Vh * 16, s));
                 }
             HIPCK(hipMemcpyAsync(d_restart, ctx->h_flags, sizeof(int) * N, hipMemcpyHostToDevice, s));
-            HIPCK(launch_colnorm2(R, N, Vh, ctx->nparts, s));
+            if (ops.rows) HIPCK(launch_pb_restart_rows(R, P, Rt, N, Vh, d_restart, s));
+            HIPCK(ops.rows ? launch_colnorm2_rows(R, N, Vh, ctx->nparts, s) : launch_colnorm2(R, N, Vh, ctx->nparts, s));
             HIPCK(launch_pb_start(ctx->nparts, N, Vh, st, d_restart, ctx->tol, 0, s));
             restarts += 1;
             continue;
@@ -1510,26 +1512,23 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
         int chunk = est < 2 ? 2 : (est > 48 ? 48 : est);
         if (chunk > ctx->max_iter - hp.iters) chunk = ctx->max_iter - hp.iters;
         for (int k = 0; k < chunk; ++k) {
-            RETCK(hop(ctx, Prec::FP64, 1, P, T, nullptr, N, EPI_PLAIN_, halt));
-            RETCK(hop(ctx, Prec::FP64, 0, T, AP, P, N, EPI_MASS_, halt));
+            RETCK(ops.hop1(Prec::FP64, 1, P, T, nullptr, halt));
+            RETCK(ops.hop1(Prec::FP64, 0, T, AP, P, halt));
             Prof pr(ctx, BCG_K_CG_VEC);
-            HIPCK(launch_pb_dot(P, AP, N, Vh, ctx->nparts, st, s));
+            HIPCK(launch_pb_dot(P, AP, N, Vh, ops.rows, ctx->nparts, st, s));
             HIPCK(launch_pb_alpha(ctx->nparts, N, Vh, st, s));
-            HIPCK(launch_pb_update1(X, R, P, AP, N, Vh, ctx->nparts, st, s));
+            HIPCK(launch_pb_update1(X, R, P, AP, N, Vh, ops.rows, ctx->nparts, st, s));
             HIPCK(launch_pb_beta(ctx->nparts, N, Vh, st, s));
-            HIPCK(launch_pb_update2(P, R, N, Vh, st, s));
+            HIPCK(launch_pb_update2(P, R, N, Vh, ops.rows, st, s));
         }
     }
     if (status != BCG_OK) {
-        RETCK(apply64(ctx, X, Rt, T64, N, nullptr));
+        RETCK(ops.apply(X, Rt, T64));
         HIPCK(launch_residual(B64, Rt, n, s));
-        RETCK(colnorms(ctx, Rt, N, d_true));
+        RETCK(colnorms(ctx, Rt, N, d_true, ops.rows));
         HIPCK(hipMemcpyAsync(ctx->h_vec, d_true, sizeof(double) * N, hipMemcpyDeviceToHost, s));
     }
-    {
-        Prof pr(ctx, BCG_K_CONVERT);
-        HIPCK(launch_int_to_canon(X, (double2*)Xout, N, Vh, s));
-    }
+    RETCK(ops.to_canon(X, Xout));
     RETCK(sync(ctx));
     if (status != BCG_OK)
         for (int i = 0; i < N; ++i) tr[i] = ctx->h_vec[i] / bn[i];

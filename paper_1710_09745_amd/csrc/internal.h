@@ -248,13 +248,18 @@ struct PbState {
     int active[64];
     int col_iters[64];
 };
-hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, double* partials, const PbState* st,
-                         hipStream_t s);
+// (rows: blocks in the row layout, else planes)
+hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, bool rows, double* partials,
+                         const PbState* st, hipStream_t s);
 hipError_t launch_pb_alpha(const double* partials, int N, int Vh, PbState* st, hipStream_t s);
-hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh,
+hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh, bool rows,
                              double* partials, const PbState* st, hipStream_t s);
 hipError_t launch_pb_beta(const double* partials, int N, int Vh, PbState* st, hipStream_t s);
-hipError_t launch_pb_update2(double2* P, const double2* R, int N, int Vh, const PbState* st, hipStream_t s);
+hipError_t launch_pb_update2(double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
+                             hipStream_t s);
+// row layout: R and P take the true residual Rt on the columns with restart[j] != 0 (device flags)
+hipError_t launch_pb_restart_rows(double2* R, double2* P, const double2* Rt, int N, int Vh, const int* restart,
+                                  hipStream_t s);
 // (re)start: colnorm_partials from launch_colnorm2 of R; first = 1 starts every column,
 // otherwise the columns with restart[j] != 0 restart and the others stay finished
 hipError_t launch_pb_start(const double* colnorm_partials, int N, int Vh, PbState* st, const int* restart,

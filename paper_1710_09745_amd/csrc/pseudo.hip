@@ -8,7 +8,11 @@
 // while the others go on.  FP64 storage, block vectors [N][3][Vh] pairs.
 //
 // Reductions are deterministic: one partial per (column, workgroup), summed in
-// a fixed order by a single-workgroup kernel (16 lanes per column).
+// a fixed order by a single-workgroup kernel (16 to 128 lanes per column).
+//
+// More than 4 columns are in the row layout ([Vh][3][N]): a thread keeps one column
+// for all of its rows (the threads of a workgroup cover whole rows), so that the loads
+// of a workgroup are one contiguous run and the per-column scalars stay in registers.
 #include "device_common.h"
 #include "internal.h"
 
@@ -48,25 +52,39 @@ k_pb_dot(const double2* __restrict__ P, const double2* __restrict__ AP, int Vh, 
     if (threadIdx.x == 0) partials[(long)j * gridDim.x + blockIdx.x] = s;
 }
 
-// sum over b of partials[j][b] for column j = threadIdx.x / 16, in a fixed order: lane
-// g of the column's 16 takes b = g, g + 16, ..., then an xor butterfly over the 16 lanes
-// (1024 threads: up to 64 columns); every lane of the group ends with the total
-__device__ double pb_column_sum(const double* __restrict__ partials, int nb, int N) {
-    const int j = threadIdx.x >> 4, g = threadIdx.x & 15;
+// Lanes per column of the 1024-thread sums: 16 for 64 columns, up to 128 for 8 or fewer.
+__device__ __forceinline__ int pb_lanes(int N) { return N <= 8 ? 128 : (N <= 16 ? 64 : (N <= 32 ? 32 : 16)); }
+
+// Sum over b of partials[j][b] for column j = threadIdx.x / pb_lanes(N), in a fixed order:
+// lane g of the column takes b = g, g + lanes, ... (eight loads in flight), then the
+// lanes are added in order.  Valid on lane 0 of each column; red: 1024 doubles.
+__device__ double pb_column_sum(const double* __restrict__ partials, int nb, int N, double* red) {
+    const int ln = pb_lanes(N), j = threadIdx.x / ln, g = threadIdx.x & (ln - 1);
     double v = 0.0;
     if (j < N)
-        for (int b = g; b < nb; b += 16) v += partials[(long)j * nb + b];
+        for (int b0 = g; b0 < nb; b0 += 8 * ln) {
+            double t[8];
 #pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = b0 + u * ln < nb ? partials[(long)j * nb + b0 + u * ln] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v += t[u];
+        }
     for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
-    return v;
+    red[threadIdx.x] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (g == 0)
+        for (int q = 0; q < ln; q += 16) s += red[threadIdx.x + q];
+    return s;
 }
 
 // alpha_j = rr_j / p_j^H A p_j for the active columns (0 for the others)
 __global__ void __launch_bounds__(1024) k_pb_alpha(const double* __restrict__ partials, int nb, int N, PbState* st) {
     if (st->halt) return;
-    const int j = threadIdx.x >> 4;
-    const double pap = pb_column_sum(partials, nb, N);
-    if (j < N && (threadIdx.x & 15) == 0) {
+    __shared__ double red[1024];
+    const int ln = pb_lanes(N), j = threadIdx.x / ln;
+    const double pap = pb_column_sum(partials, nb, N, red);
+    if (j < N && (threadIdx.x & (ln - 1)) == 0) {
         double a = 0.0;
         if (st->active[j]) {
             if (!(pap > 0.0)) {
@@ -113,11 +131,12 @@ k_pb_update1(double2* __restrict__ X, double2* __restrict__ R, const double2* __
 __global__ void __launch_bounds__(1024) k_pb_beta(const double* __restrict__ partials, int nb, int N, PbState* st) {
     if (st->halt) return;
     __shared__ int still;
+    __shared__ double red[1024];
     if (threadIdx.x == 0) still = 0;
     __syncthreads();
-    const int j = threadIdx.x >> 4;
-    const double rr = pb_column_sum(partials, nb, N);
-    if (j < N && (threadIdx.x & 15) == 0 && st->active[j]) {
+    const int ln = pb_lanes(N), j = threadIdx.x / ln;
+    const double rr = pb_column_sum(partials, nb, N, red);
+    if (j < N && (threadIdx.x & (ln - 1)) == 0 && st->active[j]) {
         st->beta[j] = rr / st->rr[j];
         st->rr[j] = rr;
         st->relres[j] = sqrt(rr) / st->bnorm[j];
@@ -154,6 +173,92 @@ k_pb_update2(double2* __restrict__ P, const double2* __restrict__ R, int Vh, con
         }
 }
 
+// The same three steps in the row layout.  tp = 256 / N rows of N threads; thread
+// (row, column) strides over the 3 Vh rows of the block; the workgroup's sums per column
+// are added in order of the row (partials [j][b] as above).
+__device__ __forceinline__ void pb_rows_sum(double v, double* red, int N, int tp, double* __restrict__ partials) {
+    red[threadIdx.x] = v;
+    __syncthreads();
+    if (threadIdx.x < N) {
+        double s = 0.0;
+        for (int q = 0; q < tp; ++q) s += red[q * N + threadIdx.x];
+        partials[(long)threadIdx.x * gridDim.x + blockIdx.x] = s;
+    }
+}
+
+__global__ void __launch_bounds__(256)
+k_pb_dot_rows(const double2* __restrict__ P, const double2* __restrict__ AP, int N, long rows,
+              double* __restrict__ partials, const PbState* __restrict__ st) {
+    if (st->halt) return;
+    __shared__ double red[256];
+    const int tp = 256 / N, j = threadIdx.x % N;
+    double s = 0.0;
+    if (threadIdx.x < tp * N && st->active[j]) {
+        const long step = (long)gridDim.x * tp;
+#pragma unroll 4
+        for (long r = (long)blockIdx.x * tp + threadIdx.x / N; r < rows; r += step) {
+            const double2 p = P[r * N + j], a = AP[r * N + j];
+            s += p.x * a.x + p.y * a.y;
+        }
+    }
+    pb_rows_sum(s, red, N, tp, partials);
+}
+
+__global__ void __launch_bounds__(256)
+k_pb_update1_rows(double2* __restrict__ X, double2* __restrict__ R, const double2* __restrict__ P,
+                  const double2* __restrict__ AP, int N, long rows, double* __restrict__ partials,
+                  const PbState* __restrict__ st) {
+    if (st->halt) return;
+    __shared__ double red[256];
+    const int tp = 256 / N, j = threadIdx.x % N;
+    double s = 0.0;
+    if (threadIdx.x < tp * N && st->active[j]) {
+        const double a = st->alpha[j];
+        const long step = (long)gridDim.x * tp;
+#pragma unroll 4
+        for (long r0 = (long)blockIdx.x * tp + threadIdx.x / N; r0 < rows; r0 += step) {
+            const long o = r0 * N + j;
+            const double2 p = P[o], ap = AP[o];
+            double2 x = X[o], r = R[o];
+            x.x = fma(a, p.x, x.x);
+            x.y = fma(a, p.y, x.y);
+            r.x = fma(-a, ap.x, r.x);
+            r.y = fma(-a, ap.y, r.y);
+            X[o] = x;
+            R[o] = r;
+            s += r.x * r.x + r.y * r.y;
+        }
+    }
+    pb_rows_sum(s, red, N, tp, partials);
+}
+
+__global__ void __launch_bounds__(256)
+k_pb_update2_rows(double2* __restrict__ P, const double2* __restrict__ R, int N, long rows,
+                  const PbState* __restrict__ st) {
+    if (st->halt) return;
+    const int tp = 256 / N, j = threadIdx.x % N;
+    if (threadIdx.x >= tp * N || !st->active[j]) return;
+    const double b = st->beta[j];
+    const long step = (long)gridDim.x * tp;
+#pragma unroll 4
+    for (long r0 = (long)blockIdx.x * tp + threadIdx.x / N; r0 < rows; r0 += step) {
+        const long o = r0 * N + j;
+        const double2 r = R[o];
+        double2 p = P[o];
+        p.x = fma(b, p.x, r.x);
+        p.y = fma(b, p.y, r.y);
+        P[o] = p;
+    }
+}
+
+// R and P from the true residual Rt on the columns that restart
+__global__ void __launch_bounds__(256)
+k_pb_restart_rows(double2* __restrict__ R, double2* __restrict__ P, const double2* __restrict__ Rt, int N, long n,
+                  const int* __restrict__ restart) {
+    for (long t = (long)blockIdx.x * 256 + threadIdx.x; t < n; t += (long)gridDim.x * 256)
+        if (restart[t % N]) R[t] = P[t] = Rt[t];
+}
+
 // start (or restart from the true residual) the columns whose flag is set:
 // rr_j = |r_j|^2 from the colnorm partials [b][N]; the others keep their state
 __global__ void k_pb_start(const double* __restrict__ partials, int nb, int N, PbState* st,
@@ -184,26 +289,42 @@ __global__ void k_pb_start(const double* __restrict__ partials, int nb, int N, P
     }
 }
 
-hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, double* partials, const PbState* st,
-                         hipStream_t s) {
-    hipLaunchKernelGGL(k_pb_dot, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, AP, Vh, partials, st);
+// workgroups of the row kernels: the same count as partials per column as the planes'
+static dim3 pb_rows_grid(int Vh) { return dim3(pb_blocks(Vh)); }
+
+hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, bool rows, double* partials,
+                         const PbState* st, hipStream_t s) {
+    if (rows)
+        hipLaunchKernelGGL(k_pb_dot_rows, pb_rows_grid(Vh), dim3(256), 0, s, P, AP, N, 3L * Vh, partials, st);
+    else
+        hipLaunchKernelGGL(k_pb_dot, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, AP, Vh, partials, st);
     return hipGetLastError();
 }
 hipError_t launch_pb_alpha(const double* partials, int N, int Vh, PbState* st, hipStream_t s) {
     hipLaunchKernelGGL(k_pb_alpha, dim3(1), dim3(1024), 0, s, partials, pb_blocks(Vh), N, st);
     return hipGetLastError();
 }
-hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh,
+hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh, bool rows,
                              double* partials, const PbState* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_pb_update1, dim3(pb_blocks(Vh), N), dim3(256), 0, s, X, R, P, AP, Vh, partials, st);
+    if (rows)
+        hipLaunchKernelGGL(k_pb_update1_rows, pb_rows_grid(Vh), dim3(256), 0, s, X, R, P, AP, N, 3L * Vh, partials, st);
+    else
+        hipLaunchKernelGGL(k_pb_update1, dim3(pb_blocks(Vh), N), dim3(256), 0, s, X, R, P, AP, Vh, partials, st);
     return hipGetLastError();
 }
 hipError_t launch_pb_beta(const double* partials, int N, int Vh, PbState* st, hipStream_t s) {
     hipLaunchKernelGGL(k_pb_beta, dim3(1), dim3(1024), 0, s, partials, pb_blocks(Vh), N, st);
     return hipGetLastError();
 }
-hipError_t launch_pb_update2(double2* P, const double2* R, int N, int Vh, const PbState* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_pb_update2, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, R, Vh, st);
+hipError_t launch_pb_update2(double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
+                             hipStream_t s) {
+    if (rows) hipLaunchKernelGGL(k_pb_update2_rows, dim3(4 * pb_blocks(Vh)), dim3(256), 0, s, P, R, N, 3L * Vh, st);
+    else hipLaunchKernelGGL(k_pb_update2, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, R, Vh, st);
+    return hipGetLastError();
+}
+hipError_t launch_pb_restart_rows(double2* R, double2* P, const double2* Rt, int N, int Vh, const int* restart,
+                                  hipStream_t s) {
+    hipLaunchKernelGGL(k_pb_restart_rows, dim3(4 * pb_blocks(Vh)), dim3(256), 0, s, R, P, Rt, N, 3L * Vh * N, restart);
     return hipGetLastError();
 }
 hipError_t launch_pb_start(const double* colnorm_partials, int N, int Vh, PbState* st, const int* restart,

@@ -93,3 +93,15 @@ def test_row_link_force_matches_oracle(dims, improved, n):
     assert np.abs(gf.cpu().numpy() - rf).max() <= 1e-12 * np.abs(rf).max()
     if improved:
         assert np.abs(gl.cpu().numpy() - rl).max() <= 1e-12 * np.abs(rl).max()
+
+
+@pytest.mark.parametrize("n", [5, 24, 40])
+def test_row_pseudo_block_iterates_match_oracle_cg(n):
+    dims, k = (6, 6, 6, 2), 3
+    fat, lng, B = inputs(dims, True, n, 16000 + n)
+    ctx = context(dims, True, fat, lng, 0.1, tol=1e-14, max_iter=k)
+    X, info = ctx.solve_pseudo(to_dev(B), raise_on_error=False)
+    assert info["iters"] == k
+    op = oracle.Operator(dims, fat, lng, 0.1)
+    ref = np.stack([oracle.cg(op.apply, B[i], 1e-14, max_iter=k)[0] for i in range(n)])
+    assert col_rel_err(X.cpu().numpy(), ref).max() <= 1e-10
