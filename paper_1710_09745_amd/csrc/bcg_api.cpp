@@ -1044,7 +1044,7 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         }
         {
             Prof pr(ctx, BCG_K_SMALL);
-            HIPCK(launch_small1(M(ctx, M_G), M(ctx, M_C), M(ctx, M_BETA), M(ctx, M_BETAC), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], s));
+            HIPCK(launch_small1(M(ctx, M_G), M(ctx, M_C), M(ctx, M_BETA), M(ctx, M_BETAC), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], 0, s));
         }
         if (ops.rows) {
             {
@@ -1072,7 +1072,7 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         }
         {
             Prof pr(ctx, BCG_K_SMALL);
-            HIPCK(launch_small2(M(ctx, M_H), M(ctx, M_C), M(ctx, M_SINV), M(ctx, M_SH), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], s));
+            HIPCK(launch_small2(M(ctx, M_H), M(ctx, M_C), M(ctx, M_SINV), M(ctx, M_SH), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], 0, s));
         }
         {
             Prof pr(ctx, BCG_K_PASS_B);

@@ -280,12 +280,13 @@ hipError_t launch_small_init(const double2* H, double2* C, double2* Cinv, SolveS
 hipError_t launch_sstep_coef(const double2* Gv, const double2* Gvv, const double2* Ga, const double2* Wp,
                              const double2* Pv, double2* Bk, double2* alpha, double2* nalpha, int* status, int K,
                              int N, int first, hipStream_t s);
-// beta = G^{-1}, betaC = beta C
+// beta = G^{-1}, betaC = beta C.  parts > 0 (small_sums_parts only): G is that many Gram
+// partials of leading dimension pad_n(N), which the kernel sums itself
 hipError_t launch_small1(const double2* G, const double2* C, double2* beta, double2* betaC,
-                         SolveState* st, int N, int req, hipStream_t s);
+                         SolveState* st, int N, int req, int parts, hipStream_t s);
 // residual test, S from H = S^H S, Sinv, S^H, C <- S C; sets pb_mode / halt
 hipError_t launch_small2(const double2* H, double2* C, double2* Sinv, double2* SH, SolveState* st,
-                         int N, int req, hipStream_t s);
+                         int N, int req, int parts, hipStream_t s);
 // reliable update from H = R^H R of the true residual: true residuals; if conv_check and
 // all <= tol: done; else C^ , C^-1, S^H = (C^ C^-1)^H, C <- C^, resume
 // first_pass: stop after C^ (in SH) and C^{-1} (in Chinv) for CholQR2

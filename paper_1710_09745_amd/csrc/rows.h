@@ -42,7 +42,7 @@ namespace bcg {
         "v_fmac_" T "_dpp %1, %7, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
         "v_fmac_" T "_dpp %3, %9, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM "\n\t"   \
         "v_fmac_" T "_dpp %5, %11, %12 row_newbcast:%14 row_mask:0xf bank_mask:" BM         \
-        : "+v"(acc[0].re), "+v"(acc[0].im), "+v"(acc[1].re), "+v"(acc[1].im), "+v"(acc[2].re), "+v"(acc[2].im) \
+        : "+&v"(acc[0].re), "+&v"(acc[0].im), "+&v"(acc[1].re), "+&v"(acc[1].im), "+&v"(acc[2].re), "+&v"(acc[2].im) \
         : "v"(w0.re), "v"(w0.im), "v"(w1.re), "v"(w1.im), "v"(w2.re), "v"(w2.im), "v"(v.re), "v"(v.im), "n"(K))
 template <int K, int BM>
 __device__ __forceinline__ void mac3(C2<double> acc[3], C2<double> w0, C2<double> w1, C2<double> w2, C2<double> v) {

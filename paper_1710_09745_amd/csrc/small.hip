@@ -15,6 +15,7 @@
 // The working copies live in LDS (two N x N complex matrices, dynamic).
 #include "device_common.h"
 #include "internal.h"
+#include "row_matrix.h"
 
 namespace bcg {
 
@@ -592,6 +593,257 @@ k_small2(const double2* __restrict__ H, double2* __restrict__ C, double2* __rest
     if (threadIdx.x == 0) st->pb_mode = PB_FULL;
 }
 
+// ---------------------------------------------------------------------------------------------
+// N <= 16 (NN = 8 or 16): the whole matrix in the registers of a row of lanes (row_matrix.h).
+//
+// The workgroup kernels above spend their time in a chain of an LDS read, a pivot, an
+// update and a barrier per step.  Here lane j holds column j, so a step needs the pivot
+// (one broadcast, one reciprocal) and multiply-adds that broadcast column k themselves:
+// each of the four waves factors the matrix on its own and they divide the rows of the
+// results, with two barriers in the whole kernel.  Both phases together, per iteration:
+// N = 16 26.6 -> 21.7 us, N = 8 15.6 -> 9.8 us, N = 4 8.5 -> 6.5 us.
+// ---------------------------------------------------------------------------------------------
+template <int... I, typename F> __device__ __forceinline__ void unroll_(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int M, typename F> __device__ __forceinline__ void unroll(F&& f) {
+    unroll_(std::make_integer_sequence<int, M>{}, f);
+}
+
+// H (leading dimension MAXN, or the sum over p of P partials of leading dimension NN)
+// into LDS t[i][NN + 1], and C beside it, by 256 threads; the identity outside N x N
+template <int NN>
+__device__ __forceinline__ void stage16(const double2* __restrict__ H, int P, const double2* __restrict__ C, int N,
+                                        Z2* __restrict__ th, Z2* __restrict__ tc) {
+    constexpr int E = NN * NN, G = 256 / E;  // threads per entry
+    const int e = threadIdx.x % E, g = threadIdx.x / E, i = e / NN, j = e % NN;
+    const bool in = i < N && j < N;
+    Z2 s{0.0, 0.0};
+    if (P == 0) {
+        if (in && g == 0) s = gld(H + i * MAXN + j);
+    } else {
+        for (int p0 = g; p0 < P; p0 += 8 * G) {
+            double2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = p0 + u * G < P ? H[(long)(p0 + u * G) * E + e] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                s.re += v[u].x;
+                s.im += v[u].y;
+            }
+        }
+        if (!in) s = Z2{0.0, 0.0};
+    }
+    if (g == 0) tc[i * (NN + 1) + j] = in ? gld(C + i * MAXN + j) : Z2{i == j ? 1.0 : 0.0, 0.0};
+    if (!in && g == 0) s.re = i == j ? 1.0 : 0.0;
+    if constexpr (G == 1) {
+        th[i * (NN + 1) + j] = s;
+    } else {
+        __shared__ Z2 part[256];
+        part[threadIdx.x] = s;
+        __syncthreads();
+        if (g == 0) {
+#pragma unroll
+            for (int q = 1; q < G; ++q) {
+                s.re += part[q * E + e].re;
+                s.im += part[q * E + e].im;
+            }
+            th[i * (NN + 1) + j] = s;
+        }
+    }
+}
+
+// lane j: column j of the Hermitian part of t
+template <int NN> __device__ __forceinline__ void herm_column(const Z2* t, int j, Z2 A[NN]) {
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+        const Z2 a = t[i * (NN + 1) + j], b = t[j * (NN + 1) + i];
+        A[i] = Z2{0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
+    }
+}
+
+// 1 / d and 1 / sqrt(d) for a positive normal d: the hardware estimate and two Newton
+// steps (the pivots are a serial chain, and the IEEE division is twice as long)
+__device__ __forceinline__ double rcp_nr(double d) {
+    double x = __builtin_amdgcn_rcp(d);
+    x = fma(x, fma(-d, x, 1.0), x);
+    return fma(x, fma(-d, x, 1.0), x);
+}
+__device__ __forceinline__ double rsqrt_nr(double d) {
+    double x = __builtin_amdgcn_rsq(d);
+    x = fma(0.5 * x, fma(-d * x, x, 1.0), x);
+    return fma(0.5 * x, fma(-d * x, x, 1.0), x);
+}
+
+// A = L1 D L1^H with L1 unit lower triangular, and Z = L1^{-1}.  On return lane k holds
+// L1[i][k] d_k in register i >= k of A (its upper triangle is not meaningful), d[k] = d_k,
+// id[k] = 1 / d_k.  False if a pivot is not positive and finite.
+template <int NN> __device__ __forceinline__ bool ldl16(Z2 A[NN], Z2 Z[NN], double d[NN], double id[NN], int lane) {
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) Z[i] = Z2{i == lane ? 1.0 : 0.0, 0.0};
+    unroll<NN>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        d[k] = row_bcast<k>(A[k].re);
+        ok = ok && d[k] > 0.0 && isfinite(d[k]);
+        id[k] = rcp_nr(d[k]);
+        if constexpr (k + 1 < NN) {
+            const double s = lane > k ? id[k] : 0.0;
+            const Z2 m{A[k].re * s, A[k].im * s};
+            const Z2 mz{-Z[k].re * id[k], -Z[k].im * id[k]};
+            constexpr int q0 = (k + 1) / 4, r0 = 4 - (k + 1) % 4;  // first group of four rows, its rows past k
+            unroll<NN / 4 - q0>([&](auto qc) { row_elim4<k>(A + 4 * (q0 + decltype(qc)::value), m); });
+            row_mac<r0, k>(Z + k + 1, A + k + 1, mz);
+            unroll<NN / 4 - q0 - 1>([&](auto qc) {
+                constexpr int i = 4 * (q0 + 1 + decltype(qc)::value);
+                row_mac<4, k>(Z + i, A + i, mz);
+            });
+        }
+    });
+    return ok;
+}
+
+// f(integral_constant<int, w>) for the wave's own w < W
+template <int W, typename F> __device__ __forceinline__ void wave_case(int w, F&& f) {
+    unroll<W>([&](auto wc) {
+        if (w == decltype(wc)::value) f(wc);
+    });
+}
+
+// k_small1 (phase 1) and k_small2 (phase 2) on a row of lanes, one kernel
+// so that both phases of an iteration run the same factorisation code: straight-line code
+// of some 10 KB, which costs more to fetch than to execute when it is cold.
+// Phase 1: out1 = beta, out2 = beta C.  Phase 2: out1 = S^{-1}, out2 = S^H, C updated.
+template <int NN>
+__global__ void __launch_bounds__(256)
+k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restrict__ C, double2* __restrict__ out1,
+            double2* __restrict__ out2, SolveState* st, int N) {
+    __shared__ Z2 th[NN * (NN + 1)], tc[NN * (NN + 1)];
+    __shared__ double tn[4][NN];
+    const int j = threadIdx.x & (NN - 1);
+    const int halt = st->halt, iters = st->iters, best_it0 = st->best_it, ru_window = st->ru_window;
+    const double tol = st->tol, best0 = st->best_relres, ru_delta = st->ru_delta, rho_ru = st->rho_ru;
+    const double bn = st->bnorm[j];
+    stage16<NN>(H, P, C, N, th, tc);
+    if (halt) {
+        if (phase2 && threadIdx.x == 0) st->pb_mode = PB_SKIP;
+        return;
+    }
+    __syncthreads();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Z2 A[NN];
+    herm_column<NN>(th, j, A);
+    if (phase2) {
+        // (C^H H C)_jj, rows m = 4 w ... 4 w + 3 of H C by wave w
+        wave_case<NN / 4>(w, [&](auto wc) {
+            constexpr int m0 = 4 * decltype(wc)::value;
+            Z2 hc[4] = {};
+            unroll<NN>([&](auto nc) {
+                constexpr int n = decltype(nc)::value;
+                row_mac<4, n>(hc, A + m0, tc[n * (NN + 1) + j]);
+            });
+            double t = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const Z2 c = tc[(m0 + r) * (NN + 1) + j];
+                t += c.re * hc[r].re + c.im * hc[r].im;
+            }
+            tn[m0 / 4][j] = t;
+        });
+        __syncthreads();
+        if (w >= NN / 4) return;
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < NN / 4; ++q) t += tn[q][j];
+        const double rel = j < N ? sqrt(fmax(t, 0.0)) / bn : 0.0;
+        double mx = rel;
+#pragma unroll
+        for (int off = NN / 2; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, NN));
+        // stopping and reliable-update tests, as k_small2 (every wave reaches the same decision)
+        const int it = iters + 1, best_it = mx < best0 ? it : best_it0;
+        const bool conv = mx <= tol;
+        const bool ru = (ru_delta > 0.0 && mx <= ru_delta * rho_ru) || (ru_window > 0 && it - best_it >= ru_window);
+        const int decision = conv ? HALT_CONVERGED : (ru ? HALT_RU : HALT_NONE);
+        if (threadIdx.x < NN && j < N) st->relres[j] = rel;
+        if (threadIdx.x == 0) {
+            st->max_relres = mx;
+            st->iters = it;
+            if (mx < best0) {
+                st->best_relres = mx;
+                st->best_it = it;
+            }
+            if (decision != HALT_NONE) {
+                st->halt = 1;
+                st->reason = decision;
+                st->pb_mode = PB_X_ONLY;
+            }
+        }
+        if (decision != HALT_NONE) return;
+    } else if (w >= NN / 4) {
+        return;
+    }
+    Z2 Z[NN];
+    double d[NN], id[NN];
+    if (!ldl16<NN>(A, Z, d, id, j)) {
+        if (threadIdx.x == 0) {
+            st->halt = 1;
+            st->reason = phase2 ? HALT_BREAKDOWN_H : HALT_BREAKDOWN_G;
+            if (phase2) st->pb_mode = PB_X_ONLY;
+        }
+        return;
+    }
+    const bool mine = (threadIdx.x & 63) < NN && j < N;
+    if (!phase2) {
+        wave_case<NN / 4>(w, [&](auto wc) {
+            // rows i = 4 w ... 4 w + 3 of beta = Z^H D^{-1} Z (Z[k][i] = 0 for k < i)
+            constexpr int i0 = 4 * decltype(wc)::value;
+            Z2 b[4] = {}, bc[4] = {};
+            unroll<NN - i0>([&](auto kc) {
+                constexpr int k = i0 + decltype(kc)::value;
+                constexpr int R = k - i0 + 1 < 4 ? k - i0 + 1 : 4;
+                row_cmac<R, i0>(b, Z[k], Z2{Z[k].re * id[k], Z[k].im * id[k]});
+            });
+            unroll<NN>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                row_mac<4, m>(bc, b, tc[m * (NN + 1) + j]);
+            });
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (mine && i0 + r < N) {
+                    gst(out1 + (i0 + r) * MAXN + j, b[r]);
+                    gst(out2 + (i0 + r) * MAXN + j, bc[r]);
+                }
+        });
+        return;
+    }
+    double dj = d[0];
+#pragma unroll
+    for (int k = 1; k < NN; ++k) dj = j == k ? d[k] : dj;
+    const double rj = rsqrt_nr(dj);
+    wave_case<NN / 4>(w, [&](auto wc) {
+        // rows i = 4 w ... of S = L^H, C <- S C = D^{-1/2} (L1 D)^H C, S^{-1} = (D^{-1/2} Z)^H
+        constexpr int i0 = 4 * decltype(wc)::value;
+        Z2 s[4] = {};
+        unroll<NN - i0>([&](auto mc) {
+            constexpr int m = i0 + decltype(mc)::value;
+            constexpr int R = m - i0 + 1 < 4 ? m - i0 + 1 : 4;
+            row_cmac<R, i0>(s, A[m], tc[m * (NN + 1) + j]);
+        });
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + r;
+            const double ri = rsqrt_nr(d[i]);
+            if (mine && i < N) {
+                gst(C + i * MAXN + j, j >= i ? Z2{s[r].re * ri, s[r].im * ri} : Z2{0.0, 0.0});
+                gst(out2 + i * MAXN + j, i > j ? Z2{A[i].re * rj, A[i].im * rj} : Z2{i == j ? dj * rj : 0.0, 0.0});
+                // row j of S^{-1}: conj(L^{-1}[i][j]), column i
+                gst(out1 + j * MAXN + i, j <= i ? Z2{Z[i].re * ri, -Z[i].im * ri} : Z2{0.0, 0.0});
+            }
+        }
+    });
+    if (threadIdx.x == 0) st->pb_mode = PB_FULL;
+}
+
 // End of a reliable update: with C^ in SH (upper) and C_k in C, S^ = C^ C_k^{-1},
 // C <- C^, SH <- S^^H, and the iteration resumes.  A, W: LDS N x N scratch.
 __device__ void ru_set_s(double2* __restrict__ C, double2* __restrict__ SH, Z2* A, Z2* W, SolveState* st,
@@ -950,12 +1202,24 @@ hipError_t launch_sstep_coef(const double2* Gv, const double2* Gvv, const double
     return hipGetLastError();
 }
 hipError_t launch_small1(const double2* G, const double2* C, double2* beta, double2* betaC,
-                         SolveState* st, int N, int req, hipStream_t s) {
+                         SolveState* st, int N, int req, int parts, hipStream_t s) {
+    if (N <= 16 && req == 0) {
+        auto k = N <= 8 ? k_small_row<8> : k_small_row<16>;
+        hipLaunchKernelGGL(k, dim3(1), dim3(256), 0, s, false, G, parts, const_cast<double2*>(C), beta, betaC, st, N);
+        return hipGetLastError();
+    }
+    if (parts) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_small1, dim3(1), dim3(small_threads(N, req)), small_lds(N), s, G, C, beta, betaC, st, N);
     return hipGetLastError();
 }
 hipError_t launch_small2(const double2* H, double2* C, double2* Sinv, double2* SH, SolveState* st,
-                         int N, int req, hipStream_t s) {
+                         int N, int req, int parts, hipStream_t s) {
+    if (N <= 16 && req == 0) {
+        auto k = N <= 8 ? k_small_row<8> : k_small_row<16>;
+        hipLaunchKernelGGL(k, dim3(1), dim3(256), 0, s, true, H, parts, C, Sinv, SH, st, N);
+        return hipGetLastError();
+    }
+    if (parts) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_small2, dim3(1), dim3(small_threads(N, req)), small_lds(N), s, H, C, Sinv, SH, st, N);
     return hipGetLastError();
 }
