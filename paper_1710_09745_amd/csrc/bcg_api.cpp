@@ -368,9 +368,9 @@ bool fused_ok(bcg_ctx* ctx, Prec p, int N) {
 }
 
 int reduce(bcg_ctx* ctx, const double2* pa, int na, const double2* pb, int nb, double alpha, int N,
-           double2* out, const int* halt) {
+           double2* out, const int* halt, int ld = 0) {
     Prof pr(ctx, BCG_K_REDUCE);
-    HIPCK(launch_gram_reduce(pa, na, pb, nb, alpha, N, out, halt, ctx->stream));
+    HIPCK(launch_gram_reduce(pa, na, pb, nb, alpha, N, out, halt, ctx->stream, ld));
     return BCG_OK;
 }
 
@@ -437,7 +437,41 @@ struct BlockOps {
             Prof pr(ctx, BCG_K_GRAM);
             HIPCK(launch_gram_rows(p, A, B, N, Vh(), ord, ctx->partials, halt, ctx->stream));
         }
-        return reduce(ctx, ctx->partials, gram_rows_parts(N, Vh(), ord), nullptr, 0, 0.0, N, out, halt);
+        return reduce(ctx, ctx->partials, gram_rows_parts(N, Vh(), ord), nullptr, 0, 0.0, N, out, halt, row_ld(N));
+    }
+    // AP = 4 m^2 P - D T and its Gram with P, row layout: `parts` partials in ctx->partials
+    // for the small kernels to sum, or (parts = 0) P^H AP in out
+    int hop_gram(Prec p, const void* T, void* AP, const void* P, double2* out, int& parts, const int* halt) const {
+        parts = 0;
+        if (!hop_rows_gram(N, Vh())) {
+            RETCK(hop1(p, 0, T, AP, P, halt));
+            return gram_of(p, P, AP, out, halt);
+        }
+        {
+            const void* Wp = p == Prec::FP64 ? ctx->W64r[0] : ctx->Wslr[0];
+            Prof pr(ctx, BCG_K_HOP_EO, true);
+            HIPCK(launch_hop_gram_rows(p, ctx->nl, Wp, T, AP, P, 4.0 * ctx->mass * ctx->mass, N, ctx->g, ord, 0,
+                                       ctx->partials, halt, ctx->stream));
+        }
+        return sum_or_leave(hop_gram_parts(N, Vh(), ord), out, parts, halt);
+    }
+    // Qt = Q - AP beta and Qt^H Qt, as hop_gram
+    int pass_a_gram(Prec p, void* Q, const void* AP, const double2* beta, double2* out, int& parts,
+                    const int* halt) const {
+        {
+            Prof pr(ctx, BCG_K_PASS_A);
+            HIPCK(launch_pass_a_rows(p, Q, AP, beta, N, Vh(), ord, ctx->partials, halt, ctx->stream));
+        }
+        parts = 0;
+        if (!pass_a_rows_gram(N)) return gram_of(p, Q, Q, out, halt);
+        return sum_or_leave(gram_rows_parts(N, Vh(), ord), out, parts, halt);
+    }
+    int sum_or_leave(int n, double2* out, int& parts, const int* halt) const {
+        if (small_sums_parts(N, n, ctx->opt[BCG_OPT_SMALL_THREADS])) {
+            parts = n;
+            return BCG_OK;
+        }
+        return reduce(ctx, ctx->partials, n, nullptr, 0, 0.0, N, out, halt, row_ld(N));
     }
     int bmul(Prec px, const void* X, Prec py, const void* Z, void* Y, const double2* M, const int* skip) const {
         HIPCK(rows ? launch_bmul_rows(px, X, py, Z, Y, M, N, Vh(), ord, skip, ctx->stream)
@@ -1033,46 +1067,42 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     // one iteration of Alg. 1 on the ping-pong buffers c (P, Q) -> 1 - c (P', Q')
     auto iteration = [&](int c) -> int {
         void *P = Pb[c], *Q = Qb[c], *Pn = Pb[1 - c], *Qn = Qb[1 - c];
+        const int req = ctx->opt[BCG_OPT_SMALL_THREADS];
+        int parts = 0;  // Gram partials left for the N x N kernel to sum
         if (fuse) {
             RETCK(hop(ctx, ps, 1, P, T, nullptr, N, EPI_PLAIN_, halt, nullptr, ctx->part_tt));
             RETCK(hop(ctx, ps, 0, T, AP, P, N, EPI_MASS_, halt));
             RETCK(reduce(ctx, ctx->part_tt, n_tt, ctx->part_pp, n_pp, m2, N, M(ctx, M_G), halt));
         } else {
             RETCK(ops.hop1(ps, 1, P, T, nullptr, halt));
-            RETCK(ops.hop1(ps, 0, T, AP, P, halt));
-            RETCK(ops.gram_of(ps, P, AP, M(ctx, M_G), halt));
+            if (ops.rows) {
+                RETCK(ops.hop_gram(ps, T, AP, P, M(ctx, M_G), parts, halt));
+            } else {
+                RETCK(hop(ctx, ps, 0, T, AP, P, N, EPI_MASS_, halt));
+                RETCK(gram(ctx, ps, P, AP, N, M(ctx, M_G), halt));
+            }
         }
         {
             Prof pr(ctx, BCG_K_SMALL);
-            HIPCK(launch_small1(M(ctx, M_G), M(ctx, M_C), M(ctx, M_BETA), M(ctx, M_BETAC), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], 0, s));
+            HIPCK(launch_small1(parts ? ctx->partials : M(ctx, M_G), M(ctx, M_C), M(ctx, M_BETA), M(ctx, M_BETAC), st, N,
+                                req, parts, s));
         }
+        parts = 0;
         if (ops.rows) {
-            {
-                Prof pr(ctx, BCG_K_PASS_A);
-                HIPCK(launch_pass_a_rows(ps, Q, AP, M(ctx, M_BETA), N, Vh, ops.ord, ctx->partials, halt, s));
-            }
-            if (pass_a_rows_gram(N))
-                RETCK(reduce(ctx, ctx->partials, gram_rows_parts(N, Vh, ops.ord), nullptr, 0, 0.0, N, M(ctx, M_H), halt));
-            else
-                RETCK(ops.gram_of(ps, Q, Q, M(ctx, M_H), halt));
-        } else if (fuse) {
-            {
-                Prof pr(ctx, BCG_K_PASS_A);
-                HIPCK(launch_pass_a(ps, Q, AP, M(ctx, M_BETA), N, Vh, halt, ctx->partials, ctx->opt[BCG_OPT_PASS_CPT], bps64(ctx),
-                                      ctx->opt[BCG_OPT_PASS_KERNEL], s));
-            }
-            RETCK(reduce(ctx, ctx->partials, n_h, nullptr, 0, 0.0, N, M(ctx, M_H), halt));
+            RETCK(ops.pass_a_gram(ps, Q, AP, M(ctx, M_BETA), M(ctx, M_H), parts, halt));
         } else {
             {
                 Prof pr(ctx, BCG_K_PASS_A);
-                HIPCK(launch_pass_a(ps, Q, AP, M(ctx, M_BETA), N, Vh, halt, nullptr, ctx->opt[BCG_OPT_PASS_CPT], bps64(ctx),
-                                      ctx->opt[BCG_OPT_PASS_KERNEL], s));
+                HIPCK(launch_pass_a(ps, Q, AP, M(ctx, M_BETA), N, Vh, halt, fuse ? ctx->partials : nullptr,
+                                    ctx->opt[BCG_OPT_PASS_CPT], bps64(ctx), ctx->opt[BCG_OPT_PASS_KERNEL], s));
             }
-            RETCK(gram(ctx, ps, Q, Q, N, M(ctx, M_H), halt));
+            if (fuse) RETCK(reduce(ctx, ctx->partials, n_h, nullptr, 0, 0.0, N, M(ctx, M_H), halt));
+            else RETCK(gram(ctx, ps, Q, Q, N, M(ctx, M_H), halt));
         }
         {
             Prof pr(ctx, BCG_K_SMALL);
-            HIPCK(launch_small2(M(ctx, M_H), M(ctx, M_C), M(ctx, M_SINV), M(ctx, M_SH), st, N, ctx->opt[BCG_OPT_SMALL_THREADS], 0, s));
+            HIPCK(launch_small2(parts ? ctx->partials : M(ctx, M_H), M(ctx, M_C), M(ctx, M_SINV), M(ctx, M_SH), st, N,
+                                req, parts, s));
         }
         {
             Prof pr(ctx, BCG_K_PASS_B);

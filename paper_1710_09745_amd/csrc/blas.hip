@@ -450,8 +450,8 @@ k_gram_reduce(const double2* __restrict__ pa, int na, const double2* __restrict_
 constexpr int REDUCE_LPE = 32;
 
 hipError_t launch_gram_reduce(const double2* pa, int na, const double2* pb, int nb, double alpha, int N,
-                              double2* out, const int* halt, hipStream_t s) {
-    const int NBv = pad_n(N);
+                              double2* out, const int* halt, hipStream_t s, int ld) {
+    const int NBv = ld ? ld : pad_n(N);
     constexpr int EPW = 256 / REDUCE_LPE;
     const int grid = (NBv * NBv + EPW - 1) / EPW;
     hipLaunchKernelGGL(k_gram_reduce<REDUCE_LPE>, dim3(grid), dim3(256), 0, s, pa, na, pb, nb, alpha, NBv, N, out,

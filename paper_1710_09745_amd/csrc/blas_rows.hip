@@ -60,15 +60,6 @@ hipError_t launch_rows_to_canon(const double2* src, double2* dst, int N, int Vh,
 // v_mfma_f64_16x16x4f64 (lane l supplies A[l % 16][l / 16]) with the four sites as the
 // contraction index, so a Gram product needs neither LDS nor a second read of its block.
 // ---------------------------------------------------------------------------------------------
-typedef double dvec4 __attribute__((ext_vector_type(4)));
-
-// Site block of turn `it` of wave quad `wb` (of NWB) of workgroup g (of G): with an
-// order, the blocks of workgroup g's XCD.  -1 past the end.
-__device__ __forceinline__ int row_turn(int it, int g, int G, int NWB, int wb, int nb, const RowOrder& o) {
-    const int b = o.on ? ((it * (G >> 3) + (g >> 3)) * NWB + wb) * 8 + (g & 7) : (it * G + g) * NWB + wb;
-    return b < nb ? row_block(b, o) : -1;
-}
-
 // one wave's sites and columns
 template <typename S, int NT, bool HR> struct RowLane {
     int i;         // site (clamped)
@@ -103,71 +94,6 @@ __device__ __forceinline__ void row_product(C2<R> acc[3], const C2<R> v[3], F&& 
         }
     });
 }
-
-// Upper tiles of a Gram product A^H B (SAME: A = B), accumulated over sites.
-template <int NT, bool SAME> struct RowGram {
-    static constexpr int NUP = NT * (NT + 1) / 2;
-    dvec4 re[NUP], im[NUP];
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int u = 0; u < NUP; ++u) re[u] = im[u] = dvec4{0.0, 0.0, 0.0, 0.0};
-    }
-    // one colour of four sites (half rows: eight), tile t in ar[t], ai[t] and br, bi
-    __device__ __forceinline__ void add(const double* ar, const double* ai, const double* br, const double* bi) {
-        int u = 0;
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-            for (int b = a; b < NT; ++b, ++u) {
-                re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[a], br[b], re[u], 0, 0, 0);
-                re[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[a], bi[b], re[u], 0, 0, 0);
-                im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[a], bi[b], im[u], 0, 0, 0);
-                // A = B: the diagonal tile keeps M = Xr^T Xi, Im G = M - M^T at the end
-                if (!(SAME && a == b)) im[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai[a], br[b], im[u], 0, 0, 0);
-            }
-    }
-    // fixed-order sum of the workgroup's NW waves and the partial of this workgroup,
-    // leading dimension ld; red: NW x 512 doubles of LDS.  Half rows: the two 8 x 8
-    // diagonal blocks (the two sites of a row) are added.
-    template <int NW, bool HR>
-    __device__ __forceinline__ void finish(double* red, double2* __restrict__ out, int ld) {
-        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-        int u = 0;
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-            for (int b = a; b < NT; ++b, ++u) {
-                __syncthreads();
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int e = (4 * r + (lane >> 4)) * 16 + (lane & 15);
-                    red[w * 512 + e] = re[u][r];
-                    red[w * 512 + 256 + e] = im[u][r];
-                }
-                __syncthreads();
-                if (threadIdx.x < 256) {
-                    const int i = threadIdx.x >> 4, j = threadIdx.x & 15;
-                    if (!HR || (i < 8 && j < 8)) {
-                        double sr = 0.0, si = 0.0;
-#pragma unroll
-                        for (int h = 0; h < (HR ? 2 : 1); ++h) {
-                            const int e = (i + 8 * h) * 16 + j + 8 * h, et = (j + 8 * h) * 16 + i + 8 * h;
-                            for (int v = 0; v < NW; ++v) {
-                                sr += red[v * 512 + e];
-                                si += (SAME && a == b) ? red[v * 512 + 256 + e] - red[v * 512 + 256 + et]
-                                                       : red[v * 512 + 256 + e];
-                            }
-                        }
-                        const int gi = 16 * a + i, gj = 16 * b + j;
-                        out[gi * ld + gj] = make_double2(sr, si);
-                        if (a != b) out[gj * ld + gi] = make_double2(sr, -si);
-                    }
-                }
-            }
-    }
-};
-
-constexpr int ROW_NW = 8;  // waves per workgroup of the streaming kernels
 
 // Waves of a Gram workgroup: four from three tiles on, whose accumulators need more
 // than the 256 registers a lane has in a workgroup of eight.
@@ -550,23 +476,13 @@ k_colnorm2_rows(const double2* __restrict__ V, int N, int cp, long rows, double*
 // ---------------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------------
-static int row_blocks(int N, int Vh) { return N <= 8 ? (Vh + 31) / 32 : (Vh + 15) / 16; }
-
-// workgroups: at most `most`, a multiple of 8 when the blocks are walked per XCD
-static int row_grid(int nb, const RowOrder& o, int most, int nw = ROW_NW) {
-    const int nwb = nw / 4, g = (nb + nwb - 1) / nwb;
-    if (!o.on) return g < most ? g : most;
-    const int per = (nb / 8 + nwb - 1) / nwb;  // turns of one XCD
-    return 8 * (per < most / 8 ? per : most / 8);
-}
-
 static int gram_nw(int N) { return row_gram_nw(N <= 8 ? 1 : (N + 15) / 16); }
 int gram_rows_parts(int N, int Vh, const RowOrder& o) { return row_grid(row_blocks(N, Vh), o, GRAM_BLOCKS, gram_nw(N)); }
 
 template <typename S, bool SAME>
 static void gram_rows_go(const void* A, const void* B, int N, int Vh, const RowOrder& o, double2* part,
                          const int* halt, hipStream_t s) {
-    const int nb = row_blocks(N, Vh), ld = pad_n(N);
+    const int nb = row_blocks(N, Vh), ld = row_ld(N);
     const int nw = gram_nw(N);
     const dim3 grid(row_grid(nb, o, GRAM_BLOCKS, nw)), blk(64 * nw);
     const size_t lds = (size_t)nw * 512 * sizeof(double);
@@ -601,7 +517,7 @@ bool pass_a_rows_gram(int N) { return N <= 32; }
 template <typename S>
 static void pass_a_rows_go(void* Q, const void* AP, const double2* beta, int N, int Vh, const RowOrder& o,
                            double2* part, const int* halt, hipStream_t s) {
-    const int nb = row_blocks(N, Vh), ld = pad_n(N);
+    const int nb = row_blocks(N, Vh), ld = row_ld(N);
     const dim3 grid(row_grid(nb, o, GRAM_BLOCKS)), blk(64 * ROW_NW);
     const int np = N <= 8 ? 8 : (N + 15) / 16 * 16;
     const size_t cf = (size_t)np * np * sizeof(C2<typename S::real>), red = ROW_NW * 512 * sizeof(double);

@@ -46,36 +46,25 @@ __device__ __forceinline__ void row_matvec(C2<R> acc[3], const C2<R> w[9], const
     mac3<K, BM>(acc, w[2], w[5], w[8], v[2]);
 }
 
-// out = D in (MASS: m2 * ctr - D in) on one parity; D directions in flight, at least
-// WPS waves per SIMD.  Grid: (site blocks) x (tiles of 16 columns), the tiles of a
-// block next to each other on one XCD.
-template <typename S, int NL, bool MASS, bool HR, int D, int WPS>
-__global__ void __launch_bounds__(256, WPS)
-k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
-           const char* __restrict__ ctr, double m2d, int N, int nct, Geom g, RowOrder ord, int out_parity,
-           const int* __restrict__ halt) {
+// The hop at one block of sites (four waves) and column tile ct: acc = D in, or with MASS
+// acc = m2 * ctr - D in and z = ctr, at the lane's site and column.  D directions are in
+// flight at a time.
+template <typename S, int NL, bool MASS, bool HR, int D>
+__device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const char* __restrict__ in,
+                                               const char* __restrict__ ctr, double m2d, int N, const Geom& g,
+                                               int out_parity, int sb, int w, int ct, int lane,
+                                               C2<typename S::real> acc[3], C2<typename S::real> z[3], bool& stores,
+                                               size_t& out_off) {
     using R = typename S::real;
     constexpr int SPB = row_block_sites<HR>(), SPW = SPB / 4;
     constexpr unsigned WB = S::scaled ? 40u * NL : 9u * NL * S::bytes;  // link bytes of a site
-    if (halt != nullptr && *halt) return;
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int sb, ct;
-    if (ord.on) {
-        const int q = blockIdx.x >> 3;
-        ct = q % nct;
-        sb = row_block((q / nct) * 8 + (blockIdx.x & 7), ord);
-    } else {
-        sb = blockIdx.x / nct;
-        ct = blockIdx.x - sb * nct;
-    }
     const int i_w = sb * SPB + w * SPW;               // first site of the wave
     const int base = i_w < g.Vh ? i_w : g.Vh - 1;
     const int i0 = i_w + row_lane_site<HR>(lane);
     const bool live = i0 < g.Vh;
     const int i = live ? i0 : g.Vh - 1;               // spare lanes work on the last site and store nothing
     const int c0 = ct * 16 + row_lane_col<HR>(lane);
-    const bool stores = live && c0 < N;
+    stores = live && c0 < N;
     const int c = c0 < N ? c0 : N - 1;
     const rsrc_t wr = make_rsrc(W + (size_t)base * WB), vr = make_rsrc(in);
     const unsigned cs = row_cs<S>(N), ss = row_ss<S>(N), co = (unsigned)c * row_col_bytes<S>();
@@ -107,7 +96,8 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
     };
     RowRaw<S> v[D];
     static_for<D>([&](auto k) { fetch(v[k.value], k); });
-    C2<R> acc[3] = {c2<R>(0, 0), c2<R>(0, 0), c2<R>(0, 0)};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) acc[a] = c2<R>(0, 0);
     static_for<NL>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         __builtin_amdgcn_sched_barrier(0);
@@ -121,22 +111,78 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
         }
         if constexpr (k + D < NL) fetch(v[k % D], std::integral_constant<int, k + D>{});
     });
-    if (stores) {
-        const size_t o = (size_t)i * ss + co;
-        if constexpr (MASS) {
-            const R m2 = (R)m2d;
-            RowRaw<S> zr;
-            zr.load(make_rsrc(ctr), (unsigned)i * ss + co, cs);
-            C2<R> z[3];
-            zr.get(z);
+    out_off = (size_t)i * ss + co;
+    if constexpr (MASS) {
+        const R m2 = (R)m2d;
+        RowRaw<S> zr;
+        zr.load(make_rsrc(ctr), (unsigned)i * ss + co, cs);
+        zr.get(z);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                acc[a].re = m2 * z[a].re - acc[a].re;
-                acc[a].im = m2 * z[a].im - acc[a].im;
-            }
+        for (int a = 0; a < 3; ++a) {
+            acc[a].re = m2 * z[a].re - acc[a].re;
+            acc[a].im = m2 * z[a].im - acc[a].im;
         }
-        row_store<S, R>(out, o, cs, acc);
     }
+}
+
+// out = D in (MASS: m2 * ctr - D in) on one parity, at least WPS waves per SIMD.  Grid:
+// (site blocks) x (tiles of 16 columns), the tiles of a block next to each other on one XCD.
+template <typename S, int NL, bool MASS, bool HR, int D, int WPS>
+__global__ void __launch_bounds__(256, WPS)
+k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
+           const char* __restrict__ ctr, double m2d, int N, int nct, Geom g, RowOrder ord, int out_parity,
+           const int* __restrict__ halt) {
+    using R = typename S::real;
+    if (halt != nullptr && *halt) return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int sb, ct;
+    if (ord.on) {
+        const int q = blockIdx.x >> 3;
+        ct = q % nct;
+        sb = row_block((q / nct) * 8 + (blockIdx.x & 7), ord);
+    } else {
+        sb = blockIdx.x / nct;
+        ct = blockIdx.x - sb * nct;
+    }
+    C2<R> acc[3], z[3];
+    bool stores;
+    size_t o;
+    hop_rows_block<S, NL, MASS, HR, D>(W, in, ctr, m2d, N, g, out_parity, sb, w, ct, threadIdx.x & 63, acc, z, stores, o);
+    if (stores) row_store<S, R>(out, o, row_cs<S>(N), acc);
+}
+
+// out = m2 * ctr - D in and the Gram partials of ctr^H out (as stored), N <= 16: a lane
+// holds the two numbers of its (site, column) when it stores out, which is the operand
+// layout of the matrix instruction, so the Gram costs neither a launch nor a second read
+// of both blocks.  Persistent workgroups of NW waves over the site blocks.
+template <typename S, int NL, bool HR, int D, int WPS, int NW>
+__global__ void __launch_bounds__(64 * NW, WPS)
+k_hop_gram_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
+                const char* __restrict__ ctr, double m2d, int N, Geom g, RowOrder ord, int nb, int out_parity,
+                double2* __restrict__ partials, const int* __restrict__ halt) {
+    using R = typename S::real;
+    __shared__ double red[NW * 512];
+    if (halt != nullptr && *halt) return;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    RowGram<1, false> G;
+    G.zero();
+    int it = 0;
+    for (int sb; (sb = row_turn(it, blockIdx.x, gridDim.x, NW / 4, w >> 2, nb, ord)) >= 0; ++it) {
+        C2<R> acc[3], z[3];
+        bool stores;
+        size_t o;
+        hop_rows_block<S, NL, true, HR, D>(W, in, ctr, m2d, N, g, out_parity, sb, w & 3, 0, lane, acc, z, stores, o);
+        row_store_rt<S, R>(out, o, row_cs<S>(N), acc, stores);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double zr = stores ? (double)z[c].re : 0.0, zi = stores ? (double)z[c].im : 0.0;
+            const double ar = (double)acc[c].re, ai = (double)acc[c].im;
+            G.add(&zr, &zi, &ar, &ai);
+        }
+    }
+    constexpr int LD = HR ? 8 : 16;
+    G.template finish<NW, HR>(red, partials + (long)blockIdx.x * LD * LD, LD);
 }
 
 // Row-layout FP64 links of one parity from the canonical ones: a row of lanes per
@@ -266,7 +312,9 @@ hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh,
     return hipGetLastError();
 }
 
-bool rows_fit(int N, long Vh) { return N > 4 && N <= MAXN && (double)Vh * 3.0 * N * 16.0 < 4294967296.0; }
+bool rows_fit(int N, long Vh) {
+    return N >= 2 && N <= MAXN && (N > 4 || Vh <= ROWS_SMALL_SITES) && (double)Vh * 3.0 * N * 16.0 < 4294967296.0;
+}
 
 RowOrder row_order(const Geom& g, int N) {
     RowOrder o{};
@@ -304,6 +352,52 @@ static void hop_rows_go(const void* W, const void* in, void* out, const void* ct
     if (hr) GO(true, F ? 4 : 8, F ? 3 : 4);
     else GO(false, F ? 4 : 8, 4);
 #undef GO
+}
+
+constexpr int HOP_GRAM_NW = 8;
+// The fused Gram saves a launch and a read of both blocks, but its persistent workgroups
+// give up the overlap of one workgroup's start with another's end: 16^4, N = 16, FP64
+// 39 + 11.6 us apart, 41.3 us fused (N = 8: 24.4 + 6.9, 28.6); at 32^3 x 64, N = 16,
+// FP32 701 + 154 us apart and 825 to 909 us fused at any grid.
+bool hop_rows_gram(int N, int Vh) { return N <= 16 && Vh <= 65536; }
+int hop_gram_parts(int N, int Vh, const RowOrder& ord) {
+    return row_grid(row_blocks(N, Vh), ord, GRAM_BLOCKS, HOP_GRAM_NW);
+}
+
+template <typename S, int NL>
+static void hop_gram_rows_go(const void* W, const void* in, void* out, const void* ctr, double m2, int N,
+                             const Geom& g, const RowOrder& ord, int out_parity, double2* partials, const int* halt,
+                             hipStream_t s) {
+    constexpr bool F = std::is_same<S, F64>::value;
+    constexpr int NW = HOP_GRAM_NW;
+    const int nb = row_blocks(N, g.Vh);
+    const dim3 grid(hop_gram_parts(N, g.Vh, ord));
+#define GO(HRV, DV, WV)                                                                                            \
+    BCG_TIMED_LAUNCH((k_hop_gram_rows<S, NL, HRV, DV, WV, NW>), grid, dim3(64 * NW), 0, s, (const char*)W,         \
+                     (const char*)in, (char*)out, (const char*)ctr, m2, N, g, ord, nb, out_parity, partials, halt)
+    if (N <= 8) GO(true, F ? 2 : 8, F ? 2 : 4);
+    else GO(false, F ? 2 : 8, 4);
+#undef GO
+}
+
+hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr,
+                                double m2, int N, const Geom& g, const RowOrder& ord, int out_parity,
+                                double2* partials, const int* halt, hipStream_t s) {
+    if (!rows_fit(N, g.Vh) || !hop_rows_gram(N, g.Vh) || ctr == nullptr) return hipErrorInvalidValue;
+#define GO(S)                                                                                                       \
+    do {                                                                                                            \
+        if (nl == 16) hop_gram_rows_go<S, 16>(W, in, out, ctr, m2, N, g, ord, out_parity, partials, halt, s);       \
+        else hop_gram_rows_go<S, 8>(W, in, out, ctr, m2, N, g, ord, out_parity, partials, halt, s);                 \
+    } while (0)
+    switch (prec) {
+        case Prec::FP64: GO(F64); break;
+        case Prec::FP32: GO(F32); break;
+        case Prec::FP16: GO(H16); break;
+        case Prec::BF16: GO(B16); break;
+        case Prec::FX16: GO(X16); break;
+    }
+#undef GO
+    return hipGetLastError();
 }
 
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,

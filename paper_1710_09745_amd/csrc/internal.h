@@ -108,10 +108,17 @@ int hop_grid(const Geom& g, const HopShape& h, bool fused);
 enum { EPI_PLAIN_ = 0, EPI_MASS_ = 1, EPI_MASS_DOT_ = 2 };
 
 // hop_rows.hip ----------------------------------------------------------------------------------
-// whether N columns on Vh sites can use the row layout: more than 4 columns (below, a
-// row of lanes would be mostly idle and the links, which a plane layout streams just as
-// well, are most of the bytes) and FP64 vectors within 32-bit byte offsets
+// Whether N columns on Vh sites use the row layout: FP64 vectors within 32-bit byte
+// offsets, and more than 4 columns (below, a row of lanes is mostly idle and the links,
+// which the plane layout streams just as well, are most of the bytes), or 2 to 4 columns
+// on a lattice so small that the number of launches counts (us per block CG iteration,
+// FP64, N = 4, rows against planes: 41 / 53 at 4^4, 45 / 56 at 8^2 x 12^2, 61 / 67 at
+// 16^3 x 8, 93 / 87 at 16^4; an application, N = 2: 19 / 21, then 29 / 25 at 12^4; one
+// column is never faster in rows)
+constexpr long ROWS_SMALL_SITES = 8192;
 bool rows_fit(int N, long Vh);
+// leading dimension of the row kernels' Gram partials
+inline int row_ld(int N) { return N <= 8 ? 8 : pad_n(N); }
 RowOrder row_order(const Geom& g, int N);
 // FP64 row-layout links of one parity from the canonical ones; from those the FP64 plane
 // layout, and other storages
@@ -122,6 +129,14 @@ hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh,
 // out = D_{p,1-p} in, or with ctr: out = m2 ctr - D_{p,1-p} in
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
                            int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s);
+
+// the same with ctr, and hop_gram_parts partials (leading dimension row_ld(N)) of
+// ctr^H out, for hop_rows_gram(N, Vh)
+bool hop_rows_gram(int N, int Vh);
+int hop_gram_parts(int N, int Vh, const RowOrder& ord);
+hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr,
+                                double m2, int N, const Geom& g, const RowOrder& ord, int out_parity,
+                                double2* partials, const int* halt, hipStream_t s);
 
 // blas_rows.hip ---------------------------------------------------------------------------------
 // canonical [N][Vh][3] complex128 <-> FP64 row layout
@@ -156,8 +171,9 @@ hipError_t launch_gram(Prec prec, const void* A, const void* B, int N, int Vh, d
 // number of partials launch_gram writes
 int gram_parts(int N, int Vh, bool mfma);
 // out[i*64 + j] = sum_b pa[b][i*NB + j] + alpha * sum_b pb[b][i*NB + j]  (fixed order; pb may be NULL)
+// ld: leading dimension of the partials (0: pad_n(N))
 hipError_t launch_gram_reduce(const double2* pa, int na, const double2* pb, int nb, double alpha, int N,
-                              double2* out, const int* halt, hipStream_t s);
+                              double2* out, const int* halt, hipStream_t s, int ld = 0);
 // LDS bytes of a fused Gram epilogue of the streaming passes (0: does not fit, use launch_gram)
 size_t fused_tile_bytes(Prec prec, int N);
 int fused_grid(int Vh);
@@ -281,7 +297,10 @@ hipError_t launch_sstep_coef(const double2* Gv, const double2* Gvv, const double
                              const double2* Pv, double2* Bk, double2* alpha, double2* nalpha, int* status, int K,
                              int N, int first, hipStream_t s);
 // beta = G^{-1}, betaC = beta C.  parts > 0 (small_sums_parts only): G is that many Gram
-// partials of leading dimension pad_n(N), which the kernel sums itself
+// partials of leading dimension row_ld(N), which the kernel sums itself
+// whether the kernels of N columns sum `parts` Gram partials (leading dimension row_ld(N))
+// themselves rather than leave it to launch_gram_reduce
+bool small_sums_parts(int N, int parts, int req);
 hipError_t launch_small1(const double2* G, const double2* C, double2* beta, double2* betaC,
                          SolveState* st, int N, int req, int parts, hipStream_t s);
 // residual test, S from H = S^H S, Sinv, S^H, C <- S C; sets pb_mode / halt

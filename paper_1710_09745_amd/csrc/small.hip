@@ -611,23 +611,25 @@ template <int M, typename F> __device__ __forceinline__ void unroll(F&& f) {
 }
 
 // H (leading dimension MAXN, or the sum over p of P partials of leading dimension NN)
-// into LDS t[i][NN + 1], and C beside it, by 256 threads; the identity outside N x N
+// into LDS t[i][NN + 1], and C beside it, by SMALL_ROW_THREADS threads; the identity
+// outside N x N
+constexpr int SMALL_ROW_THREADS = 512;
 template <int NN>
 __device__ __forceinline__ void stage16(const double2* __restrict__ H, int P, const double2* __restrict__ C, int N,
                                         Z2* __restrict__ th, Z2* __restrict__ tc) {
-    constexpr int E = NN * NN, G = 256 / E;  // threads per entry
+    constexpr int E = NN * NN, G = SMALL_ROW_THREADS / E, U = 16;  // threads per entry, loads in flight
     const int e = threadIdx.x % E, g = threadIdx.x / E, i = e / NN, j = e % NN;
     const bool in = i < N && j < N;
     Z2 s{0.0, 0.0};
     if (P == 0) {
         if (in && g == 0) s = gld(H + i * MAXN + j);
     } else {
-        for (int p0 = g; p0 < P; p0 += 8 * G) {
-            double2 v[8];
+        for (int p0 = g; p0 < P; p0 += U * G) {
+            double2 v[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = p0 + u * G < P ? H[(long)(p0 + u * G) * E + e] : make_double2(0.0, 0.0);
+            for (int u = 0; u < U; ++u) v[u] = p0 + u * G < P ? H[(long)(p0 + u * G) * E + e] : make_double2(0.0, 0.0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < U; ++u) {
                 s.re += v[u].x;
                 s.im += v[u].y;
             }
@@ -639,7 +641,7 @@ __device__ __forceinline__ void stage16(const double2* __restrict__ H, int P, co
     if constexpr (G == 1) {
         th[i * (NN + 1) + j] = s;
     } else {
-        __shared__ Z2 part[256];
+        __shared__ Z2 part[SMALL_ROW_THREADS];
         part[threadIdx.x] = s;
         __syncthreads();
         if (g == 0) {
@@ -715,7 +717,7 @@ template <int W, typename F> __device__ __forceinline__ void wave_case(int w, F&
 // of some 10 KB, which costs more to fetch than to execute when it is cold.
 // Phase 1: out1 = beta, out2 = beta C.  Phase 2: out1 = S^{-1}, out2 = S^H, C updated.
 template <int NN>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(SMALL_ROW_THREADS)
 k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restrict__ C, double2* __restrict__ out1,
             double2* __restrict__ out2, SolveState* st, int N) {
     __shared__ Z2 th[NN * (NN + 1)], tc[NN * (NN + 1)];
@@ -1201,11 +1203,15 @@ hipError_t launch_sstep_coef(const double2* Gv, const double2* Gvv, const double
                        s, Gv, Gvv, Ga, Wp, Pv, Bk, alpha, nalpha, status, K, N, first);
     return hipGetLastError();
 }
+// One CU reads the partials at some tens of bytes per cycle, so beyond a few hundred KB
+// the many workgroups of k_gram_reduce win back their launch.
+bool small_sums_parts(int N, int parts, int req) { return req == 0 && N <= 16 && parts <= (N <= 8 ? 256 : 128); }
+
 hipError_t launch_small1(const double2* G, const double2* C, double2* beta, double2* betaC,
                          SolveState* st, int N, int req, int parts, hipStream_t s) {
     if (N <= 16 && req == 0) {
         auto k = N <= 8 ? k_small_row<8> : k_small_row<16>;
-        hipLaunchKernelGGL(k, dim3(1), dim3(256), 0, s, false, G, parts, const_cast<double2*>(C), beta, betaC, st, N);
+        hipLaunchKernelGGL(k, dim3(1), dim3(SMALL_ROW_THREADS), 0, s, false, G, parts, const_cast<double2*>(C), beta, betaC, st, N);
         return hipGetLastError();
     }
     if (parts) return hipErrorInvalidValue;
@@ -1216,7 +1222,7 @@ hipError_t launch_small2(const double2* H, double2* C, double2* Sinv, double2* S
                          int N, int req, int parts, hipStream_t s) {
     if (N <= 16 && req == 0) {
         auto k = N <= 8 ? k_small_row<8> : k_small_row<16>;
-        hipLaunchKernelGGL(k, dim3(1), dim3(256), 0, s, true, H, parts, C, Sinv, SH, st, N);
+        hipLaunchKernelGGL(k, dim3(1), dim3(SMALL_ROW_THREADS), 0, s, true, H, parts, C, Sinv, SH, st, N);
         return hipGetLastError();
     }
     if (parts) return hipErrorInvalidValue;
