@@ -72,7 +72,10 @@ template <typename S, int NT, bool HR> struct RowLane {
         cl = row_lane_col<HR>(lane);
     }
     __device__ __forceinline__ int col(int t) const { return t * 16 + cl; }
-    // byte offset of column tile t in storage T (columns past N: column N - 1)
+    // row_cs of column tile t, and its byte offset, in storage T (columns past N: column N - 1)
+    template <typename T> __device__ __forceinline__ unsigned cs(int t, int N) const {
+        return row_cs<T>(N, col(t) < N ? col(t) : N - 1);
+    }
     template <typename T> __device__ __forceinline__ unsigned off(int t, int N) const {
         const int c = col(t) < N ? col(t) : N - 1;
         return (unsigned)i * row_ss<T>(N) + (unsigned)c * row_col_bytes<T>();
@@ -111,7 +114,6 @@ k_gram_rows(const char* __restrict__ A, const char* __restrict__ B, int N, int V
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const rsrc_t ra = make_rsrc(A), rb = make_rsrc(B);
-    const unsigned cs = row_cs<S>(N);
     RowGram<NT, SAME> G;
     G.zero();
     RowLane<S, NT, HR> L;
@@ -123,8 +125,8 @@ k_gram_rows(const char* __restrict__ A, const char* __restrict__ B, int N, int V
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const unsigned o = L.template off<S>(t, N);
-            a[t].load(ra, o, cs);
-            if constexpr (!SAME) b[t].load(rb, o, cs);
+            a[t].load(ra, o, L.template cs<S>(t, N));
+            if constexpr (!SAME) b[t].load(rb, o, L.template cs<S>(t, N));
         }
     };
     int it = 0;
@@ -177,7 +179,6 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
     }
     __syncthreads();
     const rsrc_t rq = make_rsrc(Q), ra = make_rsrc(AP);
-    const unsigned cs = row_cs<S>(N);
     RowGram<GR ? NT : 1, true> G;
     if constexpr (GR) G.zero();
     RowLane<S, NT, HR> L;
@@ -190,8 +191,8 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const unsigned o = L.template off<S>(t, N);
-                a[t].load(ra, o, cs);
-                q[t].load(rq, o, cs);
+                a[t].load(ra, o, L.template cs<S>(t, N));
+                q[t].load(rq, o, L.template cs<S>(t, N));
             }
         };
         if (sb >= 0) fetch();
@@ -217,7 +218,7 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
                     qv[t][c].im -= acc[c].im;
                 }
                 const bool st = M.live && M.col(t) < N;
-                row_store_rt<S, R>(Q, M.template off<S>(t, N), cs, qv[t], st);
+                row_store_rt<S, R>(Q, M.template off<S>(t, N), M.template cs<S>(t, N), qv[t], st);
             }
             if constexpr (GR) {
 #pragma unroll
@@ -240,12 +241,12 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
 #pragma unroll 1
             for (int t = 0; t < NT; ++t) {
                 RowRaw<S> qr;
-                qr.load(rq, L.template off<S>(t, N), cs);
+                qr.load(rq, L.template off<S>(t, N), L.template cs<S>(t, N));
                 C2<R> acc[3] = {c2<R>(0, 0), c2<R>(0, 0), c2<R>(0, 0)};
 #pragma unroll 1
                 for (int lt = 0; lt < NT; ++lt) {
                     RowRaw<S> ar;
-                    ar.load(ra, L.template off<S>(lt, N), cs);
+                    ar.load(ra, L.template off<S>(lt, N), L.template cs<S>(lt, N));
                     C2<R> av[3];
                     ar.get(av);
                     const C2<R>* m = cf + lt * 16 * NP + t * 16 + L.cl;
@@ -258,7 +259,7 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
                     qv[c].re -= acc[c].re;
                     qv[c].im -= acc[c].im;
                 }
-                row_store_rt<S, R>(Q, L.template off<S>(t, N), cs, qv, L.live && L.col(t) < N);
+                row_store_rt<S, R>(Q, L.template off<S>(t, N), L.template cs<S>(t, N), qv, L.live && L.col(t) < N);
             }
         }
     }
@@ -303,7 +304,6 @@ k_pass_b_rows(double2* __restrict__ X, const char* __restrict__ Qt, const char* 
     }
     __syncthreads();
     const rsrc_t rq = make_rsrc(Qt), rp = make_rsrc(P), rx = make_rsrc(X);
-    const unsigned cs = row_cs<S>(N), cx64 = row_cs<F64>(N);
     RowLane<S, NT, HR> L;
     // one operand tile into the sums of output tile jt
     auto tile = [&](int lt, int jt, const C2<R> pv[3], const C2<R> qv[3], C2<double> xa[3], C2<R> pa[3], C2<R> qa[3]) {
@@ -334,10 +334,10 @@ k_pass_b_rows(double2* __restrict__ X, const char* __restrict__ Qt, const char* 
             pa[c].re += qa[c].re;
             pa[c].im += qa[c].im;
         }
-        row_store<F64, double>(X, ox, cx64, x);
+        row_store<F64, double>(X, ox, L.template cs<F64>(jt, N), x);
         if (!full) return;
-        row_store<S, R>(Qn, o, cs, qa);
-        row_store<S, R>(Pn, o, cs, pa);
+        row_store<S, R>(Qn, o, L.template cs<S>(jt, N), qa);
+        row_store<S, R>(Pn, o, L.template cs<S>(jt, N), pa);
     };
     if constexpr (NT <= 2) {
         RowRaw<S> p[NT], q[NT];
@@ -349,9 +349,9 @@ k_pass_b_rows(double2* __restrict__ X, const char* __restrict__ Qt, const char* 
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const unsigned o = L.template off<S>(t, N);
-                p[t].load(rp, o, cs);
-                q[t].load(rq, o, cs);
-                x[t].load(rx, L.template off<F64>(t, N), cx64);
+                p[t].load(rp, o, L.template cs<S>(t, N));
+                q[t].load(rq, o, L.template cs<S>(t, N));
+                x[t].load(rx, L.template off<F64>(t, N), L.template cs<F64>(t, N));
             }
             C2<R> pv[NT][3], qv[NT][3];
 #pragma unroll
@@ -376,15 +376,15 @@ k_pass_b_rows(double2* __restrict__ X, const char* __restrict__ Qt, const char* 
 #pragma unroll 1
             for (int jt = 0; jt < NT; ++jt) {
                 RowRaw<F64> xr;
-                xr.load(rx, L.template off<F64>(jt, N), cx64);
+                xr.load(rx, L.template off<F64>(jt, N), L.template cs<F64>(jt, N));
                 C2<double> xa[3] = {};
                 C2<R> pa[3] = {}, qa[3] = {};
 #pragma unroll 1
                 for (int lt = 0; lt < NT; ++lt) {
                     RowRaw<S> pr, qr;
                     const unsigned o = L.template off<S>(lt, N);
-                    pr.load(rp, o, cs);
-                    if (lt <= jt) qr.load(rq, o, cs);
+                    pr.load(rp, o, L.template cs<S>(lt, N));
+                    if (lt <= jt) qr.load(rq, o, L.template cs<S>(lt, N));
                     C2<R> pv[3], qv[3];
                     pr.get(pv);
                     qr.get(qv);
@@ -415,7 +415,6 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
     }
     __syncthreads();
     const rsrc_t rx = make_rsrc(X), rz = make_rsrc(Z != nullptr ? Z : X);
-    const unsigned csx = row_cs<SX>(N), csy = row_cs<SY>(N);
     RowLane<SX, 4, HR> L;
     int it = 0;
     for (int sb; (sb = row_turn(it, blockIdx.x, gridDim.x, ROW_NW / 4, w >> 2, nb, ord)) >= 0; ++it) {
@@ -426,7 +425,7 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
 #pragma unroll 1
             for (int lt = 0; lt < nt; ++lt) {
                 RowRaw<SX> xr;
-                xr.load(rx, L.template off<SX>(lt, N), csx);
+                xr.load(rx, L.template off<SX>(lt, N), L.template cs<SX>(lt, N));
                 C2<typename SX::real> xv[3];
                 xr.get(xv);
                 C2<double> xd[3];
@@ -439,7 +438,7 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
             const unsigned o = L.template off<SY>(t, N);
             if (Z != nullptr) {
                 RowRaw<SY> zr;
-                zr.load(rz, o, csy);
+                zr.load(rz, o, L.template cs<SY>(t, N));
                 C2<typename SY::real> z[3];
                 zr.get(z);
 #pragma unroll
@@ -448,7 +447,7 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
                     acc[c].im += (double)z[c].im;
                 }
             }
-            row_store<SY, double>(Y, o, csy, acc);
+            row_store<SY, double>(Y, o, L.template cs<SY>(t, N), acc);
         }
     }
 }

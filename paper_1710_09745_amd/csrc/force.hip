@@ -86,7 +86,7 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
     // fields at x (parity p) and at y (parity 1 - p)
     const rsrc_t ru1 = make_rsrc(p == 0 ? Lam : YX), ru2 = make_rsrc(p == 0 ? X : YL);
     const rsrc_t rv1 = make_rsrc(p == 0 ? YX : Lam), rv2 = make_rsrc(p == 0 ? YL : X);
-    const unsigned cs = row_cs<F64>(N), ss = row_ss<F64>(N);
+    const unsigned cs = row_cs<F64>(N, 0), ss = row_ss<F64>(N);
     unsigned co[NT];
     C2<double> u1[NT][3], u2[NT][3];
 #pragma unroll

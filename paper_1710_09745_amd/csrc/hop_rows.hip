@@ -1,4 +1,4 @@
-// Multi-right-hand-side staggered hop in the row layout (rows.h), for N > 4 columns.
+// Multi-right-hand-side staggered hop in the row layout (rows.h).
 //
 // The hop is bound by what it moves: the 16 neighbour vectors of a site pass through
 // L1 once each, and past L2 as often as the caches miss.  With lanes across columns a
@@ -17,7 +17,8 @@
 namespace bcg {
 
 // The folded link entries of a site as a row's lanes hold them: lane k matrix k.
-template <typename S, int NL> struct RowLinks {
+template <typename S, int NL, bool NT> struct RowLinks {
+    static constexpr int AUX = NT ? AUX_NT : AUX_NONE;
     C2<typename S::real> w[9];
     // base: links of the wave's first site (uniform), site: offset of the lane's site
     __device__ __forceinline__ void load(rsrc_t r, unsigned site, int lane) {
@@ -25,36 +26,31 @@ template <typename S, int NL> struct RowLinks {
         if constexpr (!S::scaled) {
             const unsigned o = site * (9u * NL * S::bytes) + k * S::bytes;
 #pragma unroll
-            for (int e = 0; e < 9; ++e) w[e] = buf_pair<AUX_NONE>(r, o, e * (NL * S::bytes), (typename S::real)0);
+            for (int e = 0; e < 9; ++e) w[e] = buf_pair<AUX>(r, o, e * (NL * S::bytes), (typename S::real)0);
         } else {
             const unsigned o = site * (10u * NL * 4u) + k * 4u;
             unsigned u[10];
 #pragma unroll
-            for (int e = 0; e < 10; ++e) u[e] = __builtin_amdgcn_raw_buffer_load_b32(r, o, e * (NL * 4), AUX_NONE);
-            const float s = __builtin_bit_cast(float, u[9]);
+            for (int e = 0; e < 10; ++e) u[e] = __builtin_amdgcn_raw_buffer_load_b32(r, o, e * (NL * 4), AUX);
+            const float s = row_scale<S>(__builtin_bit_cast(float, u[9]));
 #pragma unroll
             for (int e = 0; e < 9; ++e)
-                w[e] = C2<float>{S::dec((unsigned short)(u[e] & 0xffffu)) * s, S::dec((unsigned short)(u[e] >> 16)) * s};
+                w[e] = C2<float>{row_dec<S>((unsigned short)(u[e] & 0xffffu)) * s, row_dec<S>((unsigned short)(u[e] >> 16)) * s};
         }
     }
 };
 
-template <int K, int BM, typename R>
-__device__ __forceinline__ void row_matvec(C2<R> acc[3], const C2<R> w[9], const C2<R> v[3]) {
-    mac3<K, BM>(acc, w[0], w[3], w[6], v[0]);
-    mac3<K, BM>(acc, w[1], w[4], w[7], v[1]);
-    mac3<K, BM>(acc, w[2], w[5], w[8], v[2]);
-}
-
-// The hop at one block of sites (four waves) and column tile ct: acc = D in, or with MASS
-// acc = m2 * ctr - D in and z = ctr, at the lane's site and column.  D directions are in
-// flight at a time.
-template <typename S, int NL, bool MASS, bool HR, int D>
+// The hop at one block of sites (four waves) and the NT column tiles from column ct0 on:
+// acc = D in, or with MASS acc = m2 * ctr - D in and z = ctr, at the lane's site and
+// columns.  D directions are in flight at a time.  Two tiles share the links, the site's
+// coordinates and the neighbour offsets (16^3 x 48, N = 32, FP32: 217 -> 185 us for both
+// hops).
+template <typename S, int NL, bool MASS, bool HR, int NT, int D, bool LNT>
 __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const char* __restrict__ in,
                                                const char* __restrict__ ctr, double m2d, int N, const Geom& g,
-                                               int out_parity, int sb, int w, int ct, int lane,
-                                               C2<typename S::real> acc[3], C2<typename S::real> z[3], bool& stores,
-                                               size_t& out_off) {
+                                               int out_parity, int sb, int w, int ct0, int lane,
+                                               C2<typename S::real> acc[NT][3], C2<typename S::real> z[NT][3],
+                                               bool stores[NT], size_t out_off[NT], unsigned cs[NT]) {
     using R = typename S::real;
     constexpr int SPB = row_block_sites<HR>(), SPW = SPB / 4;
     constexpr unsigned WB = S::scaled ? 40u * NL : 9u * NL * S::bytes;  // link bytes of a site
@@ -63,12 +59,8 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
     const int i0 = i_w + row_lane_site<HR>(lane);
     const bool live = i0 < g.Vh;
     const int i = live ? i0 : g.Vh - 1;               // spare lanes work on the last site and store nothing
-    const int c0 = ct * 16 + row_lane_col<HR>(lane);
-    stores = live && c0 < N;
-    const int c = c0 < N ? c0 : N - 1;
     const rsrc_t wr = make_rsrc(W + (size_t)base * WB), vr = make_rsrc(in);
-    const unsigned cs = row_cs<S>(N), ss = row_ss<S>(N), co = (unsigned)c * row_col_bytes<S>();
-    RowLinks<S, NL> la, lb;
+    RowLinks<S, NL, LNT> la, lb;
     if constexpr (HR) {
         const int p0 = base + (lane >> 4) * 2;         // the row's two sites
         la.load(wr, (unsigned)((p0 < g.Vh ? p0 : g.Vh - 1) - base), lane & 15);
@@ -78,56 +70,80 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
     }
     int x[4];
     site_coords(g, i, out_parity, x);
-    const int st[4] = {1, g.L[0], g.L[0] * g.L[1], g.L[0] * g.L[1] * g.L[2]};
-    const int lex = x[0] + st[1] * x[1] + st[2] * x[2] + st[3] * x[3];
-    auto fetch = [&](RowRaw<S>& v, auto kc) {
+    const unsigned ss = row_ss<S>(N);
+    unsigned co[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int c0 = ct0 + 16 * t + row_lane_col<HR>(lane);
+        const int c = c0 < N ? c0 : N - 1;
+        stores[t] = live && c0 < N;
+        co[t] = (unsigned)c * row_col_bytes<S>();
+        cs[t] = row_cs<S>(N, c);
+    }
+    // Byte offset of a neighbour's first column: the site's own plus one of two uniform
+    // steps, the second around the lattice.  Along x the neighbours' pair index depends on
+    // whether x0 is odd.  (An extent of 2 takes the three-hop neighbour one hop away.)
+    const unsigned own = (unsigned)i * ss, own_x = own + ((x[0] & 1) ? ss : 0u);
+    const int half[4] = {0, g.L[0] / 2, g.L[0] / 2 * g.L[1], g.L[0] / 2 * g.L[1] * g.L[2]};
+    auto fetch = [&](RowRaw<S> v[NT], auto kc) {
         constexpr int k = decltype(kc)::value;
-        constexpr int mu = hop_mu<NL>(k), d = hop_d<NL>(k);
-        const int L = g.L[mu], wrap = L * st[mu];
-        int y = x[mu] + d, nbl = lex + d * st[mu];
-        if constexpr (d > 0) {
-            if (y >= L) { y -= L; nbl -= wrap; }
-            if (d == 3 && y >= L) nbl -= wrap;
+        constexpr int mu = hop_mu<NL>(k), d0 = hop_d<NL>(k), sg = d0 > 0 ? 1 : -1;
+        const int L = g.L[mu], d = (d0 == 3 || d0 == -3) && L == 2 ? sg : d0;
+        const bool around = d0 > 0 ? x[mu] >= L - d : x[mu] < -d;
+        unsigned o;
+        if constexpr (mu == 0) {
+            const int step = d > 0 ? (d - 1) / 2 : -((1 - d) / 2);
+            o = own_x + (around ? (unsigned)(step - sg * (L / 2)) * ss : (unsigned)step * ss);
         } else {
-            if (y < 0) { y += L; nbl += wrap; }
-            if (d == -3 && y < 0) nbl += wrap;
+            const unsigned step = (unsigned)(d * half[mu]) * ss, back = (unsigned)((d - sg * L) * half[mu]) * ss;
+            o = own + (around ? back : step);
         }
-        v.load(vr, (unsigned)(nbl >> 1) * ss + co, cs);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) v[t].load(vr, o + co[t], cs[t]);
     };
-    RowRaw<S> v[D];
+    RowRaw<S> v[D][NT];
     static_for<D>([&](auto k) { fetch(v[k.value], k); });
 #pragma unroll
-    for (int a = 0; a < 3; ++a) acc[a] = c2<R>(0, 0);
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) acc[t][a] = c2<R>(0, 0);
     static_for<NL>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         __builtin_amdgcn_sched_barrier(0);
-        C2<R> u[3];
-        v[k % D].get(u);
-        if constexpr (HR) {
-            row_matvec<k, 0x3>(acc, la.w, u);
-            row_matvec<k, 0xc>(acc, lb.w, u);
-        } else {
-            row_matvec<k, 0xf>(acc, la.w, u);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            C2<R> u[3];
+            v[k % D][t].get(u);
+            if constexpr (HR) {
+                row_matvec<k, 0x3>(acc[t], la.w, u);
+                row_matvec<k, 0xc>(acc[t], lb.w, u);
+            } else {
+                row_matvec<k, 0xf>(acc[t], la.w, u);
+            }
         }
         if constexpr (k + D < NL) fetch(v[k % D], std::integral_constant<int, k + D>{});
     });
-    out_off = (size_t)i * ss + co;
-    if constexpr (MASS) {
-        const R m2 = (R)m2d;
-        RowRaw<S> zr;
-        zr.load(make_rsrc(ctr), (unsigned)i * ss + co, cs);
-        zr.get(z);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            acc[a].re = m2 * z[a].re - acc[a].re;
-            acc[a].im = m2 * z[a].im - acc[a].im;
+    for (int t = 0; t < NT; ++t) {
+        out_off[t] = (size_t)i * ss + co[t];
+        if constexpr (MASS) {
+            const R m2 = (R)m2d;
+            RowRaw<S> zr;
+            zr.load(make_rsrc(ctr), (unsigned)i * ss + co[t], cs[t]);
+            zr.get(z[t]);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                acc[t][a].re = m2 * z[t][a].re - acc[t][a].re;
+                acc[t][a].im = m2 * z[t][a].im - acc[t][a].im;
+            }
         }
     }
 }
 
 // out = D in (MASS: m2 * ctr - D in) on one parity, at least WPS waves per SIMD.  Grid:
-// (site blocks) x (tiles of 16 columns), the tiles of a block next to each other on one XCD.
-template <typename S, int NL, bool MASS, bool HR, int D, int WPS>
+// (site blocks) x (groups of NT tiles of 16 columns), the groups of a block next to each
+// other on one XCD; a last group of one tile takes the one-tile code.
+template <typename S, int NL, bool MASS, bool HR, int NT, int D, int WPS, bool LNT>
 __global__ void __launch_bounds__(256, WPS)
 k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
            const char* __restrict__ ctr, double m2d, int N, int nct, Geom g, RowOrder ord, int out_parity,
@@ -144,11 +160,22 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
         sb = blockIdx.x / nct;
         ct = blockIdx.x - sb * nct;
     }
-    C2<R> acc[3], z[3];
-    bool stores;
-    size_t o;
-    hop_rows_block<S, NL, MASS, HR, D>(W, in, ctr, m2d, N, g, out_parity, sb, w, ct, threadIdx.x & 63, acc, z, stores, o);
-    if (stores) row_store<S, R>(out, o, row_cs<S>(N), acc);
+    auto tiles = [&](auto ntc) {
+        constexpr int T = decltype(ntc)::value;
+        C2<R> acc[T][3], z[T][3];
+        bool stores[T];
+        size_t o[T];
+        unsigned cs[T];
+        hop_rows_block<S, NL, MASS, HR, T, T == NT ? D : 2 * D, LNT>(W, in, ctr, m2d, N, g, out_parity, sb, w,
+                                                                     16 * NT * ct, threadIdx.x & 63, acc, z, stores, o, cs);
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            if (stores[t]) row_store<S, R>(out, o[t], cs[t], acc[t]);
+    };
+    if constexpr (NT == 2) {
+        if (16 * NT * ct + 16 >= N) return tiles(std::integral_constant<int, 1>{});
+    }
+    tiles(std::integral_constant<int, NT>{});
 }
 
 // out = m2 * ctr - D in and the Gram partials of ctr^H out (as stored), N <= 16: a lane
@@ -169,15 +196,17 @@ k_hop_gram_rows(const char* __restrict__ W, const char* __restrict__ in, char* _
     G.zero();
     int it = 0;
     for (int sb; (sb = row_turn(it, blockIdx.x, gridDim.x, NW / 4, w >> 2, nb, ord)) >= 0; ++it) {
-        C2<R> acc[3], z[3];
-        bool stores;
-        size_t o;
-        hop_rows_block<S, NL, true, HR, D>(W, in, ctr, m2d, N, g, out_parity, sb, w & 3, 0, lane, acc, z, stores, o);
-        row_store_rt<S, R>(out, o, row_cs<S>(N), acc, stores);
+        C2<R> acc[1][3], z[1][3];
+        bool stores[1];
+        size_t o[1];
+        unsigned cs[1];
+        hop_rows_block<S, NL, true, HR, 1, D, false>(W, in, ctr, m2d, N, g, out_parity, sb, w & 3, 0, lane, acc, z,
+                                                     stores, o, cs);
+        row_store_rt<S, R>(out, o[0], cs[0], acc[0], stores[0]);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const double zr = stores ? (double)z[c].re : 0.0, zi = stores ? (double)z[c].im : 0.0;
-            const double ar = (double)acc[c].re, ai = (double)acc[c].im;
+            const double zr = stores[0] ? (double)z[0][c].re : 0.0, zi = stores[0] ? (double)z[0][c].im : 0.0;
+            const double ar = (double)acc[0][c].re, ai = (double)acc[0][c].im;
             G.add(&zr, &zi, &ar, &ai);
         }
     }
@@ -323,34 +352,51 @@ RowOrder row_order(const Geom& g, int N) {
     if (plane % spb) return o;
     const long bpp = plane / spb, nb = bpp * g.L[2] * g.L[3];
     if (nb % 8) return o;
-    // cells of up to 4 x 8 (z, t) that divide the lattice and each XCD's eighth
-    for (int bt : {8, 6, 4, 2, 1})
-        for (int bz : {4, 2, 1}) {
-            if (g.L[3] % bt || g.L[2] % bz || (nb / 8) % (bpp * bz * bt)) continue;
-            o.on = 1;
-            o.bpp = o.by = (int)bpp;
-            o.bz = bz;
-            o.bt = bt;
-            o.lz = g.L[2];
-            o.nb = (int)nb;
-            return o;
-        }
+    // Cells of up to 4 x 8 (z, t) that divide the lattice and each XCD's eighth, in y the
+    // whole plane while a cell's vectors fit an XCD's 4 MB L2 at 16 FP64 columns, else 4
+    // rows (both hops, us, whole planes / 4 rows: 16^4, N = 16, FP64 78.5 / 81.5, 16^3 x 48,
+    // N = 32 416 / 425; 24^4, N = 24 597 / 590, 32^3 x 64, N = 16, FP64 2653 / 2547, FP32
+    // 1217 / 1204)
+    const int y4 = (int)((2L * g.L[0] + spb - 1) / spb);  // blocks of 4 rows
+    for (int by : {bpp * spb > 256 ? y4 : (int)bpp, (int)bpp})
+        for (int bt : {8, 6, 4, 2, 1})
+            for (int bz : {4, 2, 1}) {
+                if (bpp % by || g.L[3] % bt || g.L[2] % bz || (nb / 8) % ((long)by * bz * bt)) continue;
+                o.on = 1;
+                o.bpp = (int)bpp;
+                o.by = by;
+                o.bz = bz;
+                o.bt = bt;
+                o.lz = g.L[2];
+                o.nb = (int)nb;
+                return o;
+            }
     return o;
 }
 
-template <typename S, int NL, bool MASS>
+// Links past the caches: with both parities' links beyond 200 MB (of 256 MB) no link stays
+// in the Infinity Cache from one hop of a parity to the next, and streaming loads leave
+// the room to the vectors (both hops, us, kept / streamed: 16^4, N = 16, FP64, 151 MB 69 /
+// 73; 16^3 x 48, N = 32, FP32, 226 MB 191 / 179; 32^3 x 64, N = 16, FP32 1241 / 1198).
+static bool stream_links(Prec p, int nl, long Vh) {
+    return 2.0 * nl * Vh * (p == Prec::FP64 ? 144 : (p == Prec::FP32 ? 72 : 40)) > 200e6;
+}
+
+template <typename S, int NL, bool MASS, bool LNT>
 static void hop_rows_go(const void* W, const void* in, void* out, const void* ctr, double m2, int N, const Geom& g,
                         const RowOrder& ord, int out_parity, const int* halt, hipStream_t s) {
     constexpr bool F = std::is_same<S, F64>::value;
-    const bool hr = N <= 8;
-    const int nct = hr ? 1 : (N + 15) / 16;
-    const long nb = (g.Vh + (hr ? 31 : 15)) / (hr ? 32 : 16);
-    const dim3 grid((unsigned)(nb * nct));
-#define GO(HRV, DV, WV)                                                                                          \
-    BCG_TIMED_LAUNCH((k_hop_rows<S, NL, MASS, HRV, DV, WV>), grid, dim3(256), 0, s, (const char*)W, (const char*)in, \
-                     (char*)out, (const char*)ctr, m2, N, nct, g, ord, out_parity, halt)
-    if (hr) GO(true, F ? 4 : 8, F ? 3 : 4);
-    else GO(false, F ? 4 : 8, 4);
+    const long nb = row_blocks(N, g.Vh);
+#define GO(HRV, NTV, DV, WV)                                                                                         \
+    do {                                                                                                             \
+        const int nct = (N + 16 * NTV - 1) / (16 * NTV);                                                             \
+        const dim3 grid((unsigned)(nb * nct));                                                                       \
+        BCG_TIMED_LAUNCH((k_hop_rows<S, NL, MASS, HRV, NTV, DV, WV, LNT>), grid, dim3(256), 0, s, (const char*)W,    \
+                         (const char*)in, (char*)out, (const char*)ctr, m2, N, nct, g, ord, out_parity, halt);       \
+    } while (0)
+    if (N <= 8) GO(true, 1, F ? 4 : 8, F ? 3 : 4);
+    else if (N <= 16) GO(false, 1, F ? 4 : 8, 4);
+    else GO(false, 2, F ? 2 : 4, 4);
 #undef GO
 }
 
@@ -403,15 +449,21 @@ hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
                            int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s) {
     if (!rows_fit(N, g.Vh)) return hipErrorInvalidValue;
-#define GO(S)                                                                                                   \
-    do {                                                                                                        \
-        if (nl == 16) {                                                                                         \
-            if (ctr) hop_rows_go<S, 16, true>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);             \
-            else hop_rows_go<S, 16, false>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);                \
-        } else {                                                                                                \
-            if (ctr) hop_rows_go<S, 8, true>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);              \
-            else hop_rows_go<S, 8, false>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);                 \
-        }                                                                                                       \
+    const bool lnt = stream_links(prec, nl, g.Vh);
+#define GO3(S, NL, MASS)                                                                                  \
+    do {                                                                                                  \
+        if (lnt) hop_rows_go<S, NL, MASS, true>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);     \
+        else hop_rows_go<S, NL, MASS, false>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);        \
+    } while (0)
+#define GO(S)                               \
+    do {                                    \
+        if (nl == 16) {                     \
+            if (ctr) GO3(S, 16, true);      \
+            else GO3(S, 16, false);         \
+        } else {                            \
+            if (ctr) GO3(S, 8, true);       \
+            else GO3(S, 8, false);          \
+        }                                   \
     } while (0)
     switch (prec) {
         case Prec::FP64: GO(F64); break;
@@ -420,6 +472,7 @@ hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, voi
         case Prec::BF16: GO(B16); break;
         case Prec::FX16: GO(X16); break;
     }
+#undef GO3
 #undef GO
     return hipGetLastError();
 }

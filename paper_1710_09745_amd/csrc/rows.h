@@ -1,9 +1,13 @@
 // Row layout of block vectors and links, and the wave mapping its kernels share.
 //
 // The three colours of a site hold their N columns next to each other:
-//   vectors  FP64, FP32  [V/2][3][N] pairs
+//   vectors  FP64        [V/2][3][N] pairs
+//            FP32        [V/2] of {[N] of {c0, c1}, [N] of c2}: 16 and 8 bytes a column
 //            16-bit      [V/2][N] of {c0, c1, c2, scale}: the three packed colour
 //                        pairs of a (site, column) and their FP32 scale in 16 bytes
+//            (16 bytes to a lane where they can be: L1 answers four 128-byte runs of
+//            8 bytes a lane in some 23 cycles, eight of 16 bytes in some 33; both FP32
+//            hops at 32^3 x 64, N = 16: 1335 -> 1241 us)
 //   links    FP64, FP32  [V/2][9][NL] pairs: entry e = 3 a + b of the NL folded
 //                        matrices of a site side by side
 //            16-bit      [V/2][10][NL] words: the nine packed entries, then the scale
@@ -58,6 +62,64 @@ __device__ __forceinline__ void mac3(C2<float> acc[3], C2<float> w0, C2<float> w
 }
 #undef BCG_MAC3
 
+// acc += W v for the 3 x 3 matrix W that lane K of the row holds, as one block of 36
+// multiply-adds with one wait for all of them (24^4, N = 24, 16-bit, where the vector unit
+// is busy throughout: with the cheaper neighbour offsets 307 -> 284 us for both hops)
+#define BCG_MATVEC(T, BM)                                                                   \
+    asm("s_nop 1\n\t"                                                                       \
+        "v_fmac_" T "_dpp %0, %6, %24 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %2, %12, %24 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %4, %18, %24 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %6, %25 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %3, %12, %25 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %5, %18, %25 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %0, -%7, %25 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %2, -%13, %25 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %4, -%19, %25 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %7, %24 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %3, %13, %24 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %5, %19, %24 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %0, %8, %26 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %2, %14, %26 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %4, %20, %26 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %8, %27 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %3, %14, %27 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %5, %20, %27 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %0, -%9, %27 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %2, -%15, %27 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %4, -%21, %27 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %9, %26 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %3, %15, %26 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %5, %21, %26 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %0, %10, %28 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %2, %16, %28 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %4, %22, %28 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %10, %29 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %3, %16, %29 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %5, %22, %29 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %0, -%11, %29 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %2, -%17, %29 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %4, -%23, %29 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %1, %11, %28 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %3, %17, %28 row_newbcast:%30 row_mask:0xf bank_mask:" BM "\n\t" \
+        "v_fmac_" T "_dpp %5, %23, %28 row_newbcast:%30 row_mask:0xf bank_mask:" BM \
+        : "+&v"(acc[0].re), "+&v"(acc[0].im), "+&v"(acc[1].re), "+&v"(acc[1].im), "+&v"(acc[2].re), "+&v"(acc[2].im) \
+        : "v"(w[0].re), "v"(w[0].im), "v"(w[1].re), "v"(w[1].im), "v"(w[2].re), "v"(w[2].im), "v"(w[3].re), "v"(w[3].im), "v"(w[4].re), "v"(w[4].im), "v"(w[5].re), "v"(w[5].im), "v"(w[6].re), "v"(w[6].im), "v"(w[7].re), "v"(w[7].im), "v"(w[8].re), "v"(w[8].im), \
+          "v"(v[0].re), "v"(v[0].im), "v"(v[1].re), "v"(v[1].im), "v"(v[2].re), "v"(v[2].im), "n"(K))
+template <int K, int BM, typename R>
+__device__ __forceinline__ void row_matvec(C2<R> acc[3], const C2<R> w[9], const C2<R> v[3]) {
+    if constexpr (std::is_same<R, double>::value) {
+        if constexpr (BM == 0xf) BCG_MATVEC("f64", "0xf");
+        else if constexpr (BM == 0x3) BCG_MATVEC("f64", "0x3");
+        else BCG_MATVEC("f64", "0xc");
+    } else {
+        if constexpr (BM == 0xf) BCG_MATVEC("f32", "0xf");
+        else if constexpr (BM == 0x3) BCG_MATVEC("f32", "0x3");
+        else BCG_MATVEC("f32", "0xc");
+    }
+}
+#undef BCG_MATVEC
+
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, M - 1>)
 template <int... I, typename F> __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F&& f) {
     (f(std::integral_constant<int, I>{}), ...);
@@ -67,7 +129,8 @@ template <int M, typename F> __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // The three colours of one (site, column): as loaded, and decoded to the arithmetic
-// type.  off: byte offset of (site, column, colour 0), cs: bytes between colours.
+// type.  off: byte offset of (site, column), cs: bytes from there to the next colour
+// (FP64) or to the third (FP32), see row_cs.
 template <typename S> struct RowRaw {
     C2<typename S::real> v[3];
     __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned cs) {
@@ -79,27 +142,55 @@ template <typename S> struct RowRaw {
         for (int c = 0; c < 3; ++c) o[c] = v[c];
     }
 };
+// 16-bit components: stored number x group scale, with the unit 1 / 32767 of the fixed-point
+// format taken into the scale (one product per component instead of two)
+template <typename S> __device__ __forceinline__ float row_dec(unsigned short u) {
+    if constexpr (std::is_same<S, X16>::value) return (float)(short)u;
+    else return S::dec(u);
+}
+template <typename S> __device__ __forceinline__ float row_scale(float s) {
+    return std::is_same<S, X16>::value ? s * (1.0f / 32767.0f) : s;
+}
 template <typename S> struct RowRaw16 {
     uint4 u;
     __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned) {
         u = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX_NONE));
     }
     __device__ __forceinline__ void get(C2<float> o[3]) const {
-        const float s = __builtin_bit_cast(float, u.w);
+        const float s = row_scale<S>(__builtin_bit_cast(float, u.w));
         const unsigned p[3] = {u.x, u.y, u.z};
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            o[c] = C2<float>{S::dec((unsigned short)(p[c] & 0xffffu)) * s, S::dec((unsigned short)(p[c] >> 16)) * s};
+            o[c] = C2<float>{row_dec<S>((unsigned short)(p[c] & 0xffffu)) * s, row_dec<S>((unsigned short)(p[c] >> 16)) * s};
+    }
+};
+struct __attribute__((packed, aligned(8))) RowPair32 { float a, b, c, d; };  // {c0, c1} of a column
+template <> struct RowRaw<F32> {
+    C2<float> v[3];
+    __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned cs) {
+        const float4 p = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX_NONE));
+        v[0] = C2<float>{p.x, p.y};
+        v[1] = C2<float>{p.z, p.w};
+        v[2] = buf_pair<AUX_NONE>(r, off + cs, 0, 0.0f);
+    }
+    __device__ __forceinline__ void get(C2<float> o[3]) const {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = v[c];
     }
 };
 template <> struct RowRaw<H16> : RowRaw16<H16> {};
 template <> struct RowRaw<B16> : RowRaw16<B16> {};
 template <> struct RowRaw<X16> : RowRaw16<X16> {};
 
-// bytes between the columns of a site, between its colours, and between sites
-template <typename S> __device__ __forceinline__ constexpr unsigned row_col_bytes() { return S::scaled ? 16u : (unsigned)S::bytes; }
-template <typename S> __device__ __forceinline__ unsigned row_cs(int N) { return S::scaled ? 0u : (unsigned)N * S::bytes; }
-template <typename S> __device__ __forceinline__ unsigned row_ss(int N) { return S::scaled ? (unsigned)N * 16u : 3u * (unsigned)N * S::bytes; }
+// bytes between the columns of a site, from column c's entry to its next colour (FP32: its
+// third), and between sites
+template <typename S> __device__ __forceinline__ constexpr unsigned row_col_bytes() { return 16u; }
+template <typename S> __device__ __forceinline__ unsigned row_cs(int N, int c) {
+    if constexpr (S::scaled) return 0u;
+    else if constexpr (S::bytes == 8) return 16u * (unsigned)N - 8u * (unsigned)c;
+    else return 16u * (unsigned)N;
+}
+template <typename S> __device__ __forceinline__ unsigned row_ss(int N) { return (S::scaled ? 16u : 3u * S::bytes) * (unsigned)N; }
 
 // Store the three colours of a (site, column) in storage S if `st`; v becomes the
 // values as stored, so that a fused product sees what later kernels will load.
@@ -107,13 +198,21 @@ template <typename S, typename R>
 __device__ __forceinline__ void row_store_rt(void* base, size_t off, unsigned cs, C2<R> v[3], bool st) {
     char* p = reinterpret_cast<char*>(base) + off;
     if constexpr (!S::scaled) {
+        typename S::pair w[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            typename S::pair w;
-            w.x = (typename S::real)v[c].re;
-            w.y = (typename S::real)v[c].im;
-            if (st) *reinterpret_cast<typename S::pair*>(p + c * cs) = w;
-            v[c] = C2<R>{(R)w.x, (R)w.y};
+            w[c].x = (typename S::real)v[c].re;
+            w[c].y = (typename S::real)v[c].im;
+            v[c] = C2<R>{(R)w[c].x, (R)w[c].y};
+        }
+        if constexpr (S::bytes == 8) {
+            if (st) {
+                *reinterpret_cast<RowPair32*>(p) = RowPair32{w[0].x, w[0].y, w[1].x, w[1].y};
+                *reinterpret_cast<float2*>(p + cs) = w[2];
+            }
+        } else if (st) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) *reinterpret_cast<typename S::pair*>(p + c * cs) = w[c];
         }
     } else {
         float m = 0.0f;
@@ -125,7 +224,7 @@ __device__ __forceinline__ void row_store_rt(void* base, size_t off, unsigned cs
         for (int c = 0; c < 3; ++c) {
             const unsigned short lo = S::enc((float)v[c].re * inv), hi = S::enc((float)v[c].im * inv);
             u[c] = (unsigned)lo | ((unsigned)hi << 16);
-            v[c] = C2<R>{(R)(S::dec(lo) * m), (R)(S::dec(hi) * m)};
+            v[c] = C2<R>{(R)(row_dec<S>(lo) * row_scale<S>(m)), (R)(row_dec<S>(hi) * row_scale<S>(m))};
         }
         if (st) *reinterpret_cast<uint4*>(p) = make_uint4(u[0], u[1], u[2], __builtin_bit_cast(unsigned, m));
     }

@@ -30,6 +30,18 @@ def test_row_apply_matches_oracle(dims, improved, n):
     assert elem_rel_err(got, ref).max() <= 1e-12
 
 
+@pytest.mark.parametrize("dims,n", [((16, 16, 16, 24), 20), ((24, 24, 4, 8), 9)])
+def test_row_apply_on_larger_lattices(dims, n):
+    """Links past the caches (streamed), a second tile of 4 columns, and planes of more than
+    256 sites (cells of 4 rows)."""
+    fat, lng, B = inputs(dims, True, n, 11300 + n)
+    ctx = context(dims, True, fat, lng, 0.07)
+    op = oracle.Operator(dims, fat, lng, 0.07)
+    assert elem_rel_err(ctx.apply(to_dev(B)).cpu().numpy(), op.apply(B)).max() <= 1e-12
+    got = ctx.apply_prec("fp32", to_dev(B)).cpu().numpy()
+    assert site_scaled_err(got, emulated_sloppy_apply(op, "fp32", B)) <= SLOPPY_TOL["fp32"]
+
+
 @pytest.mark.parametrize("n", [2, 5])
 def test_reloaded_links_reach_both_layouts(n):
     """New links replace those of both layouts: the plane copy (up to 4 columns) is made
