@@ -344,11 +344,11 @@ int hop(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const v
 
 // the hop in the row layout (ctr as launch_hop_rows)
 int hop_rows(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const void* ctr, int N,
-             const int* halt) {
+             const int* halt, double* dots = nullptr) {
     const void* Wp = p == Prec::FP64 ? ctx->W64r[out_parity] : ctx->Wslr[out_parity];
     Prof pr(ctx, out_parity == 1 ? BCG_K_HOP_OE : BCG_K_HOP_EO, true);
     HIPCK(launch_hop_rows(p, ctx->nl, Wp, in, out, ctr, 4.0 * ctx->mass * ctx->mass, N, ctx->g, row_order(ctx->g, N),
-                          out_parity, halt, ctx->stream));
+                          out_parity, halt, ctx->stream, dots));
     return BCG_OK;
 }
 
@@ -1543,13 +1543,16 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
         if (chunk > ctx->max_iter - hp.iters) chunk = ctx->max_iter - hp.iters;
         for (int k = 0; k < chunk; ++k) {
             RETCK(ops.hop1(Prec::FP64, 1, P, T, nullptr, halt));
-            RETCK(ops.hop1(Prec::FP64, 0, T, AP, P, halt));
+            double* dots = reinterpret_cast<double*>(Rt);  // free between the checks of the true residual
+            if (ops.rows) RETCK(hop_rows(ctx, Prec::FP64, 0, T, AP, P, N, halt, dots));
+            else RETCK(ops.hop1(Prec::FP64, 0, T, AP, P, halt));
             Prof pr(ctx, BCG_K_CG_VEC);
-            HIPCK(launch_pb_dot(P, AP, N, Vh, ops.rows, ctx->nparts, st, s));
-            HIPCK(launch_pb_alpha(ctx->nparts, N, Vh, st, s));
-            HIPCK(launch_pb_update1(X, R, P, AP, N, Vh, ops.rows, ctx->nparts, st, s));
+            HIPCK(ops.rows ? launch_pb_dot_sum(dots, N, Vh, ctx->nparts, st, s)
+                           : launch_pb_dot(P, AP, N, Vh, ctx->nparts, st, s));
+            HIPCK(launch_pb_alpha(ctx->nparts, N, Vh, ops.rows, st, s));
+            HIPCK(launch_pb_update1(R, AP, N, Vh, ops.rows, ctx->nparts, st, s));
             HIPCK(launch_pb_beta(ctx->nparts, N, Vh, st, s));
-            HIPCK(launch_pb_update2(P, R, N, Vh, ops.rows, st, s));
+            HIPCK(launch_pb_update2(X, P, R, N, Vh, ops.rows, st, s));
         }
     }
     if (status != BCG_OK) {

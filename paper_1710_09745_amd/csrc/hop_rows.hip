@@ -143,12 +143,17 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
 // out = D in (MASS: m2 * ctr - D in) on one parity, at least WPS waves per SIMD.  Grid:
 // (site blocks) x (groups of NT tiles of 16 columns), the groups of a block next to each
 // other on one XCD; a last group of one tile takes the one-tile code.
-template <typename S, int NL, bool MASS, bool HR, int NT, int D, int WPS, bool LNT>
+//
+// DOT: also Re ctr^H out of each column over the block's sites, to dots[block][N], while
+// both are in registers (16^3 x 48, N = 24, FP64: the hop 167 -> 169 us, in place of a
+// 39 us pass over both blocks).
+template <typename S, int NL, bool MASS, bool HR, int NT, int D, int WPS, bool LNT, bool DOT>
 __global__ void __launch_bounds__(256, WPS)
 k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
            const char* __restrict__ ctr, double m2d, int N, int nct, Geom g, RowOrder ord, int out_parity,
-           const int* __restrict__ halt) {
+           double* __restrict__ dots, const int* __restrict__ halt) {
     using R = typename S::real;
+    __shared__ double red[DOT ? 4 * NT * 16 : 1];
     if (halt != nullptr && *halt) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int sb, ct;
@@ -171,6 +176,26 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
 #pragma unroll
         for (int t = 0; t < T; ++t)
             if (stores[t]) row_store<S, R>(out, o[t], cs[t], acc[t]);
+        if constexpr (DOT) {
+            constexpr int TW = HR ? 8 : 16;
+            const int lane = threadIdx.x & 63;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                double d = 0.0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) d += (double)z[t][c].re * acc[t][c].re + (double)z[t][c].im * acc[t][c].im;
+                if (!stores[t]) d = 0.0;
+#pragma unroll
+                for (int off = 32; off >= TW; off >>= 1) d += __shfl_xor(d, off, 64);
+                if (lane < TW) red[(t * 4 + w) * 16 + lane] = d;
+            }
+            __syncthreads();
+            const int t = threadIdx.x / TW, j = threadIdx.x % TW, c = 16 * (NT * ct + t) + j;
+            if (t < T && c < N) {
+                const double* r = red + t * 64 + j;
+                dots[(long)sb * N + c] = (r[0] + r[16]) + (r[32] + r[48]);
+            }
+        }
     };
     if constexpr (NT == 2) {
         if (16 * NT * ct + 16 >= N) return tiles(std::integral_constant<int, 1>{});
@@ -384,20 +409,31 @@ static bool stream_links(Prec p, int nl, long Vh) {
 
 template <typename S, int NL, bool MASS, bool LNT>
 static void hop_rows_go(const void* W, const void* in, void* out, const void* ctr, double m2, int N, const Geom& g,
-                        const RowOrder& ord, int out_parity, const int* halt, hipStream_t s) {
+                        const RowOrder& ord, int out_parity, double* dots, const int* halt, hipStream_t s) {
     constexpr bool F = std::is_same<S, F64>::value;
     const long nb = row_blocks(N, g.Vh);
-#define GO(HRV, NTV, DV, WV)                                                                                         \
+#define GO2(HRV, NTV, DV, WV, DOT)                                                                                   \
     do {                                                                                                             \
         const int nct = (N + 16 * NTV - 1) / (16 * NTV);                                                             \
         const dim3 grid((unsigned)(nb * nct));                                                                       \
-        BCG_TIMED_LAUNCH((k_hop_rows<S, NL, MASS, HRV, NTV, DV, WV, LNT>), grid, dim3(256), 0, s, (const char*)W,    \
-                         (const char*)in, (char*)out, (const char*)ctr, m2, N, nct, g, ord, out_parity, halt);       \
+        BCG_TIMED_LAUNCH((k_hop_rows<S, NL, MASS, HRV, NTV, DV, WV, LNT, DOT>), grid, dim3(256), 0, s,               \
+                         (const char*)W, (const char*)in, (char*)out, (const char*)ctr, m2, N, nct, g, ord,          \
+                         out_parity, dots, halt);                                                                    \
+    } while (0)
+#define GO(HRV, NTV, DV, WV)                                       \
+    do {                                                           \
+        if constexpr (F && MASS) {                                 \
+            if (dots != nullptr) GO2(HRV, NTV, DV, WV, true);      \
+            else GO2(HRV, NTV, DV, WV, false);                     \
+        } else {                                                   \
+            GO2(HRV, NTV, DV, WV, false);                          \
+        }                                                          \
     } while (0)
     if (N <= 8) GO(true, 1, F ? 4 : 8, F ? 3 : 4);
     else if (N <= 16) GO(false, 1, F ? 4 : 8, 4);
     else GO(false, 2, F ? 2 : 4, 4);
 #undef GO
+#undef GO2
 }
 
 constexpr int HOP_GRAM_NW = 8;
@@ -447,13 +483,14 @@ hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in
 }
 
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
-                           int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s) {
-    if (!rows_fit(N, g.Vh)) return hipErrorInvalidValue;
+                           int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s,
+                           double* dots) {
+    if (!rows_fit(N, g.Vh) || (dots != nullptr && (prec != Prec::FP64 || ctr == nullptr))) return hipErrorInvalidValue;
     const bool lnt = stream_links(prec, nl, g.Vh);
 #define GO3(S, NL, MASS)                                                                                  \
     do {                                                                                                  \
-        if (lnt) hop_rows_go<S, NL, MASS, true>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);     \
-        else hop_rows_go<S, NL, MASS, false>(W, in, out, ctr, m2, N, g, ord, out_parity, halt, s);        \
+        if (lnt) hop_rows_go<S, NL, MASS, true>(W, in, out, ctr, m2, N, g, ord, out_parity, dots, halt, s);  \
+        else hop_rows_go<S, NL, MASS, false>(W, in, out, ctr, m2, N, g, ord, out_parity, dots, halt, s);     \
     } while (0)
 #define GO(S)                               \
     do {                                    \

@@ -127,8 +127,10 @@ hipError_t pack_links_rows(const void* fat, const void* lng, void* W, const Geom
 hipError_t row_links_to_planes(const void* Wr, void* Wp, int nl, long Vh, hipStream_t s);
 hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh, hipStream_t s);
 // out = D_{p,1-p} in, or with ctr: out = m2 ctr - D_{p,1-p} in
+// (dots, FP64 with ctr: also Re ctr^H out of each column and block of sites, [row_blocks][N])
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
-                           int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s);
+                           int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s,
+                           double* dots = nullptr);
 
 // the same with ctr, and hop_gram_parts partials (leading dimension row_ld(N)) of
 // ctr^H out, for hop_rows_gram(N, Vh)
@@ -254,7 +256,7 @@ struct PbState {
     int halt;
     int reason;
     int iters;        // lockstep iterations
-    int pad;
+    int step;         // alpha holds this iteration's step (not halted before it)
     double tol;
     double rr[64];
     double alpha[64];
@@ -265,13 +267,15 @@ struct PbState {
     int col_iters[64];
 };
 // (rows: blocks in the row layout, else planes)
-hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, bool rows, double* partials,
-                         const PbState* st, hipStream_t s);
-hipError_t launch_pb_alpha(const double* partials, int N, int Vh, PbState* st, hipStream_t s);
-hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh, bool rows,
-                             double* partials, const PbState* st, hipStream_t s);
+// partials of P^H AP per column, from both blocks (planes) or from the hop's block sums
+hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, double* partials, const PbState* st,
+                         hipStream_t s);
+hipError_t launch_pb_dot_sum(const double* dots, int N, int Vh, double* partials, const PbState* st, hipStream_t s);
+hipError_t launch_pb_alpha(const double* partials, int N, int Vh, bool rows, PbState* st, hipStream_t s);
+hipError_t launch_pb_update1(double2* R, const double2* AP, int N, int Vh, bool rows, double* partials,
+                             const PbState* st, hipStream_t s);
 hipError_t launch_pb_beta(const double* partials, int N, int Vh, PbState* st, hipStream_t s);
-hipError_t launch_pb_update2(double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
+hipError_t launch_pb_update2(double2* X, double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
                              hipStream_t s);
 // row layout: R and P take the true residual Rt on the columns with restart[j] != 0 (device flags)
 hipError_t launch_pb_restart_rows(double2* R, double2* P, const double2* Rt, int N, int Vh, const int* restart,

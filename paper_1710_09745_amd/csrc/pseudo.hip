@@ -10,11 +10,16 @@
 // Reductions are deterministic: one partial per (column, workgroup), summed in
 // a fixed order by a single-workgroup kernel (16 to 128 lanes per column).
 //
-// More than 4 columns are in the row layout ([Vh][3][N]): a thread keeps one column
-// for all of its rows (the threads of a workgroup cover whole rows), so that the loads
-// of a workgroup are one contiguous run and the per-column scalars stay in registers.
+// x is updated together with p, whose old value both need: the iteration reads P, X, R, AP
+// once each for 8 block transfers instead of 9 (update1 and update2 at 16^3 x 48, N = 24:
+// 117 + 56 -> 61 + 89 us).
+//
+// In the row layout ([Vh][3][N]) a thread keeps one column for all of its rows (the
+// threads of a workgroup cover whole rows), so that the loads of a workgroup are one
+// contiguous run and the per-column scalars stay in registers; p^H A p comes from the hop.
 #include "device_common.h"
 #include "internal.h"
+#include "rows.h"
 
 namespace bcg {
 
@@ -80,16 +85,22 @@ __device__ double pb_column_sum(const double* __restrict__ partials, int nb, int
 
 // alpha_j = rr_j / p_j^H A p_j for the active columns (0 for the others)
 __global__ void __launch_bounds__(1024) k_pb_alpha(const double* __restrict__ partials, int nb, int N, PbState* st) {
-    if (st->halt) return;
+    if (st->halt) {
+        if (threadIdx.x == 0) st->step = 0;
+        return;
+    }
     __shared__ double red[1024];
     const int ln = pb_lanes(N), j = threadIdx.x / ln;
     const double pap = pb_column_sum(partials, nb, N, red);
+    if (threadIdx.x == 0) st->step = 1;
+    __syncthreads();
     if (j < N && (threadIdx.x & (ln - 1)) == 0) {
         double a = 0.0;
         if (st->active[j]) {
             if (!(pap > 0.0)) {
                 st->halt = 1;
                 st->reason = HALT_BREAKDOWN_G;
+                st->step = 0;
             } else {
                 a = st->rr[j] / pap;
             }
@@ -98,10 +109,9 @@ __global__ void __launch_bounds__(1024) k_pb_alpha(const double* __restrict__ pa
     }
 }
 
-// x_j += alpha_j p_j, r_j -= alpha_j Ap_j; partials[j][b] = |r_j|^2 over workgroup b's sites
+// r_j -= alpha_j Ap_j; partials[j][b] = |r_j|^2 over workgroup b's sites
 __global__ void __launch_bounds__(256)
-k_pb_update1(double2* __restrict__ X, double2* __restrict__ R, const double2* __restrict__ P,
-             const double2* __restrict__ AP, int Vh, double* __restrict__ partials, const PbState* __restrict__ st) {
+k_pb_update1(double2* __restrict__ R, const double2* __restrict__ AP, int Vh, double* __restrict__ partials, const PbState* __restrict__ st) {
     if (st->halt) return;
     const int j = blockIdx.y;
     __shared__ double red[4];
@@ -112,13 +122,10 @@ k_pb_update1(double2* __restrict__ X, double2* __restrict__ R, const double2* __
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const long o = ((long)j * 3 + c) * Vh + i;
-                const double2 p = P[o], ap = AP[o];
-                double2 x = X[o], r = R[o];
-                x.x = fma(a, p.x, x.x);
-                x.y = fma(a, p.y, x.y);
+                const double2 ap = AP[o];
+                double2 r = R[o];
                 r.x = fma(-a, ap.x, r.x);
                 r.y = fma(-a, ap.y, r.y);
-                X[o] = x;
                 R[o] = r;
                 s += r.x * r.x + r.y * r.y;
             }
@@ -154,22 +161,30 @@ __global__ void __launch_bounds__(1024) k_pb_beta(const double* __restrict__ par
     }
 }
 
-// p_j = r_j + beta_j p_j for the columns still active
+// x_j += alpha_j p_j (alpha = 0: no step), then p_j = r_j + beta_j p_j for the columns
+// still active; after a halt that came with a step, x alone
 __global__ void __launch_bounds__(256)
-k_pb_update2(double2* __restrict__ P, const double2* __restrict__ R, int Vh, const PbState* __restrict__ st) {
-    if (st->halt) return;
+k_pb_update2(double2* __restrict__ X, double2* __restrict__ P, const double2* __restrict__ R, int Vh,
+             const PbState* __restrict__ st) {
+    if (!st->step) return;
     const int j = blockIdx.y;
-    if (!st->active[j]) return;
-    const double b = st->beta[j];
+    const double a = st->alpha[j], b = st->beta[j];
+    if (a == 0.0) return;
+    const bool go = st->active[j];
     for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < Vh; i += (long)gridDim.x * 256)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const long o = ((long)j * 3 + c) * Vh + i;
-            const double2 r = R[o];
-            double2 p = P[o];
-            p.x = fma(b, p.x, r.x);
-            p.y = fma(b, p.y, r.y);
-            P[o] = p;
+            double2 p = P[o], x = X[o];
+            x.x = fma(a, p.x, x.x);
+            x.y = fma(a, p.y, x.y);
+            X[o] = x;
+            if (go) {
+                const double2 r = R[o];
+                p.x = fma(b, p.x, r.x);
+                p.y = fma(b, p.y, r.y);
+                P[o] = p;
+            }
         }
 }
 
@@ -186,28 +201,26 @@ __device__ __forceinline__ void pb_rows_sum(double v, double* red, int N, int tp
     }
 }
 
+// partials of p^H A p per column from the block sums of the hop (dots[nb][N])
+constexpr int PB_DOT_PARTS = 64;
 __global__ void __launch_bounds__(256)
-k_pb_dot_rows(const double2* __restrict__ P, const double2* __restrict__ AP, int N, long rows,
-              double* __restrict__ partials, const PbState* __restrict__ st) {
+k_pb_dot_sum(const double* __restrict__ dots, int N, long nb, double* __restrict__ partials,
+             const PbState* __restrict__ st) {
     if (st->halt) return;
     __shared__ double red[256];
     const int tp = 256 / N, j = threadIdx.x % N;
     double s = 0.0;
-    if (threadIdx.x < tp * N && st->active[j]) {
+    if (threadIdx.x < tp * N) {
         const long step = (long)gridDim.x * tp;
 #pragma unroll 4
-        for (long r = (long)blockIdx.x * tp + threadIdx.x / N; r < rows; r += step) {
-            const double2 p = P[r * N + j], a = AP[r * N + j];
-            s += p.x * a.x + p.y * a.y;
-        }
+        for (long b = (long)blockIdx.x * tp + threadIdx.x / N; b < nb; b += step) s += dots[b * N + j];
     }
     pb_rows_sum(s, red, N, tp, partials);
 }
 
 __global__ void __launch_bounds__(256)
-k_pb_update1_rows(double2* __restrict__ X, double2* __restrict__ R, const double2* __restrict__ P,
-                  const double2* __restrict__ AP, int N, long rows, double* __restrict__ partials,
-                  const PbState* __restrict__ st) {
+k_pb_update1_rows(double2* __restrict__ R, const double2* __restrict__ AP, int N, long rows,
+                  double* __restrict__ partials, const PbState* __restrict__ st) {
     if (st->halt) return;
     __shared__ double red[256];
     const int tp = 256 / N, j = threadIdx.x % N;
@@ -218,13 +231,10 @@ k_pb_update1_rows(double2* __restrict__ X, double2* __restrict__ R, const double
 #pragma unroll 4
         for (long r0 = (long)blockIdx.x * tp + threadIdx.x / N; r0 < rows; r0 += step) {
             const long o = r0 * N + j;
-            const double2 p = P[o], ap = AP[o];
-            double2 x = X[o], r = R[o];
-            x.x = fma(a, p.x, x.x);
-            x.y = fma(a, p.y, x.y);
+            const double2 ap = AP[o];
+            double2 r = R[o];
             r.x = fma(-a, ap.x, r.x);
             r.y = fma(-a, ap.y, r.y);
-            X[o] = x;
             R[o] = r;
             s += r.x * r.x + r.y * r.y;
         }
@@ -233,21 +243,26 @@ k_pb_update1_rows(double2* __restrict__ X, double2* __restrict__ R, const double
 }
 
 __global__ void __launch_bounds__(256)
-k_pb_update2_rows(double2* __restrict__ P, const double2* __restrict__ R, int N, long rows,
+k_pb_update2_rows(double2* __restrict__ X, double2* __restrict__ P, const double2* __restrict__ R, int N, long rows,
                   const PbState* __restrict__ st) {
-    if (st->halt) return;
+    if (!st->step) return;
     const int tp = 256 / N, j = threadIdx.x % N;
-    if (threadIdx.x >= tp * N || !st->active[j]) return;
-    const double b = st->beta[j];
+    if (threadIdx.x >= tp * N) return;
+    const double a = st->alpha[j], b = st->beta[j];
+    if (a == 0.0) return;
+    const bool go = st->active[j];
     const long step = (long)gridDim.x * tp;
 #pragma unroll 4
     for (long r0 = (long)blockIdx.x * tp + threadIdx.x / N; r0 < rows; r0 += step) {
         const long o = r0 * N + j;
-        const double2 r = R[o];
-        double2 p = P[o];
+        double2 p = P[o], x = X[o];
+        const double2 r = go ? R[o] : p;
+        x.x = fma(a, p.x, x.x);
+        x.y = fma(a, p.y, x.y);
+        X[o] = x;
         p.x = fma(b, p.x, r.x);
         p.y = fma(b, p.y, r.y);
-        P[o] = p;
+        if (go) P[o] = p;
     }
 }
 
@@ -292,34 +307,33 @@ __global__ void k_pb_start(const double* __restrict__ partials, int nb, int N, P
 // workgroups of the row kernels: the same count as partials per column as the planes'
 static dim3 pb_rows_grid(int Vh) { return dim3(pb_blocks(Vh)); }
 
-hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, bool rows, double* partials,
-                         const PbState* st, hipStream_t s) {
-    if (rows)
-        hipLaunchKernelGGL(k_pb_dot_rows, pb_rows_grid(Vh), dim3(256), 0, s, P, AP, N, 3L * Vh, partials, st);
-    else
-        hipLaunchKernelGGL(k_pb_dot, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, AP, Vh, partials, st);
+hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, double* partials, const PbState* st,
+                         hipStream_t s) {
+    hipLaunchKernelGGL(k_pb_dot, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, AP, Vh, partials, st);
     return hipGetLastError();
 }
-hipError_t launch_pb_alpha(const double* partials, int N, int Vh, PbState* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_pb_alpha, dim3(1), dim3(1024), 0, s, partials, pb_blocks(Vh), N, st);
+hipError_t launch_pb_dot_sum(const double* dots, int N, int Vh, double* partials, const PbState* st, hipStream_t s) {
+    hipLaunchKernelGGL(k_pb_dot_sum, dim3(PB_DOT_PARTS), dim3(256), 0, s, dots, N, row_blocks(N, Vh), partials, st);
     return hipGetLastError();
 }
-hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh, bool rows,
-                             double* partials, const PbState* st, hipStream_t s) {
-    if (rows)
-        hipLaunchKernelGGL(k_pb_update1_rows, pb_rows_grid(Vh), dim3(256), 0, s, X, R, P, AP, N, 3L * Vh, partials, st);
-    else
-        hipLaunchKernelGGL(k_pb_update1, dim3(pb_blocks(Vh), N), dim3(256), 0, s, X, R, P, AP, Vh, partials, st);
+hipError_t launch_pb_alpha(const double* partials, int N, int Vh, bool rows, PbState* st, hipStream_t s) {
+    hipLaunchKernelGGL(k_pb_alpha, dim3(1), dim3(1024), 0, s, partials, rows ? PB_DOT_PARTS : pb_blocks(Vh), N, st);
+    return hipGetLastError();
+}
+hipError_t launch_pb_update1(double2* R, const double2* AP, int N, int Vh, bool rows, double* partials,
+                             const PbState* st, hipStream_t s) {
+    if (rows) hipLaunchKernelGGL(k_pb_update1_rows, pb_rows_grid(Vh), dim3(256), 0, s, R, AP, N, 3L * Vh, partials, st);
+    else hipLaunchKernelGGL(k_pb_update1, dim3(pb_blocks(Vh), N), dim3(256), 0, s, R, AP, Vh, partials, st);
     return hipGetLastError();
 }
 hipError_t launch_pb_beta(const double* partials, int N, int Vh, PbState* st, hipStream_t s) {
     hipLaunchKernelGGL(k_pb_beta, dim3(1), dim3(1024), 0, s, partials, pb_blocks(Vh), N, st);
     return hipGetLastError();
 }
-hipError_t launch_pb_update2(double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
+hipError_t launch_pb_update2(double2* X, double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
                              hipStream_t s) {
-    if (rows) hipLaunchKernelGGL(k_pb_update2_rows, dim3(4 * pb_blocks(Vh)), dim3(256), 0, s, P, R, N, 3L * Vh, st);
-    else hipLaunchKernelGGL(k_pb_update2, dim3(pb_blocks(Vh), N), dim3(256), 0, s, P, R, Vh, st);
+    if (rows) hipLaunchKernelGGL(k_pb_update2_rows, dim3(4 * pb_blocks(Vh)), dim3(256), 0, s, X, P, R, N, 3L * Vh, st);
+    else hipLaunchKernelGGL(k_pb_update2, dim3(pb_blocks(Vh), N), dim3(256), 0, s, X, P, R, Vh, st);
     return hipGetLastError();
 }
 hipError_t launch_pb_restart_rows(double2* R, double2* P, const double2* Rt, int N, int Vh, const int* restart,
