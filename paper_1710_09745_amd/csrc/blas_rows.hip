@@ -82,11 +82,11 @@ template <typename S, int NT, bool HR> struct RowLane {
     }
 };
 
-// acc += (values of columns 0 .. 15 of the tile held in v) x the coefficients m(l),
-// l = 0 .. 15 (half rows: 0 .. 7), of the lane's output column
-template <bool HR, typename R, typename F>
-__device__ __forceinline__ void row_product(C2<R> acc[3], const C2<R> v[3], F&& m) {
-    static_for<HR ? 8 : 16>([&](auto lc) {
+// acc += (values of columns 0 .. M - 1 of the tile held in v) x the coefficients m(l),
+// l = 0 .. M - 1, of the lane's output column
+template <bool HR, int M, typename R, typename F>
+__device__ __forceinline__ void row_product_m(C2<R> acc[3], const C2<R> v[3], F&& m) {
+    static_for<M>([&](auto lc) {
         constexpr int l = decltype(lc)::value;
         const C2<R> b = m(l);
         if constexpr (HR) {
@@ -97,7 +97,15 @@ __device__ __forceinline__ void row_product(C2<R> acc[3], const C2<R> v[3], F&& 
         }
     });
 }
-
+// all columns of a tile: 8 in a half row, and in the last of several tiles (T8) that has
+// at most 8, else 16.  At 17 to 24 columns the passes are bound by these multiply-adds, and
+// three eighths of a 32 x 32 product is padding that the shorter tile halves (24^4, N = 24,
+// 16-bit: pass A 128 -> 113, pass B 201 -> 167 us)
+template <bool HR, bool T8, typename R, typename F>
+__device__ __forceinline__ void row_product(C2<R> acc[3], const C2<R> v[3], bool last, F&& m) {
+    if (HR || (T8 && last)) row_product_m<HR, 8>(acc, v, m);
+    else row_product_m<HR, HR ? 8 : 16>(acc, v, m);
+}
 // Waves of a Gram workgroup: four from three tiles on, whose accumulators need more
 // than the 256 registers a lane has in a workgroup of eight.
 constexpr int row_gram_nw(int nt) { return nt <= 2 ? ROW_NW : 4; }
@@ -161,7 +169,7 @@ k_gram_rows(const char* __restrict__ A, const char* __restrict__ B, int N, int V
 // Pass A: Q <- Q - AP beta and, with GR, the partials of H = Qt^H Qt of the stored Qt
 // (its own kernel for three and four tiles, whose accumulators would not leave room).
 // Bound by the read of Q and AP and the write of Q.
-template <typename S, int NT, bool HR, bool GR>
+template <typename S, int NT, bool HR, bool T8, bool GR>
 __global__ void __launch_bounds__(64 * ROW_NW)
 k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* __restrict__ beta, int N, int Vh,
               RowOrder ord, int nb, int ld, double2* __restrict__ partials, const int* __restrict__ halt) {
@@ -211,7 +219,7 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
                 C2<R> acc[3] = {c2<R>(0, 0), c2<R>(0, 0), c2<R>(0, 0)};
 #pragma unroll
                 for (int lt = 0; lt < NT; ++lt)
-                    row_product<HR>(acc, av[lt], [&](int l) { return cf[(lt * 16 + l) * NP + t * 16 + M.cl]; });
+                    row_product<HR, T8>(acc, av[lt], lt == NT - 1, [&](int l) { return cf[(lt * 16 + l) * NP + t * 16 + M.cl]; });
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     qv[t][c].re -= acc[c].re;
@@ -250,7 +258,7 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
                     C2<R> av[3];
                     ar.get(av);
                     const C2<R>* m = cf + lt * 16 * NP + t * 16 + L.cl;
-                    row_product<HR>(acc, av, [&](int l) { return m[l * NP]; });
+                    row_product<HR, T8>(acc, av, lt == NT - 1, [&](int l) { return m[l * NP]; });
                 }
                 C2<R> qv[3];
                 qr.get(qv);
@@ -269,7 +277,7 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
 // Pass B: X += P (beta C) in FP64, Qn = Qt S^{-1}, Pn = Qn + P S^H, as pb_mode selects.
 // LDS: beta C whole, the upper tiles of S^{-1} and the lower tiles of S^H (the others
 // are zero), [l][j] within a tile.
-template <typename S, int NT, bool HR>
+template <typename S, int NT, bool HR, bool T8>
 __global__ void __launch_bounds__(64 * ROW_NW)
 k_pass_b_rows(double2* __restrict__ X, const char* __restrict__ Qt, const char* __restrict__ P, char* __restrict__ Qn,
               char* __restrict__ Pn, const double2* __restrict__ betaC, const double2* __restrict__ Sinv,
@@ -311,15 +319,15 @@ k_pass_b_rows(double2* __restrict__ X, const char* __restrict__ Qt, const char* 
 #pragma unroll
         for (int c = 0; c < 3; ++c) pd[c] = C2<double>{(double)pv[c].re, (double)pv[c].im};
         const C2<double>* mx = cx + lt * TW * NP + jt * TW + L.cl;
-        row_product<HR>(xa, pd, [&](int l) { return mx[l * NP]; });
+        row_product<HR, T8>(xa, pd, lt == NT - 1, [&](int l) { return mx[l * NP]; });
         if (!full) return;
         if (lt >= jt) {
             const C2<R>* m = ch + (lt * (lt + 1) / 2 + jt) * TE + L.cl;
-            row_product<HR>(pa, pv, [&](int l) { return m[l * TW]; });
+            row_product<HR, T8>(pa, pv, lt == NT - 1, [&](int l) { return m[l * TW]; });
         }
         if (lt <= jt) {
             const C2<R>* m = ci + (jt * (jt + 1) / 2 + lt) * TE + L.cl;
-            row_product<HR>(qa, qv, [&](int l) { return m[l * TW]; });
+            row_product<HR, T8>(qa, qv, lt == NT - 1, [&](int l) { return m[l * TW]; });
         }
     };
     auto store = [&](int jt, const RowRaw<F64>& xr, C2<double> xa[3], C2<R> pa[3], C2<R> qa[3]) {
@@ -432,7 +440,7 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
 #pragma unroll
                 for (int c = 0; c < 3; ++c) xd[c] = C2<double>{(double)xv[c].re, (double)xv[c].im};
                 const C2<double>* m = cf + lt * 16 * np + t * 16 + L.cl;
-                row_product<HR>(acc, xd, [&](int l) { return m[l * np]; });
+                row_product<HR, false>(acc, xd, false, [&](int l) { return m[l * np]; });
             }
             if (!(L.live && L.col(t) < N)) continue;
             const unsigned o = L.template off<SY>(t, N);
@@ -475,6 +483,9 @@ k_colnorm2_rows(const double2* __restrict__ V, int N, int cp, long rows, double*
 // ---------------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------------
+// the last of several tiles has at most 8 columns (row_product)
+static bool last_tile_8(int N) { return N > 16 && (N - 1) % 16 < 8; }
+
 static int gram_nw(int N) { return row_gram_nw(N <= 8 ? 1 : (N + 15) / 16); }
 int gram_rows_parts(int N, int Vh, const RowOrder& o) { return row_grid(row_blocks(N, Vh), o, GRAM_BLOCKS, gram_nw(N)); }
 
@@ -521,13 +532,20 @@ static void pass_a_rows_go(void* Q, const void* AP, const double2* beta, int N, 
     const int np = N <= 8 ? 8 : (N + 15) / 16 * 16;
     const size_t cf = (size_t)np * np * sizeof(C2<typename S::real>), red = ROW_NW * 512 * sizeof(double);
     const size_t lds = pass_a_rows_gram(N) && red > cf ? red : cf;
-#define GO(NT, HR, GR) \
-    hipLaunchKernelGGL((k_pass_a_rows<S, NT, HR, GR>), grid, blk, lds, s, (char*)Q, (const char*)AP, beta, N, Vh, o, nb, ld, part, halt)
-    if (N <= 8) GO(1, true, true);
-    else if (N <= 16) GO(1, false, true);
-    else if (N <= 32) GO(2, false, true);
-    else if (N <= 48) GO(3, false, false);
-    else GO(4, false, false);
+#define GO(NT, HR, T8, GR)                                                                                         \
+    hipLaunchKernelGGL((k_pass_a_rows<S, NT, HR, T8, GR>), grid, blk, lds, s, (char*)Q, (const char*)AP, beta, N, \
+                       Vh, o, nb, ld, part, halt)
+#define GO8(NT, GR)                                 \
+    do {                                            \
+        if (last_tile_8(N)) GO(NT, false, true, GR); \
+        else GO(NT, false, false, GR);              \
+    } while (0)
+    if (N <= 8) GO(1, true, false, true);
+    else if (N <= 16) GO(1, false, false, true);
+    else if (N <= 32) GO8(2, true);
+    else if (N <= 48) GO8(3, false);
+    else GO8(4, false);
+#undef GO8
 #undef GO
 }
 
@@ -556,14 +574,20 @@ static void pass_b_rows_go(double2* X, const void* Qt, const void* P, void* Qn, 
     const int nb = row_blocks(N, Vh);
     const size_t lds = pass_b_rows_lds<S>(N);
     const dim3 grid(row_grid(nb, o, 2048)), blk(64 * ROW_NW);
-#define GO(NT, HR)                                                                                                    \
-    hipLaunchKernelGGL((k_pass_b_rows<S, NT, HR>), grid, blk, lds, s, X, (const char*)Qt, (const char*)P, (char*)Qn, \
-                       (char*)Pn, betaC, Sinv, SH, N, Vh, o, nb, st)
-    if (N <= 8) GO(1, true);
-    else if (N <= 16) GO(1, false);
-    else if (N <= 32) GO(2, false);
-    else if (N <= 48) GO(3, false);
-    else GO(4, false);
+#define GO(NT, HR, T8)                                                                                         \
+    hipLaunchKernelGGL((k_pass_b_rows<S, NT, HR, T8>), grid, blk, lds, s, X, (const char*)Qt, (const char*)P, \
+                       (char*)Qn, (char*)Pn, betaC, Sinv, SH, N, Vh, o, nb, st)
+#define GO8(NT)                                 \
+    do {                                        \
+        if (last_tile_8(N)) GO(NT, false, true); \
+        else GO(NT, false, false);              \
+    } while (0)
+    if (N <= 8) GO(1, true, false);
+    else if (N <= 16) GO(1, false, false);
+    else if (N <= 32) GO8(2);
+    else if (N <= 48) GO8(3);
+    else GO8(4);
+#undef GO8
 #undef GO
 }
 
@@ -631,8 +655,10 @@ template <typename S> static hipError_t rows_setup_s() {
         const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pass_b_rows_lds<S>(N));
         if (e == hipSuccess) e = r;
     };
-    big(reinterpret_cast<const void*>(&k_pass_b_rows<S, 3, false>), 48);
-    big(reinterpret_cast<const void*>(&k_pass_b_rows<S, 4, false>), 64);
+    big(reinterpret_cast<const void*>(&k_pass_b_rows<S, 3, false, false>), 48);
+    big(reinterpret_cast<const void*>(&k_pass_b_rows<S, 3, false, true>), 48);
+    big(reinterpret_cast<const void*>(&k_pass_b_rows<S, 4, false, false>), 64);
+    big(reinterpret_cast<const void*>(&k_pass_b_rows<S, 4, false, true>), 64);
     return e;
 }
 hipError_t blas_rows_setup() {
