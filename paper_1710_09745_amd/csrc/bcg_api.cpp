@@ -344,18 +344,18 @@ int hop(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const v
 
 // the hop in the row layout (ctr as launch_hop_rows)
 int hop_rows(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const void* ctr, int N,
-             const int* halt, double* dots = nullptr) {
+             const int* halt, double* dots = nullptr, bool canon = false) {
     const void* Wp = p == Prec::FP64 ? ctx->W64r[out_parity] : ctx->Wslr[out_parity];
     Prof pr(ctx, out_parity == 1 ? BCG_K_HOP_OE : BCG_K_HOP_EO, true);
     HIPCK(launch_hop_rows(p, ctx->nl, Wp, in, out, ctr, 4.0 * ctx->mass * ctx->mass, N, ctx->g, row_order(ctx->g, N),
-                          out_parity, halt, ctx->stream, dots));
+                          out_parity, halt, ctx->stream, dots, canon));
     return BCG_OK;
 }
 
 // out = A in, FP64, row layout; tmp: odd-parity scratch
-int apply64_rows(bcg_ctx* ctx, const void* in, void* out, void* tmp, int N, const int* halt) {
+int apply64_rows(bcg_ctx* ctx, const void* in, void* out, void* tmp, int N, const int* halt, bool canon = false) {
     RETCK(hop_rows(ctx, Prec::FP64, 1, in, tmp, nullptr, N, halt));
-    return hop_rows(ctx, Prec::FP64, 0, tmp, out, in, N, halt);
+    return hop_rows(ctx, Prec::FP64, 0, tmp, out, in, N, halt, nullptr, canon);
 }
 
 // the fused Gram epilogues fit in LDS for this precision and block size
@@ -430,6 +430,12 @@ struct BlockOps {
     }
     int apply(const void* in, void* out, void* tmp) const {
         return rows ? apply64_rows(ctx, in, out, tmp, N, nullptr) : apply64(ctx, in, out, tmp, N, nullptr);
+    }
+    // the same with out in the canonical layout (internal: planes' scratch)
+    int apply_to_canon(const void* in, void* out, void* tmp, double2* internal) const {
+        if (rows) return apply64_rows(ctx, in, out, tmp, N, nullptr, true);
+        RETCK(apply64(ctx, in, internal, tmp, N, nullptr));
+        return to_canon(internal, out);
     }
     int gram_of(Prec p, const void* A, const void* B, double2* out, const int* halt) const {
         if (!rows) return gram(ctx, p, A, B, N, out, halt);
@@ -848,8 +854,7 @@ int bcg_apply(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
         Prof pr(ctx, BCG_K_CONVERT);
         RETCK(ops.from_canon(in, Wd(ctx, WB_A0)));
     }
-    RETCK(ops.apply(W(ctx, WB_A0), W(ctx, WB_A1), W(ctx, WB_A2)));
-    return ops.to_canon(Wd(ctx, WB_A1), out);
+    return ops.apply_to_canon(W(ctx, WB_A0), out, W(ctx, WB_A2), Wd(ctx, WB_A1));
 }
 
 int bcg_apply_noalloc(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
@@ -872,8 +877,7 @@ int bcg_apply_noalloc(bcg_ctx* ctx, const void* in, void* out, int nrhs) {
     ctx->prof_mask = 0;
     const BlockOps ops(ctx, nrhs);
     int rc = ops.from_canon(in, A0);
-    if (rc == BCG_OK) rc = ops.apply(A0, A1, A2);
-    if (rc == BCG_OK) rc = ops.to_canon(A1, out);
+    if (rc == BCG_OK) rc = ops.apply_to_canon(A0, out, A2, A1);
     ctx->prof_mask = mask;
     return rc;
 }
@@ -920,6 +924,8 @@ int bcg_hop(bcg_ctx* ctx, int out_parity, const void* in, void* out, int nrhs) {
         Prof pr(ctx, BCG_K_CONVERT);
         RETCK(ops.from_canon(in, Wd(ctx, WB_A0)));
     }
+    if (ops.rows)
+        return hop_rows(ctx, Prec::FP64, out_parity, W(ctx, WB_A0), out, nullptr, nrhs, nullptr, nullptr, true);
     RETCK(ops.hop1(Prec::FP64, out_parity, W(ctx, WB_A0), W(ctx, WB_A1), nullptr, nullptr));
     return ops.to_canon(Wd(ctx, WB_A1), out);
 }

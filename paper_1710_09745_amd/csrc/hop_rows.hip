@@ -144,16 +144,24 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
 // (site blocks) x (groups of NT tiles of 16 columns), the groups of a block next to each
 // other on one XCD; a last group of one tile takes the one-tile code.
 //
-// DOT: also Re ctr^H out of each column over the block's sites, to dots[block][N], while
-// both are in registers (16^3 x 48, N = 24, FP64: the hop 167 -> 169 us, in place of a
+// ROWS_DOT: also Re ctr^H out of each column over the block's sites, to dots[block][N],
+// while both are in registers (16^3 x 48, N = 24, FP64: the hop 167 -> 169 us, in place of a
 // 39 us pass over both blocks).
-template <typename S, int NL, bool MASS, bool HR, int NT, int D, int WPS, bool LNT, bool DOT>
+//
+// ROWS_CANON: out in the canonical layout [N][V/2][3], through LDS so that a column's
+// sites of the block are one run (768 bytes), in place of a kernel that reads and writes
+// the block once more (apply, us: 4^4, N = 4 14.5 -> 11-13, 16^4,
+// N = 16 95 -> 86, 32^3 x 64, N = 12 2505 -> 2287).
+enum { ROWS_PLAIN = 0, ROWS_DOT = 1, ROWS_CANON = 2 };
+template <typename S, int NL, bool MASS, bool HR, int NT, int D, int WPS, bool LNT, int EPI>
 __global__ void __launch_bounds__(256, WPS)
 k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
            const char* __restrict__ ctr, double m2d, int N, int nct, Geom g, RowOrder ord, int out_parity,
            double* __restrict__ dots, const int* __restrict__ halt) {
     using R = typename S::real;
-    __shared__ double red[DOT ? 4 * NT * 16 : 1];
+    constexpr int TW = HR ? 8 : 16, RW = 3 * row_block_sites<HR>();  // columns of a tile, numbers a column has
+    __shared__ double red[EPI == ROWS_DOT ? 4 * NT * 16 : 1];
+    __shared__ C2<R> tile[EPI == ROWS_CANON ? NT * TW * (RW + 1) : 1];
     if (halt != nullptr && *halt) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int sb, ct;
@@ -175,10 +183,24 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
                                                                      16 * NT * ct, threadIdx.x & 63, acc, z, stores, o, cs);
 #pragma unroll
         for (int t = 0; t < T; ++t)
-            if (stores[t]) row_store<S, R>(out, o[t], cs[t], acc[t]);
-        if constexpr (DOT) {
-            constexpr int TW = HR ? 8 : 16;
-            const int lane = threadIdx.x & 63;
+            if (EPI != ROWS_CANON && stores[t]) row_store<S, R>(out, o[t], cs[t], acc[t]);
+        const int lane = threadIdx.x & 63;
+        if constexpr (EPI == ROWS_CANON) {
+            const int r0 = 3 * (w * (row_block_sites<HR>() / 4) + row_lane_site<HR>(lane));
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) tile[(t * TW + row_lane_col<HR>(lane)) * (RW + 1) + r0 + c] = acc[t][c];
+            __syncthreads();
+            const long rows = 3L * g.Vh, b0 = (long)sb * RW;
+            const int m = rows - b0 < RW ? (int)(rows - b0) : RW;
+            C2<R>* dst = reinterpret_cast<C2<R>*>(out) + b0;
+            for (int e = threadIdx.x; e < T * TW * RW; e += 256) {
+                const int j = e / RW, r = e - RW * j, c = 16 * NT * ct + j;
+                if (c < N && r < m) dst[(long)c * rows + r] = tile[j * (RW + 1) + r];
+            }
+        }
+        if constexpr (EPI == ROWS_DOT) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 double d = 0.0;
@@ -409,25 +431,26 @@ static bool stream_links(Prec p, int nl, long Vh) {
 
 template <typename S, int NL, bool MASS, bool LNT>
 static void hop_rows_go(const void* W, const void* in, void* out, const void* ctr, double m2, int N, const Geom& g,
-                        const RowOrder& ord, int out_parity, double* dots, const int* halt, hipStream_t s) {
+                        const RowOrder& ord, int out_parity, double* dots, bool canon, const int* halt, hipStream_t s) {
     constexpr bool F = std::is_same<S, F64>::value;
     const long nb = row_blocks(N, g.Vh);
-#define GO2(HRV, NTV, DV, WV, DOT)                                                                                   \
+#define GO2(HRV, NTV, DV, WV, EPI)                                                                                   \
     do {                                                                                                             \
         const int nct = (N + 16 * NTV - 1) / (16 * NTV);                                                             \
         const dim3 grid((unsigned)(nb * nct));                                                                       \
-        BCG_TIMED_LAUNCH((k_hop_rows<S, NL, MASS, HRV, NTV, DV, WV, LNT, DOT>), grid, dim3(256), 0, s,               \
+        BCG_TIMED_LAUNCH((k_hop_rows<S, NL, MASS, HRV, NTV, DV, WV, LNT, EPI>), grid, dim3(256), 0, s,               \
                          (const char*)W, (const char*)in, (char*)out, (const char*)ctr, m2, N, nct, g, ord,          \
                          out_parity, dots, halt);                                                                    \
     } while (0)
-#define GO(HRV, NTV, DV, WV)                                       \
-    do {                                                           \
-        if constexpr (F && MASS) {                                 \
-            if (dots != nullptr) GO2(HRV, NTV, DV, WV, true);      \
-            else GO2(HRV, NTV, DV, WV, false);                     \
-        } else {                                                   \
-            GO2(HRV, NTV, DV, WV, false);                          \
-        }                                                          \
+#define GO(HRV, NTV, DV, WV)                                              \
+    do {                                                                  \
+        if constexpr (F) {                                                \
+            if (canon) GO2(HRV, NTV, DV, WV, ROWS_CANON);                 \
+            else if (MASS && dots) GO2(HRV, NTV, DV, WV, MASS ? ROWS_DOT : ROWS_PLAIN); \
+            else GO2(HRV, NTV, DV, WV, ROWS_PLAIN);                       \
+        } else {                                                          \
+            GO2(HRV, NTV, DV, WV, ROWS_PLAIN);                            \
+        }                                                                 \
     } while (0)
     if (N <= 8) GO(true, 1, F ? 4 : 8, F ? 3 : 4);
     else if (N <= 16) GO(false, 1, F ? 4 : 8, 4);
@@ -484,13 +507,14 @@ hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in
 
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
                            int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s,
-                           double* dots) {
-    if (!rows_fit(N, g.Vh) || (dots != nullptr && (prec != Prec::FP64 || ctr == nullptr))) return hipErrorInvalidValue;
+                           double* dots, bool canon) {
+    if (!rows_fit(N, g.Vh) || (dots && (prec != Prec::FP64 || !ctr || canon)) || (canon && prec != Prec::FP64))
+        return hipErrorInvalidValue;
     const bool lnt = stream_links(prec, nl, g.Vh);
 #define GO3(S, NL, MASS)                                                                                  \
     do {                                                                                                  \
-        if (lnt) hop_rows_go<S, NL, MASS, true>(W, in, out, ctr, m2, N, g, ord, out_parity, dots, halt, s);  \
-        else hop_rows_go<S, NL, MASS, false>(W, in, out, ctr, m2, N, g, ord, out_parity, dots, halt, s);     \
+        if (lnt) hop_rows_go<S, NL, MASS, true>(W, in, out, ctr, m2, N, g, ord, out_parity, dots, canon, halt, s);  \
+        else hop_rows_go<S, NL, MASS, false>(W, in, out, ctr, m2, N, g, ord, out_parity, dots, canon, halt, s);     \
     } while (0)
 #define GO(S)                               \
     do {                                    \

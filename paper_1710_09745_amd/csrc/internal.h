@@ -127,10 +127,10 @@ hipError_t pack_links_rows(const void* fat, const void* lng, void* W, const Geom
 hipError_t row_links_to_planes(const void* Wr, void* Wp, int nl, long Vh, hipStream_t s);
 hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh, hipStream_t s);
 // out = D_{p,1-p} in, or with ctr: out = m2 ctr - D_{p,1-p} in
-// (dots, FP64 with ctr: also Re ctr^H out of each column and block of sites, [row_blocks][N])
+// (canon, FP64: out in the canonical layout; dots, FP64 with ctr: also Re ctr^H out of each column and block of sites, [row_blocks][N])
 hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr, double m2,
                            int N, const Geom& g, const RowOrder& ord, int out_parity, const int* halt, hipStream_t s,
-                           double* dots = nullptr);
+                           double* dots = nullptr, bool canon = false);
 
 // the same with ctr, and hop_gram_parts partials (leading dimension row_ld(N)) of
 // ctr^H out, for hop_rows_gram(N, Vh)
