@@ -461,6 +461,9 @@ struct BlockOps {
         }
         return sum_or_leave(hop_gram_parts(N, Vh(), ord), out, parts, halt);
     }
+    // Pass B may write P' and Q' over P and Q (up to two tiles it loads all columns of a
+    // site before it stores any): two blocks less to pass through the Infinity Cache
+    bool in_place() const { return rows && N <= 32; }
     // Qt = Q - AP beta and Qt^H Qt, as hop_gram
     int pass_a_gram(Prec p, void* Q, const void* AP, const double2* beta, double2* out, int& parts,
                     const int* halt) const {
@@ -1070,9 +1073,10 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     bool finished = (status != BCG_OK) || (ctx->h_state->max_relres <= ctx->tol);
     bool need_final_check = true;   // cleared when a reliable update has confirmed convergence
 
-    // one iteration of Alg. 1 on the ping-pong buffers c (P, Q) -> 1 - c (P', Q')
+    // one iteration of Alg. 1 on the buffers c (P, Q), to c (in place) or 1 - c (P', Q')
+    const int flip = ops.in_place() ? 0 : 1;
     auto iteration = [&](int c) -> int {
-        void *P = Pb[c], *Q = Qb[c], *Pn = Pb[1 - c], *Qn = Qb[1 - c];
+        void *P = Pb[c], *Q = Qb[c], *Pn = Pb[c ^ flip], *Qn = Qb[c ^ flip];
         const int req = ctx->opt[BCG_OPT_SMALL_THREADS];
         int parts = 0;  // Gram partials left for the N x N kernel to sum
         if (fuse) {
@@ -1140,7 +1144,7 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
             int rc = iteration(c0);
-            if (rc == BCG_OK) rc = iteration(1 - c0);
+            if (rc == BCG_OK) rc = iteration(c0 ^ flip);
             hipGraph_t g = nullptr;
             e = hipStreamEndCapture(s, &g);
             if (e == hipSuccess && rc == BCG_OK && g) {
@@ -1178,7 +1182,7 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         for (; k < chunk; ++k) {
             RETCK(iteration(c));
             n_pp = n_h;
-            c = 1 - c;
+            c ^= flip;
         }
         RETCK(read_state(ctx));
         if (ctx->monitor) ctx->monitor(ctx->monitor_user, hs.iters, n_ru, hs.max_relres);
@@ -1187,7 +1191,7 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
         const int reason = hs.reason;
         const int full = (halted && (reason == HALT_CONVERGED || reason == HALT_RU || reason == HALT_BREAKDOWN_H))
                              ? active - 1 : active;
-        cur = (cur + full) & 1;
+        cur ^= full & flip;
         iters_at_resume = hs.iters;
         iters_done = hs.iters;
         {

@@ -133,9 +133,9 @@ template <int M, typename F> __device__ __forceinline__ void static_for(F&& f) {
 // (FP64) or to the third (FP32), see row_cs.
 template <typename S> struct RowRaw {
     C2<typename S::real> v[3];
-    __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned cs) {
+    template <int AUX = AUX_NONE> __device__ __forceinline__ void load(rsrc_t r, unsigned off, unsigned cs) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = buf_pair<AUX_NONE>(r, off, c * cs, (typename S::real)0);
+        for (int c = 0; c < 3; ++c) v[c] = buf_pair<AUX>(r, off, c * cs, (typename S::real)0);
     }
     __device__ __forceinline__ void get(C2<typename S::real> o[3]) const {
 #pragma unroll
@@ -233,6 +233,14 @@ template <typename S, typename R>
 __device__ __forceinline__ void row_store(void* base, size_t off, unsigned cs, const C2<R> v[3]) {
     C2<R> w[3] = {v[0], v[1], v[2]};
     row_store_rt<S, R>(base, off, cs, w, true);
+}
+
+// FP64 with a streaming hint
+__device__ __forceinline__ void row_store_nt(void* base, size_t off, unsigned cs, const C2<double> v[3]) {
+    typedef double pair_t __attribute__((ext_vector_type(2)));
+    char* p = reinterpret_cast<char*>(base) + off;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) __builtin_nontemporal_store(pair_t{v[c].re, v[c].im}, reinterpret_cast<pair_t*>(p + c * cs));
 }
 
 // Site of a lane: blocks of 16 sites (half rows: 32), four waves of 4 (8) sites.
