@@ -188,6 +188,16 @@ k_pb_update2(double2* __restrict__ X, double2* __restrict__ P, const double2* __
         }
 }
 
+// Loads and stores with a streaming hint: x is touched once an iteration and A p has its
+// last use in update1, and both would only push p, r and the links out of the Infinity Cache.
+typedef double pair_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double2 ld_stream(const double2* p) {
+    return __builtin_bit_cast(double2, __builtin_nontemporal_load(reinterpret_cast<const pair_t*>(p)));
+}
+__device__ __forceinline__ void st_stream(double2* p, double2 v) {
+    __builtin_nontemporal_store(__builtin_bit_cast(pair_t, v), reinterpret_cast<pair_t*>(p));
+}
+
 // The same three steps in the row layout.  tp = 256 / N rows of N threads; thread
 // (row, column) strides over the 3 Vh rows of the block; the workgroup's sums per column
 // are added in order of the row (partials [j][b] as above).
@@ -231,7 +241,7 @@ k_pb_update1_rows(double2* __restrict__ R, const double2* __restrict__ AP, int N
 #pragma unroll 4
         for (long r0 = (long)blockIdx.x * tp + threadIdx.x / N; r0 < rows; r0 += step) {
             const long o = r0 * N + j;
-            const double2 ap = AP[o];
+            const double2 ap = ld_stream(AP + o);
             double2 r = R[o];
             r.x = fma(-a, ap.x, r.x);
             r.y = fma(-a, ap.y, r.y);
@@ -255,11 +265,11 @@ k_pb_update2_rows(double2* __restrict__ X, double2* __restrict__ P, const double
 #pragma unroll 4
     for (long r0 = (long)blockIdx.x * tp + threadIdx.x / N; r0 < rows; r0 += step) {
         const long o = r0 * N + j;
-        double2 p = P[o], x = X[o];
+        double2 p = P[o], x = ld_stream(X + o);
         const double2 r = go ? R[o] : p;
         x.x = fma(a, p.x, x.x);
         x.y = fma(a, p.y, x.y);
-        X[o] = x;
+        st_stream(X + o, x);
         p.x = fma(b, p.x, r.x);
         p.y = fma(b, p.y, r.y);
         if (go) P[o] = p;
