@@ -449,7 +449,7 @@ struct BlockOps {
     // for the small kernels to sum, or (parts = 0) P^H AP in out
     int hop_gram(Prec p, const void* T, void* AP, const void* P, double2* out, int& parts, const int* halt) const {
         parts = 0;
-        if (!hop_rows_gram(N, Vh())) {
+        if (!hop_rows_gram(N)) {
             RETCK(hop1(p, 0, T, AP, P, halt));
             return gram_of(p, P, AP, out, halt);
         }
@@ -480,7 +480,14 @@ struct BlockOps {
             parts = n;
             return BCG_OK;
         }
-        return reduce(ctx, ctx->partials, n, nullptr, 0, 0.0, N, out, halt, row_ld(N));
+        const double2* part = ctx->partials;
+        if (n > 2 * GRAM_BLOCKS) {
+            Prof pr(ctx, BCG_K_REDUCE);
+            const long e = (long)row_ld(N) * row_ld(N);
+            part += n * e;
+            HIPCK(launch_gram_fold(ctx->partials, n, row_ld(N), ctx->partials + n * e, &n, halt, ctx->stream));
+        }
+        return reduce(ctx, part, n, nullptr, 0, 0.0, N, out, halt, row_ld(N));
     }
     int bmul(Prec px, const void* X, Prec py, const void* Z, void* Y, const double2* M, const int* skip) const {
         HIPCK(rows ? launch_bmul_rows(px, X, py, Z, Y, M, N, Vh(), ord, skip, ctx->stream)

@@ -449,6 +449,34 @@ k_gram_reduce(const double2* __restrict__ pa, int na, const double2* __restrict_
 
 constexpr int REDUCE_LPE = 32;
 
+// Many partials: FOLD of them summed by each workgroup first, a thread an entry.  The
+// kernel above has a workgroup for 8 entries, 32 for 16 x 16, which read 4096 partials in
+// 36 us; in two steps 11 us.
+constexpr int FOLD = 16;
+__global__ void __launch_bounds__(256)
+k_gram_fold(const double2* __restrict__ part, int P, int NN, double2* __restrict__ out, const int* __restrict__ halt) {
+    if (halt != nullptr && *halt) return;
+    const int e = blockIdx.y * 256 + threadIdx.x, p0 = blockIdx.x * FOLD;
+    if (e >= NN) return;
+    double2 v[FOLD];
+#pragma unroll
+    for (int u = 0; u < FOLD; ++u)
+        v[u] = p0 + u < P ? part[(long)(p0 + u) * NN + e] : make_double2(0.0, 0.0);
+    double2 s = v[0];
+#pragma unroll
+    for (int u = 1; u < FOLD; ++u) {
+        s.x += v[u].x;
+        s.y += v[u].y;
+    }
+    out[(long)blockIdx.x * NN + e] = s;
+}
+hipError_t launch_gram_fold(const double2* part, int P, int ld, double2* out, int* folded, const int* halt,
+                            hipStream_t s) {
+    *folded = (P + FOLD - 1) / FOLD;
+    hipLaunchKernelGGL(k_gram_fold, dim3(*folded, (ld * ld + 255) / 256), dim3(256), 0, s, part, P, ld * ld, out, halt);
+    return hipGetLastError();
+}
+
 hipError_t launch_gram_reduce(const double2* pa, int na, const double2* pb, int nb, double alpha, int N,
                               double2* out, const int* halt, hipStream_t s, int ld) {
     const int NBv = ld ? ld : pad_n(N);

@@ -229,7 +229,7 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
 // holds the two numbers of its (site, column) when it stores out, which is the operand
 // layout of the matrix instruction, so the Gram costs neither a launch nor a second read
 // of both blocks.  Persistent workgroups of NW waves over the site blocks.
-template <typename S, int NL, bool HR, int D, int WPS, int NW>
+template <typename S, int NL, bool HR, int D, int WPS, int NW, bool LNT>
 __global__ void __launch_bounds__(64 * NW, WPS)
 k_hop_gram_rows(const char* __restrict__ W, const char* __restrict__ in, char* __restrict__ out,
                 const char* __restrict__ ctr, double m2d, int N, Geom g, RowOrder ord, int nb, int out_parity,
@@ -247,7 +247,7 @@ k_hop_gram_rows(const char* __restrict__ W, const char* __restrict__ in, char* _
         bool stores[1];
         size_t o[1];
         unsigned cs[1];
-        hop_rows_block<S, NL, true, HR, 1, D, false>(W, in, ctr, m2d, N, g, out_parity, sb, w & 3, 0, lane, acc, z,
+        hop_rows_block<S, NL, true, HR, 1, D, LNT>(W, in, ctr, m2d, N, g, out_parity, sb, w & 3, 0, lane, acc, z,
                                                      stores, o, cs);
         row_store_rt<S, R>(out, o[0], cs[0], acc[0], stores[0]);
 #pragma unroll
@@ -460,39 +460,51 @@ static void hop_rows_go(const void* W, const void* in, void* out, const void* ct
 }
 
 constexpr int HOP_GRAM_NW = 8;
-// The fused Gram saves a launch and a read of both blocks, but its persistent workgroups
-// give up the overlap of one workgroup's start with another's end: 16^4, N = 16, FP64
-// 39 + 11.6 us apart, 41.3 us fused (N = 8: 24.4 + 6.9, 28.6); at 32^3 x 64, N = 16,
-// FP32 701 + 154 us apart and 825 to 909 us fused at any grid.
-bool hop_rows_gram(int N, int Vh) { return N <= 16 && Vh <= 65536; }
+bool hop_rows_gram(int N) { return N <= 16; }
+// The fused Gram saves a launch and a read of both blocks (apart / fused, us: 16^4, N = 16,
+// FP64 39 + 12 / 41, N = 8 24 + 7 / 29; 32^3 x 64, N = 16, FP32 619 + 157 / 671).  Whole
+// rounds of the 512 workgroups that fit the chip, of 8 turns each or more: one round of many
+// turns lets the workgroups of an XCD drift apart in the lattice (32^3 x 64: 738 us at 512
+// workgroups, 705 at 2048, 671 at 4096), a part of a round leaves CUs idle at the end
+// (24^4, N = 16, 16-bit, an iteration: 431 us apart, 428 at 1024, 442 at 1296).  Above 16
+// columns the accumulators of three tiles spill (16^3 x 48, N = 32, FP32: 99 + 39 us apart,
+// 138 to 182 fused; 24^4, N = 24, 16-bit 137 + 63 and 213).
 int hop_gram_parts(int N, int Vh, const RowOrder& ord) {
-    return row_grid(row_blocks(N, Vh), ord, GRAM_BLOCKS, HOP_GRAM_NW);
+    const int nb = row_blocks(N, Vh), rounds = nb / 16 / GRAM_BLOCKS;
+    return row_grid(nb, ord, GRAM_BLOCKS * (rounds < 1 ? 1 : (rounds < 8 ? rounds : 8)), HOP_GRAM_NW);
 }
 
 template <typename S, int NL>
 static void hop_gram_rows_go(const void* W, const void* in, void* out, const void* ctr, double m2, int N,
-                             const Geom& g, const RowOrder& ord, int out_parity, double2* partials, const int* halt,
-                             hipStream_t s) {
+                             const Geom& g, const RowOrder& ord, int out_parity, double2* partials, bool lnt,
+                             const int* halt, hipStream_t s) {
     constexpr bool F = std::is_same<S, F64>::value;
     constexpr int NW = HOP_GRAM_NW;
     const int nb = row_blocks(N, g.Vh);
     const dim3 grid(hop_gram_parts(N, g.Vh, ord));
-#define GO(HRV, DV, WV)                                                                                            \
-    BCG_TIMED_LAUNCH((k_hop_gram_rows<S, NL, HRV, DV, WV, NW>), grid, dim3(64 * NW), 0, s, (const char*)W,         \
+#define GO2(HRV, DV, WV, LNT)                                                                                      \
+    BCG_TIMED_LAUNCH((k_hop_gram_rows<S, NL, HRV, DV, WV, NW, LNT>), grid, dim3(64 * NW), 0, s, (const char*)W,    \
                      (const char*)in, (char*)out, (const char*)ctr, m2, N, g, ord, nb, out_parity, partials, halt)
+#define GO(HRV, DV, WV)                     \
+    do {                                    \
+        if (lnt) GO2(HRV, DV, WV, true);    \
+        else GO2(HRV, DV, WV, false);       \
+    } while (0)
     if (N <= 8) GO(true, F ? 2 : 8, F ? 2 : 4);
     else GO(false, F ? 2 : 8, 4);
 #undef GO
+#undef GO2
 }
 
 hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr,
                                 double m2, int N, const Geom& g, const RowOrder& ord, int out_parity,
                                 double2* partials, const int* halt, hipStream_t s) {
-    if (!rows_fit(N, g.Vh) || !hop_rows_gram(N, g.Vh) || ctr == nullptr) return hipErrorInvalidValue;
+    if (!rows_fit(N, g.Vh) || !hop_rows_gram(N) || ctr == nullptr) return hipErrorInvalidValue;
+    const bool lnt = stream_links(prec, nl, g.Vh);
 #define GO(S)                                                                                                       \
     do {                                                                                                            \
-        if (nl == 16) hop_gram_rows_go<S, 16>(W, in, out, ctr, m2, N, g, ord, out_parity, partials, halt, s);       \
-        else hop_gram_rows_go<S, 8>(W, in, out, ctr, m2, N, g, ord, out_parity, partials, halt, s);                 \
+        if (nl == 16) hop_gram_rows_go<S, 16>(W, in, out, ctr, m2, N, g, ord, out_parity, partials, lnt, halt, s);  \
+        else hop_gram_rows_go<S, 8>(W, in, out, ctr, m2, N, g, ord, out_parity, partials, lnt, halt, s);            \
     } while (0)
     switch (prec) {
         case Prec::FP64: GO(F64); break;

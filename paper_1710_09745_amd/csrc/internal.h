@@ -133,8 +133,8 @@ hipError_t launch_hop_rows(Prec prec, int nl, const void* W, const void* in, voi
                            double* dots = nullptr, bool canon = false);
 
 // the same with ctr, and hop_gram_parts partials (leading dimension row_ld(N)) of
-// ctr^H out, for hop_rows_gram(N, Vh)
-bool hop_rows_gram(int N, int Vh);
+// ctr^H out, for hop_rows_gram(N)
+bool hop_rows_gram(int N);
 int hop_gram_parts(int N, int Vh, const RowOrder& ord);
 hipError_t launch_hop_gram_rows(Prec prec, int nl, const void* W, const void* in, void* out, const void* ctr,
                                 double m2, int N, const Geom& g, const RowOrder& ord, int out_parity,
@@ -174,6 +174,9 @@ hipError_t launch_gram(Prec prec, const void* A, const void* B, int N, int Vh, d
 int gram_parts(int N, int Vh, bool mfma);
 // out[i*64 + j] = sum_b pa[b][i*NB + j] + alpha * sum_b pb[b][i*NB + j]  (fixed order; pb may be NULL)
 // ld: leading dimension of the partials (0: pad_n(N))
+// sums of a fixed number of partials each, *folded of them, into out (other memory)
+hipError_t launch_gram_fold(const double2* part, int P, int ld, double2* out, int* folded, const int* halt,
+                            hipStream_t s);
 hipError_t launch_gram_reduce(const double2* pa, int na, const double2* pb, int nb, double alpha, int N,
                               double2* out, const int* halt, hipStream_t s, int ld = 0);
 // LDS bytes of a fused Gram epilogue of the streaming passes (0: does not fit, use launch_gram)

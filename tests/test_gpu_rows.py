@@ -83,6 +83,23 @@ def test_row_iterates_match_oracle(n):
     assert col_rel_err(X.cpu().numpy(), ref).max() <= 1e-10
 
 
+@pytest.mark.parametrize("n", [8, 9])
+def test_row_iterates_match_planes_on_a_large_lattice(n):
+    """The Gram partials of several rounds of workgroups (above 1024 they are summed in two
+    steps): two iterations against the plane kernels."""
+    dims = (32, 32, 32, 24 if n > 8 else 48)
+    fat, lng, B = inputs(dims, False, n, 13500 + n)
+    X = []
+    for planes in (0, 1):
+        ctx = context(dims, False, fat, lng, 0.3, tol=1e-14, max_iter=2)
+        ctx.set_option("site_order", planes)
+        x, info = ctx.solve(to_dev(B), raise_on_error=False)
+        assert info["iters"] == 2
+        X.append(x.cpu().numpy())
+    # two well conditioned iterations: the bound of the small lattices' test
+    assert col_rel_err(X[0], X[1]).max() <= 1e-10
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fix16"])
 @pytest.mark.parametrize("n", [6, 20, 50])
 def test_row_mixed_solve_meets_tolerance(prec, n):
