@@ -846,6 +846,242 @@ k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restri
     if (threadIdx.x == 0) st->pb_mode = PB_FULL;
 }
 
+// ---------------------------------------------------------------------------------------------
+// 16 < N <= 32: two 16 x 16 blocks.  With A = [A11 A12; A12^H A22], Z1 = L1^{-1} of A11 = L1 D1 L1^H
+// and T = Z1 A12 (= (L21 D1)^H), the second block factors S = A22 - T^H D1^{-1} T, and
+// L^{-1} = [Z1 0; -Z2 L21 Z1, Z2].  Each of the four waves runs both factorisations (ldl16), a
+// serial chain that more lanes do not shorten; the products between them go through LDS, and
+// there every row of lanes takes rows of its own: they are register operands (lane m: entry
+// m), the other factor one LDS read per 4 or 16 multiply-adds.  Both phases, us an iteration,
+// against the kernels above: N = 32 72.6 -> 43.9, N = 24 47 -> 40.2 (with the rows of lanes
+// doing the same rows 61 and 56; with the products as calls of one function 80 and 77).
+// ---------------------------------------------------------------------------------------------
+constexpr int SMALL_ROW2_THREADS = 256;
+
+// acc[r] += sum over m < 16 of w[r](lane m) * f(m), r < R
+template <int R, typename F> __device__ __forceinline__ void rows_product(Z2* acc, const Z2* w, F&& f) {
+    unroll<16>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        row_mac<R, m>(acc, w, f(m));
+    });
+}
+
+__global__ void __launch_bounds__(SMALL_ROW2_THREADS)
+k_small_row2(bool phase2, const double2* __restrict__ H, double2* __restrict__ C, double2* __restrict__ out1,
+             double2* __restrict__ out2, SolveState* st, int N) {
+    constexpr int NN = 32, LD = NN + 1, TD = 17;
+    __shared__ Z2 th[NN * LD];  // H (Hermitian); then L D in its lower triangle
+    __shared__ Z2 tc[NN * LD];  // C
+    __shared__ Z2 zt[NN * LD];  // L^{-1}
+    __shared__ Z2 tt[16 * TD], ts[16 * TD];
+    __shared__ double tn[4][NN], dsh[NN], ish[NN];
+    const int halt = st->halt, iters = st->iters, best_it0 = st->best_it, ru_window = st->ru_window;
+    const double tol = st->tol, best0 = st->best_relres, ru_delta = st->ru_delta, rho_ru = st->rho_ru;
+    if (halt) {
+        if (phase2 && threadIdx.x == 0) st->pb_mode = PB_SKIP;
+        return;
+    }
+    for (int e = threadIdx.x; e < NN * NN; e += SMALL_ROW2_THREADS) {
+        const int i = e / NN, k = e % NN;
+        const bool in = i < N && k < N;
+        const Z2 id{i == k ? 1.0 : 0.0, 0.0};
+        if (in) {
+            const Z2 a = gld(H + i * MAXN + k), b = gld(H + k * MAXN + i);
+            th[i * LD + k] = Z2{0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
+        } else {
+            th[i * LD + k] = id;
+        }
+        tc[i * LD + k] = in ? gld(C + i * MAXN + k) : id;
+        zt[i * LD + k] = Z2{0.0, 0.0};
+    }
+    const int lane = threadIdx.x & 63, j = lane & 15, q = (lane >> 4) & 1, col = 16 * q + j;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double bn = st->bnorm[col];
+    __syncthreads();
+    if (phase2) {
+        // (C^H H C) of column col, 4 rows of H C from m0 on
+        double t = 0.0;
+        {
+            const int m0 = 8 * w + 4 * (lane >> 5);
+            Z2 hc[4] = {};
+#pragma unroll 1
+            for (int nt = 0; nt < 2; ++nt) {
+                Z2 a[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) a[r] = th[(m0 + r) * LD + 16 * nt + j];
+                const Z2* c = tc + 16 * nt * LD + col;
+                rows_product<4>(hc, a, [&](int n) { return c[n * LD]; });
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const Z2 c = tc[(m0 + r) * LD + col];
+                t += c.re * hc[r].re + c.im * hc[r].im;
+            }
+            t += __shfl_xor(t, 32, 64);
+        }
+        if (lane < NN) tn[w][col] = t;
+        __syncthreads();
+        t = (tn[0][col] + tn[1][col]) + (tn[2][col] + tn[3][col]);
+        const double rel = col < N ? sqrt(fmax(t, 0.0)) / bn : 0.0;
+        double mx = rel;
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 32));
+        // stopping and reliable-update tests, as k_small2 (every wave reaches the same decision)
+        const int it = iters + 1, best_it = mx < best0 ? it : best_it0;
+        const bool conv = mx <= tol;
+        const bool ru = (ru_delta > 0.0 && mx <= ru_delta * rho_ru) || (ru_window > 0 && it - best_it >= ru_window);
+        const int decision = conv ? HALT_CONVERGED : (ru ? HALT_RU : HALT_NONE);
+        if (threadIdx.x < N) st->relres[threadIdx.x] = rel;
+        if (threadIdx.x == 0) {
+            st->max_relres = mx;
+            st->iters = it;
+            if (mx < best0) {
+                st->best_relres = mx;
+                st->best_it = it;
+            }
+            if (decision != HALT_NONE) {
+                st->halt = 1;
+                st->reason = decision;
+                st->pb_mode = PB_X_ONLY;
+            }
+        }
+        if (decision != HALT_NONE) return;
+    }
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+        const int o = 16 * h * (LD + 1);  // block (h, h)
+        const int i = 4 * w + (lane >> 4);  // row of the lane in the products below
+        {
+            Z2 A[16], Z[16];
+            double d[16], id[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (h == 0) {
+                    A[i] = th[i * LD + j];
+                } else {
+                    const Z2 a = ts[i * TD + j], b = ts[j * TD + i];
+                    A[i] = Z2{0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
+                }
+            }
+            if (!ldl16<16>(A, Z, d, id, j)) {
+                if (threadIdx.x == 0) {
+                    st->halt = 1;
+                    st->reason = phase2 ? HALT_BREAKDOWN_H : HALT_BREAKDOWN_G;
+                    if (phase2) st->pb_mode = PB_X_ONLY;
+                }
+                return;
+            }
+            __syncthreads();  // all waves have read the block
+            if (lane < 16) {
+                if (w == 0) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) zt[o + i * LD + j] = Z[i];
+                } else if (w == 1) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) th[o + i * LD + j] = A[i];
+                } else if (w == 2) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        if (j == k) {
+                            dsh[16 * h + k] = d[k];
+                            ish[16 * h + k] = id[k];
+                        }
+                }
+            }
+        }
+        __syncthreads();
+        Z2 v{0.0, 0.0};
+        if (h == 0) {
+            // T = Z1 A12
+            rows_product<1>(&v, &zt[i * LD + j], [&](int m) { return th[m * LD + 16 + j]; });
+            tt[i * TD + j] = v;
+            __syncthreads();
+            // S = A22 - T^H D1^{-1} T, U = L21 Z1 (kept in the upper right block of th), L21 D1 = T^H
+            const Z2 a = zconj(tt[j * TD + i]);
+            Z2 u{0.0, 0.0};
+            v = th[(16 + i) * LD + 16 + j];
+            rows_product<1>(&v, &a, [&](int k) {
+                const Z2 t = tt[k * TD + j];
+                const double s = -ish[k];
+                return Z2{t.re * s, t.im * s};
+            });
+            rows_product<1>(&u, &a, [&](int k) {
+                const Z2 z = zt[k * LD + j];
+                const double s = ish[k];
+                return Z2{z.re * s, z.im * s};
+            });
+            ts[i * TD + j] = v;
+            th[i * LD + 16 + j] = u;
+            th[(16 + i) * LD + j] = a;
+        } else {
+            // Z21 = -Z2 U
+            const Z2 z = zt[o + i * LD + j], a{-z.re, -z.im};
+            rows_product<1>(&v, &a, [&](int m) { return th[m * LD + 16 + j]; });
+            zt[(16 + i) * LD + j] = v;
+        }
+        __syncthreads();
+    }
+    const int i0 = 8 * w + 4 * (lane >> 5);  // the lane's four rows of the results, w / 2 their tile
+    Z2 v[4] = {}, a[4];
+    if (!phase2) {
+        // beta = Z^H D^{-1} Z (Z[k][i] = 0 for k < i), then beta C
+#pragma unroll 1
+        for (int kt = w / 2; kt < 2; ++kt) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] = zconj(zt[(16 * kt + j) * LD + i0 + r]);
+            const Z2* zc = zt + 16 * kt * LD + col;
+            const double* ik = ish + 16 * kt;
+            rows_product<4>(v, a, [&](int k) {
+                const Z2 z = zc[k * LD];
+                const double s = ik[k];
+                return Z2{z.re * s, z.im * s};
+            });
+        }
+        Z2 bc[4] = {};
+#pragma unroll 1
+        for (int mt = 0; mt < 2; ++mt) {
+            // column tile mt of the rows of beta on both rows of lanes
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const Z2 x{__shfl_xor(v[r].re, 16, 64), __shfl_xor(v[r].im, 16, 64)};
+                a[r] = q == mt ? v[r] : x;
+            }
+            const Z2* c = tc + 16 * mt * LD + col;
+            rows_product<4>(bc, a, [&](int m) { return c[m * LD]; });
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (col < N && i0 + r < N) {
+                gst(out1 + (i0 + r) * MAXN + col, v[r]);
+                gst(out2 + (i0 + r) * MAXN + col, bc[r]);
+            }
+        return;
+    }
+    // C <- S C = D^{-1/2} (L D)^H C, S^H = L and S^{-1} = (L^{-1})^H
+#pragma unroll 1
+    for (int mt = w / 2; mt < 2; ++mt) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            a[r] = 16 * mt + j >= i0 + r ? zconj(th[(16 * mt + j) * LD + i0 + r]) : Z2{0.0, 0.0};
+        const Z2* c = tc + 16 * mt * LD + col;
+        rows_product<4>(v, a, [&](int m) { return c[m * LD]; });
+    }
+    const double dj = dsh[col], rj = rsqrt_nr(dj);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + r;
+        const double ri = rsqrt_nr(dsh[i]);
+        if (col < N && i < N) {
+            const Z2 l = th[i * LD + col], z = zt[i * LD + col];
+            gst(C + i * MAXN + col, col >= i ? Z2{v[r].re * ri, v[r].im * ri} : Z2{0.0, 0.0});
+            gst(out2 + i * MAXN + col, i > col ? Z2{l.re * rj, l.im * rj} : Z2{i == col ? dj * rj : 0.0, 0.0});
+            // row col of S^{-1}: conj(L^{-1}[i][col]), column i
+            gst(out1 + col * MAXN + i, col <= i ? Z2{z.re * ri, -z.im * ri} : Z2{0.0, 0.0});
+        }
+    }
+    if (threadIdx.x == 0) st->pb_mode = PB_FULL;
+}
+
 // End of a reliable update: with C^ in SH (upper) and C_k in C, S^ = C^ C_k^{-1},
 // C <- C^, SH <- S^^H, and the iteration resumes.  A, W: LDS N x N scratch.
 __device__ void ru_set_s(double2* __restrict__ C, double2* __restrict__ SH, Z2* A, Z2* W, SolveState* st,
@@ -1215,6 +1451,11 @@ hipError_t launch_small1(const double2* G, const double2* C, double2* beta, doub
         return hipGetLastError();
     }
     if (parts) return hipErrorInvalidValue;
+    if (N <= 32 && req == 0) {
+        hipLaunchKernelGGL(k_small_row2, dim3(1), dim3(SMALL_ROW2_THREADS), 0, s, false, G, const_cast<double2*>(C), beta,
+                           betaC, st, N);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_small1, dim3(1), dim3(small_threads(N, req)), small_lds(N), s, G, C, beta, betaC, st, N);
     return hipGetLastError();
 }
@@ -1226,6 +1467,10 @@ hipError_t launch_small2(const double2* H, double2* C, double2* Sinv, double2* S
         return hipGetLastError();
     }
     if (parts) return hipErrorInvalidValue;
+    if (N <= 32 && req == 0) {
+        hipLaunchKernelGGL(k_small_row2, dim3(1), dim3(SMALL_ROW2_THREADS), 0, s, true, H, C, Sinv, SH, st, N);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_small2, dim3(1), dim3(small_threads(N, req)), small_lds(N), s, H, C, Sinv, SH, st, N);
     return hipGetLastError();
 }

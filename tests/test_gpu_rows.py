@@ -69,7 +69,7 @@ def test_row_sloppy_apply_matches_emulation(prec, n):
     assert site_scaled_err(ctx.apply_prec(prec, to_dev(B)).cpu().numpy(), ref) <= SLOPPY_TOL[prec]
 
 
-@pytest.mark.parametrize("n", [5, 8, 9, 16, 24, 32, 40, 64])
+@pytest.mark.parametrize("n", [5, 8, 9, 16, 17, 24, 32, 40, 64])
 def test_row_iterates_match_oracle(n):
     """Three iterations with a reliable update forced in (Gram, passes A and B, block
     multiply and column norms at every tile count), FP64 storage and CholQR2."""
