@@ -599,9 +599,11 @@ k_small2(const double2* __restrict__ H, double2* __restrict__ C, double2* __rest
 // The workgroup kernels above spend their time in a chain of an LDS read, a pivot, an
 // update and a barrier per step.  Here lane j holds column j, so a step needs the pivot
 // (one broadcast, one reciprocal) and multiply-adds that broadcast column k themselves:
-// each of the four waves factors the matrix on its own and they divide the rows of the
-// results, with two barriers in the whole kernel.  Both phases together, per iteration:
-// N = 16 26.6 -> 21.7 us, N = 8 15.6 -> 9.8 us, N = 4 8.5 -> 6.5 us.
+// each of four waves factors the matrix on its own, and for the results each of their 16
+// rows of lanes takes one row.  Both phases together, us an iteration, against the kernels
+// above: N = 16 26.6 -> 15.9, N = 8 15.6 -> 9.6, N = 4 8.5 -> 7.9 with the sums of the Gram
+// partials (N = 16 with a wave's rows of lanes all at the same four rows, in registers:
+// 18.1, and 88 KB of code against 32).
 // ---------------------------------------------------------------------------------------------
 template <int... I, typename F> __device__ __forceinline__ void unroll_(std::integer_sequence<int, I...>, F&& f) {
     (f(std::integral_constant<int, I>{}), ...);
@@ -655,13 +657,14 @@ __device__ __forceinline__ void stage16(const double2* __restrict__ H, int P, co
     }
 }
 
-// lane j: column j of the Hermitian part of t
+// the Hermitian part of t: one entry, and column j
+template <int NN> __device__ __forceinline__ Z2 herm_entry(const Z2* t, int i, int j) {
+    const Z2 a = t[i * (NN + 1) + j], b = t[j * (NN + 1) + i];
+    return Z2{0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
+}
 template <int NN> __device__ __forceinline__ void herm_column(const Z2* t, int j, Z2 A[NN]) {
 #pragma unroll
-    for (int i = 0; i < NN; ++i) {
-        const Z2 a = t[i * (NN + 1) + j], b = t[j * (NN + 1) + i];
-        A[i] = Z2{0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
-    }
+    for (int i = 0; i < NN; ++i) A[i] = herm_entry<NN>(t, i, j);
 }
 
 // 1 / d and 1 / sqrt(d) for a positive normal d: the hardware estimate and two Newton
@@ -705,10 +708,11 @@ template <int NN> __device__ __forceinline__ bool ldl16(Z2 A[NN], Z2 Z[NN], doub
     return ok;
 }
 
-// f(integral_constant<int, w>) for the wave's own w < W
-template <int W, typename F> __device__ __forceinline__ void wave_case(int w, F&& f) {
-    unroll<W>([&](auto wc) {
-        if (w == decltype(wc)::value) f(wc);
+// acc[r] += sum over m < M of w[r](lane m) * f(m), r < R
+template <int R, int M = 16, typename F> __device__ __forceinline__ void rows_product(Z2* acc, const Z2* w, F&& f) {
+    unroll<M>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        row_mac<R, m>(acc, w, f(m));
     });
 }
 
@@ -720,7 +724,8 @@ template <int NN>
 __global__ void __launch_bounds__(SMALL_ROW_THREADS)
 k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restrict__ C, double2* __restrict__ out1,
             double2* __restrict__ out2, SolveState* st, int N) {
-    __shared__ Z2 th[NN * (NN + 1)], tc[NN * (NN + 1)];
+    constexpr int LD = NN + 1;
+    __shared__ Z2 th[NN * LD], tc[NN * LD], zt[NN * LD];
     __shared__ double tn[4][NN];
     const int j = threadIdx.x & (NN - 1);
     const int halt = st->halt, iters = st->iters, best_it0 = st->best_it, ru_window = st->ru_window;
@@ -733,28 +738,21 @@ k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restri
     }
     __syncthreads();
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = (4 * w + ((threadIdx.x >> 4) & 3)) & (NN - 1);  // row of the lane in the products
     Z2 A[NN];
     herm_column<NN>(th, j, A);
     if (phase2) {
-        // (C^H H C)_jj, rows m = 4 w ... 4 w + 3 of H C by wave w
-        wave_case<NN / 4>(w, [&](auto wc) {
-            constexpr int m0 = 4 * decltype(wc)::value;
-            Z2 hc[4] = {};
-            unroll<NN>([&](auto nc) {
-                constexpr int n = decltype(nc)::value;
-                row_mac<4, n>(hc, A + m0, tc[n * (NN + 1) + j]);
-            });
-            double t = 0.0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const Z2 c = tc[(m0 + r) * (NN + 1) + j];
-                t += c.re * hc[r].re + c.im * hc[r].im;
-            }
-            tn[m0 / 4][j] = t;
-        });
+        // (C^H H C)_jj, row i of H C
+        const Z2 a = herm_entry<NN>(th, i, j);
+        Z2 hc{0.0, 0.0};
+        rows_product<1, NN>(&hc, &a, [&](int n) { return tc[n * LD + j]; });
+        const Z2 c = tc[i * LD + j];
+        double t = c.re * hc.re + c.im * hc.im;
+        t += __shfl_xor(t, 16, 64);
+        t += __shfl_xor(t, 32, 64);
+        if (w < NN / 4) tn[w][j] = t;
         __syncthreads();
-        if (w >= NN / 4) return;
-        double t = 0.0;
+        t = 0.0;
 #pragma unroll
         for (int q = 0; q < NN / 4; ++q) t += tn[q][j];
         const double rel = j < N ? sqrt(fmax(t, 0.0)) / bn : 0.0;
@@ -781,12 +779,12 @@ k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restri
             }
         }
         if (decision != HALT_NONE) return;
-    } else if (w >= NN / 4) {
-        return;
     }
     Z2 Z[NN];
     double d[NN], id[NN];
-    if (!ldl16<NN>(A, Z, d, id, j)) {
+    // four waves factor (more would share their SIMDs)
+    const bool bad = w < NN / 4 && !ldl16<NN>(A, Z, d, id, j);
+    if (__syncthreads_or(bad)) {
         if (threadIdx.x == 0) {
             st->halt = 1;
             st->reason = phase2 ? HALT_BREAKDOWN_H : HALT_BREAKDOWN_G;
@@ -794,55 +792,53 @@ k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restri
         }
         return;
     }
-    const bool mine = (threadIdx.x & 63) < NN && j < N;
-    if (!phase2) {
-        wave_case<NN / 4>(w, [&](auto wc) {
-            // rows i = 4 w ... 4 w + 3 of beta = Z^H D^{-1} Z (Z[k][i] = 0 for k < i)
-            constexpr int i0 = 4 * decltype(wc)::value;
-            Z2 b[4] = {}, bc[4] = {};
-            unroll<NN - i0>([&](auto kc) {
-                constexpr int k = i0 + decltype(kc)::value;
-                constexpr int R = k - i0 + 1 < 4 ? k - i0 + 1 : 4;
-                row_cmac<R, i0>(b, Z[k], Z2{Z[k].re * id[k], Z[k].im * id[k]});
-            });
-            unroll<NN>([&](auto mc) {
-                constexpr int m = decltype(mc)::value;
-                row_mac<4, m>(bc, b, tc[m * (NN + 1) + j]);
-            });
+    // every row of lanes takes one row of the results: its operand is a column of L^{-1} or
+    // of L D, which the waves' registers hold by rows
+    if ((threadIdx.x & 63) < NN) {
+        if (w == 0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (mine && i0 + r < N) {
-                    gst(out1 + (i0 + r) * MAXN + j, b[r]);
-                    gst(out2 + (i0 + r) * MAXN + j, bc[r]);
-                }
+            for (int k = 0; k < NN; ++k) zt[k * LD + j] = Z[k];
+        } else if (w == 1 && phase2) {
+#pragma unroll
+            for (int k = 0; k < NN; ++k) th[k * LD + j] = A[k];
+        }
+    }
+    __syncthreads();
+    if (w >= NN / 4) return;
+    const bool mine = (NN == 16 || (threadIdx.x & 8) == 0) && i < N && j < N;
+    if (!phase2) {
+        // beta = Z^H D^{-1} Z, then beta C
+        const Z2 a = zconj(zt[j * LD + i]);
+        Z2 b{0.0, 0.0}, bc{0.0, 0.0};
+        unroll<NN>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            row_mac<1, k>(&b, &a, Z2{Z[k].re * id[k], Z[k].im * id[k]});
         });
+        rows_product<1, NN>(&bc, &b, [&](int m) { return tc[m * LD + j]; });
+        if (mine) {
+            gst(out1 + i * MAXN + j, b);
+            gst(out2 + i * MAXN + j, bc);
+        }
         return;
     }
-    double dj = d[0];
+    double dj = d[0], di = d[0];
 #pragma unroll
-    for (int k = 1; k < NN; ++k) dj = j == k ? d[k] : dj;
-    const double rj = rsqrt_nr(dj);
-    wave_case<NN / 4>(w, [&](auto wc) {
-        // rows i = 4 w ... of S = L^H, C <- S C = D^{-1/2} (L1 D)^H C, S^{-1} = (D^{-1/2} Z)^H
-        constexpr int i0 = 4 * decltype(wc)::value;
-        Z2 s[4] = {};
-        unroll<NN - i0>([&](auto mc) {
-            constexpr int m = i0 + decltype(mc)::value;
-            constexpr int R = m - i0 + 1 < 4 ? m - i0 + 1 : 4;
-            row_cmac<R, i0>(s, A[m], tc[m * (NN + 1) + j]);
-        });
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = i0 + r;
-            const double ri = rsqrt_nr(d[i]);
-            if (mine && i < N) {
-                gst(C + i * MAXN + j, j >= i ? Z2{s[r].re * ri, s[r].im * ri} : Z2{0.0, 0.0});
-                gst(out2 + i * MAXN + j, i > j ? Z2{A[i].re * rj, A[i].im * rj} : Z2{i == j ? dj * rj : 0.0, 0.0});
-                // row j of S^{-1}: conj(L^{-1}[i][j]), column i
-                gst(out1 + j * MAXN + i, j <= i ? Z2{Z[i].re * ri, -Z[i].im * ri} : Z2{0.0, 0.0});
-            }
-        }
-    });
+    for (int k = 1; k < NN; ++k) {
+        dj = j == k ? d[k] : dj;
+        di = i == k ? d[k] : di;
+    }
+    const double rj = rsqrt_nr(dj), ri = rsqrt_nr(di);
+    // S = L^H, C <- S C = D^{-1/2} (L1 D)^H C, S^{-1} = (D^{-1/2} Z)^H
+    const Z2 a = j >= i ? zconj(th[j * LD + i]) : Z2{0.0, 0.0};
+    Z2 v{0.0, 0.0};
+    rows_product<1, NN>(&v, &a, [&](int m) { return tc[m * LD + j]; });
+    if (mine) {
+        const Z2 l = th[i * LD + j], z = zt[i * LD + j];
+        gst(C + i * MAXN + j, j >= i ? Z2{v.re * ri, v.im * ri} : Z2{0.0, 0.0});
+        gst(out2 + i * MAXN + j, i > j ? Z2{l.re * rj, l.im * rj} : Z2{i == j ? dj * rj : 0.0, 0.0});
+        // row j of S^{-1}: conj(L^{-1}[i][j]), column i
+        gst(out1 + j * MAXN + i, j <= i ? Z2{z.re * ri, -z.im * ri} : Z2{0.0, 0.0});
+    }
     if (threadIdx.x == 0) st->pb_mode = PB_FULL;
 }
 
@@ -857,14 +853,6 @@ k_small_row(bool phase2, const double2* __restrict__ H, int P, double2* __restri
 // doing the same rows 61 and 56; with the products as calls of one function 80 and 77).
 // ---------------------------------------------------------------------------------------------
 constexpr int SMALL_ROW2_THREADS = 256;
-
-// acc[r] += sum over m < 16 of w[r](lane m) * f(m), r < R
-template <int R, typename F> __device__ __forceinline__ void rows_product(Z2* acc, const Z2* w, F&& f) {
-    unroll<16>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        row_mac<R, m>(acc, w, f(m));
-    });
-}
 
 __global__ void __launch_bounds__(SMALL_ROW2_THREADS)
 k_small_row2(bool phase2, const double2* __restrict__ H, double2* __restrict__ C, double2* __restrict__ out1,
