@@ -293,7 +293,7 @@ int bcg_set_stability(bcg_ctx *ctx, int ru_window, int stall_limit, int qr_passe
  *                         N > 8, 2: on the vector ALUs
  *   BCG_OPT_SMALL_THREADS threads (64, 256, 1024) of the one-workgroup N x N
  *                         kernels, used when N^2 <= 4 x threads; 0 (default):
- *                         256 for N <= 16, else 1024
+ *                         the kernels on rows of lanes for N <= 32, else 1024
  *   BCG_OPT_SITE_ORDER    1: workgroups walk the lattice so that XCD x takes the
  *                         x-th eighth of every time slice and all XCDs sweep the
  *                         slices together, 2: plain lexicographic order
@@ -314,6 +314,11 @@ int bcg_set_stability(bcg_ctx *ctx, int ru_window, int stall_limit, int qr_passe
  *                         consecutive blocks of neighbouring lattice cells, then
  *                         help drain the other XCDs' queues) with 1, 2, 4 or 8
  *                         workgroups per CU in a persistent grid
+ * Without any of the options that name a kernel of the plane layout (all but
+ * BCG_OPT_SMALL_THREADS and BCG_OPT_GRAPH), blocks of 5 or more columns, and of 2
+ * or more on up to 8192 sites of a parity, run in the row layout (columns of a site
+ * side by side); one of those options set to a non-zero value selects the plane
+ * kernels it belongs to for the whole context.
  * Returns BCG_ERR_ARG for an unknown option. */
 enum { BCG_OPT_HOP_TR = 0, BCG_OPT_HOP_TPB = 1, BCG_OPT_HOP_PIPELINE = 2, BCG_OPT_PASS_CPT = 3,
        BCG_OPT_FUSE_GRAM = 4, BCG_OPT_HOP_KERNEL = 5, BCG_OPT_GRAM_KERNEL = 6, BCG_OPT_SMALL_THREADS = 7,

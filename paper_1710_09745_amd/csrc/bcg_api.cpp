@@ -299,8 +299,8 @@ int dot_parts(bcg_ctx* ctx, Prec p) {
     return (int)((ctx->Vh + sites - 1) / sites);
 }
 
-// a lattice so large that no block of more than 4 columns fits the row layout keeps its
-// links in the plane layout only
+// a lattice so large that no block of 5 columns fits the row layout keeps its links in
+// the plane layout only
 bool rows_ever(bcg_ctx* ctx) { return rows_fit(5, ctx->Vh); }
 
 // the largest half-volume of bcg_apply_noalloc (one column): these contexts own the

@@ -6,7 +6,7 @@
 // with Y_X = D_oe X, Y_L = D_oe Lam on the odd sites; output in the canonical
 // [4][V][3][3] layout.
 //
-// k_link_force_rows (row layout, more than 4 columns): a wave takes 4 sites x 16
+// k_link_force_rows (row layout): a wave takes 4 sites x 16
 // columns per tile (half rows: 8 x 8), keeps the two vectors of its sites in registers
 // for all directions, and sums the outer products of a lane's columns there; the lanes
 // of a site meet through LDS, 16 bytes per entry and lane, and store a link's nine
@@ -161,7 +161,9 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
                         site_coords(g, site, p, xs);
                         const long ls = xs[0] + (long)st[1] * xs[1] + (long)st[2] * xs[2] + (long)st[3] * xs[3];
                         const double sg = (double)eta_sign(xs, mu) * (p == 0 ? 1.0 : -1.0);
-                        out[((long)mu * 2 * g.Vh + ls) * 9 + e] = make_double2(sg * r.re, sg * r.im);
+                        typedef double pair_t __attribute__((ext_vector_type(2)));
+                        __builtin_nontemporal_store(pair_t{sg * r.re, sg * r.im},
+                                                    reinterpret_cast<pair_t*>(out + ((long)mu * 2 * g.Vh + ls) * 9 + e));
                     }
                 }
             }
