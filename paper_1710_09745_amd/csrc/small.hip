@@ -1431,15 +1431,20 @@ hipError_t launch_sstep_coef(const double2* Gv, const double2* Gvv, const double
 // the many workgroups of k_gram_reduce win back their launch.
 bool small_sums_parts(int N, int parts, int req) { return req == 0 && N <= 16 && parts <= (N <= 8 ? 256 : 128); }
 
+// N <= 16 on a row of lanes, but one or two columns whose Gram is summed already: there the
+// workgroup kernel has a step or two and no N x N arithmetic to speak of (16^4, N = 1, an
+// iteration: 67.8 us on a row of lanes, 64.7 as a workgroup)
+static bool small_on_row(int N, int parts) { return N <= 16 && (N > 2 || parts > 0); }
+
 hipError_t launch_small1(const double2* G, const double2* C, double2* beta, double2* betaC,
                          SolveState* st, int N, int req, int parts, hipStream_t s) {
-    if (N <= 16 && req == 0) {
+    if (small_on_row(N, parts) && req == 0) {
         auto k = N <= 8 ? k_small_row<8> : k_small_row<16>;
         hipLaunchKernelGGL(k, dim3(1), dim3(SMALL_ROW_THREADS), 0, s, false, G, parts, const_cast<double2*>(C), beta, betaC, st, N);
         return hipGetLastError();
     }
     if (parts) return hipErrorInvalidValue;
-    if (N <= 32 && req == 0) {
+    if (N > 16 && N <= 32 && req == 0) {
         hipLaunchKernelGGL(k_small_row2, dim3(1), dim3(SMALL_ROW2_THREADS), 0, s, false, G, const_cast<double2*>(C), beta,
                            betaC, st, N);
         return hipGetLastError();
@@ -1449,13 +1454,13 @@ hipError_t launch_small1(const double2* G, const double2* C, double2* beta, doub
 }
 hipError_t launch_small2(const double2* H, double2* C, double2* Sinv, double2* SH, SolveState* st,
                          int N, int req, int parts, hipStream_t s) {
-    if (N <= 16 && req == 0) {
+    if (small_on_row(N, parts) && req == 0) {
         auto k = N <= 8 ? k_small_row<8> : k_small_row<16>;
         hipLaunchKernelGGL(k, dim3(1), dim3(SMALL_ROW_THREADS), 0, s, true, H, parts, C, Sinv, SH, st, N);
         return hipGetLastError();
     }
     if (parts) return hipErrorInvalidValue;
-    if (N <= 32 && req == 0) {
+    if (N > 16 && N <= 32 && req == 0) {
         hipLaunchKernelGGL(k_small_row2, dim3(1), dim3(SMALL_ROW2_THREADS), 0, s, true, H, C, Sinv, SH, st, N);
         return hipGetLastError();
     }
