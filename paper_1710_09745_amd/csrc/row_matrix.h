@@ -1,7 +1,8 @@
 // Register arithmetic on 16 x 16 complex matrices spread over a row of 16 lanes: lane j
 // holds column j, register i row i, so that entry (i, K) reaches every lane of the row
 // through the DPP row broadcast of lane K inside the multiply-add (v_fmac_f64_dpp,
-// row_newbcast), without LDS, shuffles or barriers.  All four rows of a wave do the same.
+// row_newbcast), without LDS, shuffles or barriers.  In a factorisation all four rows of a
+// wave do the same, in a product each may hold rows of w of its own.
 // Each block opens with the two wait states that a vector write of a DPP operand needs,
 // and its outputs are early-clobber, as later lines still read the inputs.
 #pragma once
@@ -99,82 +100,12 @@ template <int K> __device__ __forceinline__ void row_elim4(C2<double>* a, C2<dou
         : "+&v"(a[0].re), "+&v"(a[0].im), "+&v"(a[1].re), "+&v"(a[1].im), "+&v"(a[2].re), "+&v"(a[2].im), "+&v"(a[3].re), "+&v"(a[3].im)
         : "v"(m.re), "v"(m.im), "n"(K));
 }
-// acc[r] += conj(w(lane K + r)) * v, r < 1
-template <int K> __device__ __forceinline__ void row_cmac1(C2<double>* acc, C2<double> w, C2<double> v) {
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, -%3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
-        : "+&v"(acc[0].re), "+&v"(acc[0].im)
-        : "v"(w.re), "v"(w.im), "v"(v.re), "v"(v.im), "n"(K + 0));
-}
-// acc[r] += conj(w(lane K + r)) * v, r < 2
-template <int K> __device__ __forceinline__ void row_cmac2(C2<double>* acc, C2<double> w, C2<double> v) {
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %4, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %5, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %5, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, -%5, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, -%5, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-        : "+&v"(acc[0].re), "+&v"(acc[0].im), "+&v"(acc[1].re), "+&v"(acc[1].im)
-        : "v"(w.re), "v"(w.im), "v"(v.re), "v"(v.im), "n"(K + 0), "n"(K + 1));
-}
-// acc[r] += conj(w(lane K + r)) * v, r < 3
-template <int K> __device__ __forceinline__ void row_cmac3(C2<double>* acc, C2<double> w, C2<double> v) {
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %6, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %4, %6, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %6, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %6, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %5, %6, %9 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %7, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %7, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %4, %7, %9 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, -%7, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, -%7, %8 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %5, -%7, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf"
-        : "+&v"(acc[0].re), "+&v"(acc[0].im), "+&v"(acc[1].re), "+&v"(acc[1].im), "+&v"(acc[2].re), "+&v"(acc[2].im)
-        : "v"(w.re), "v"(w.im), "v"(v.re), "v"(v.im), "n"(K + 0), "n"(K + 1), "n"(K + 2));
-}
-// acc[r] += conj(w(lane K + r)) * v, r < 4
-template <int K> __device__ __forceinline__ void row_cmac4(C2<double>* acc, C2<double> w, C2<double> v) {
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %8, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %8, %10 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %4, %8, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %6, %8, %10 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %8, %11 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %8, %11 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %5, %8, %11 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %7, %8, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %9, %11 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %9, %11 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %4, %9, %11 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %6, %9, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, -%9, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, -%9, %10 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %5, -%9, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %7, -%9, %10 row_newbcast:%15 row_mask:0xf bank_mask:0xf"
-        : "+&v"(acc[0].re), "+&v"(acc[0].im), "+&v"(acc[1].re), "+&v"(acc[1].im), "+&v"(acc[2].re), "+&v"(acc[2].im), "+&v"(acc[3].re), "+&v"(acc[3].im)
-        : "v"(w.re), "v"(w.im), "v"(v.re), "v"(v.im), "n"(K + 0), "n"(K + 1), "n"(K + 2), "n"(K + 3));
-}
 
 template <int R, int K> __device__ __forceinline__ void row_mac(C2<double>* acc, const C2<double>* w, C2<double> v) {
     if constexpr (R == 1) row_mac1<K>(acc, w, v);
     else if constexpr (R == 2) row_mac2<K>(acc, w, v);
     else if constexpr (R == 3) row_mac3<K>(acc, w, v);
     else row_mac4<K>(acc, w, v);
-}
-template <int R, int K> __device__ __forceinline__ void row_cmac(C2<double>* acc, C2<double> w, C2<double> v) {
-    if constexpr (R == 1) row_cmac1<K>(acc, w, v);
-    else if constexpr (R == 2) row_cmac2<K>(acc, w, v);
-    else if constexpr (R == 3) row_cmac3<K>(acc, w, v);
-    else row_cmac4<K>(acc, w, v);
 }
 
 // The value of lane K of each row of 16 lanes (in assembly, with the wait states, as x may
