@@ -105,7 +105,14 @@ int bcg_destroy(bcg_ctx *ctx);
  * 0 = host pointers, 1 = device pointers.  The data is copied; the staggered
  * phases and the hop signs are folded into library-owned copies for each
  * output parity and each storage precision.  Synchronous w.r.t. the inputs
- * (they may be freed on return). */
+ * (they may be freed on return).
+ * The FP64 copy is kept in two layouts, one for the calls on few columns and one
+ * for the others (2304 bytes each per site of the lattice with long links, half of
+ * that without).  Both are written here, in the memory that the first load took, so a
+ * captured bcg_apply_noalloc replays with the links loaded last.  Above 349525 sites
+ * of a parity the second one is taken only if it is at most a quarter of the memory
+ * still free, and given back to an allocation that would fail beside it; every call
+ * then runs on the first. */
 int bcg_load_links(bcg_ctx *ctx, const void *fat, const void *lng, int on_device);
 
 /* Set the mass m of A = 4 m^2 - D_eo D_oe (any real m; m = 0 gives the

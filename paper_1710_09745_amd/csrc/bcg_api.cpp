@@ -71,9 +71,7 @@ struct bcg_ctx {
     int qr_passes = 1;        // 1: CholQR, 2: CholQR2 in the initial and reliable-update QR
     bool links = false;
     void* W64[2] = {nullptr, nullptr};
-    bool planes = false;                 // W64 holds the loaded links
-    void* W64r[2] = {nullptr, nullptr};  // the FP64 links in the row layout (rows.h); W64 is
-                                         // made from them by the first call that needs it
+    void* W64r[2] = {nullptr, nullptr};  // the FP64 links in the row layout (rows.h); null: planes only
     void* Wsl[2] = {nullptr, nullptr};
     Prec wsl_prec = Prec::FP64;
     void* Wslr[2] = {nullptr, nullptr};  // sloppy links in the row layout
@@ -141,6 +139,35 @@ int fail(bcg_ctx* c, int code, const std::string& msg) {
         if (r_ != BCG_OK) return r_;     \
     } while (0)
 
+// The largest half-volume of bcg_apply_noalloc (one column).  A graph may hold that call,
+// so contexts up to this size keep their links where they are.
+constexpr long NOALLOC_SITES = (long)(SCRATCH_REGION / 48);
+
+// Gives the row-layout links back for an allocation that does not fit beside them; every
+// call then runs on the planes, until links are loaded again.
+bool drop_rows(bcg_ctx* ctx) {
+    if (!ctx->W64r[0] || ctx->Vh <= NOALLOC_SITES || hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+    (void)hipFree(ctx->W64r[0]);
+    ctx->W64r[0] = ctx->W64r[1] = nullptr;
+    for (void*& w : ctx->Wslr) {
+        if (w) (void)hipFree(w);
+        w = nullptr;
+    }
+    return true;
+}
+
+// device memory, if need be in place of the row-layout links; *p is null on failure
+bool device_alloc(bcg_ctx* ctx, void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();  // (a launch reports the last error)
+        *p = nullptr;
+        if (drop_rows(ctx)) e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) *p = nullptr;
+    return e == hipSuccess;
+}
+
 int ensure(bcg_ctx* ctx, int slot, size_t bytes) {
     Buf& b = ctx->work[slot];
     if (b.bytes >= bytes) return BCG_OK;
@@ -150,10 +177,8 @@ int ensure(bcg_ctx* ctx, int slot, size_t bytes) {
         b.p = nullptr;
         b.bytes = 0;
     }
-    if (hipMalloc(&b.p, bytes) != hipSuccess) {
-        b.p = nullptr;
+    if (!device_alloc(ctx, &b.p, bytes))
         return fail(ctx, BCG_ERR_NOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
-    }
     b.bytes = bytes;
     return BCG_OK;
 }
@@ -271,12 +296,13 @@ long nvec(bcg_ctx* ctx, int N) { return (long)N * 3 * ctx->Vh; }
 bool gram_mfma(bcg_ctx* ctx) { return ctx->opt[BCG_OPT_GRAM_KERNEL] != 2; }
 
 // The row layout (rows.h) for N columns, unless an option asks for one of the plane
-// kernels (its launch shapes and variants are theirs).
+// kernels (its launch shapes and variants are theirs) or there was no room for its links.
+// Asked for after a call's allocations, which may take that room back.
 bool use_rows(bcg_ctx* ctx, int N) {
     for (int o : {BCG_OPT_HOP_TR, BCG_OPT_HOP_TPB, BCG_OPT_HOP_PIPELINE, BCG_OPT_PASS_CPT, BCG_OPT_FUSE_GRAM,
                   BCG_OPT_HOP_KERNEL, BCG_OPT_GRAM_KERNEL, BCG_OPT_SITE_ORDER, BCG_OPT_PASS_KERNEL, BCG_OPT_HOP_SCHED})
         if (ctx->opt[o]) return false;
-    return rows_fit(N, ctx->Vh);
+    return ctx->W64r[0] != nullptr && rows_fit(N, ctx->Vh);
 }
 
 // 64-site blocks per time slice for the XCD order of the streaming passes
@@ -299,41 +325,27 @@ int dot_parts(bcg_ctx* ctx, Prec p) {
     return (int)((ctx->Vh + sites - 1) / sites);
 }
 
-// a lattice so large that no block of 5 columns fits the row layout keeps its links in
-// the plane layout only
-bool rows_ever(bcg_ctx* ctx) { return rows_fit(5, ctx->Vh); }
-
-// the largest half-volume of bcg_apply_noalloc (one column): these contexts own the
-// memory of both link layouts from bcg_load_links on, as that call may not allocate
-constexpr long NOALLOC_SITES = (long)(SCRATCH_REGION / 48);
-
 // FP64 links of both parities, in one allocation that w[0] owns
-int alloc_links(bcg_ctx* ctx, void** w) {
-    if (w[0]) return BCG_OK;
+bool alloc_links(bcg_ctx* ctx, void** w) {
     const size_t bytes = (size_t)ctx->nl * 9 * ctx->Vh * 16;
-    if (hipMalloc(&w[0], 2 * bytes) != hipSuccess) {
-        w[0] = nullptr;
-        return fail(ctx, BCG_ERR_NOMEM, "link allocation failed");
-    }
+    if (!w[0] && !device_alloc(ctx, &w[0], 2 * bytes)) return false;
     w[1] = (char*)w[0] + bytes;
-    return BCG_OK;
+    return true;
 }
 
-// FP64 links in the plane layout, made from the row layout on first use.  Under stream
-// capture the conversion becomes part of the graph and is not taken as done.
-int ensure_plane_links(bcg_ctx* ctx) {
-    if (ctx->planes) return BCG_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIPCK(hipStreamIsCapturing(ctx->stream, &cap));
-    RETCK(alloc_links(ctx, ctx->W64));
-    for (int p = 0; p < 2; ++p) HIPCK(row_links_to_planes(ctx->W64r[p], ctx->W64[p], ctx->nl, ctx->Vh, ctx->stream));
-    ctx->planes = cap == hipStreamCaptureStatusNone;
-    return BCG_OK;
+// Memory for the links in the row layout beside the planes.  None if no block of 5 columns
+// fits that layout, or no allocation, or above NOALLOC_SITES if the copy would take more
+// than a quarter of the memory still free (up to there it is at most 1.6 GB).
+void alloc_row_links(bcg_ctx* ctx) {
+    if (ctx->W64r[0] || !rows_fit(5, ctx->Vh)) return;
+    const size_t bytes = (size_t)2 * ctx->nl * 9 * ctx->Vh * 16;
+    size_t free = 0, total = 0;
+    if (ctx->Vh > NOALLOC_SITES && (hipMemGetInfo(&free, &total) != hipSuccess || free / 4 < bytes)) return;
+    (void)alloc_links(ctx, ctx->W64r);
 }
 
 int hop(bcg_ctx* ctx, Prec p, int out_parity, const void* in, void* out, const void* ctr, int N,
         int epi, const int* halt, double* dot = nullptr, double2* partials = nullptr) {
-    if (p == Prec::FP64) RETCK(ensure_plane_links(ctx));
     const void* Wp = (p == Prec::FP64) ? ctx->W64[out_parity] : ctx->Wsl[out_parity];
     HopShape h = shape(ctx, p, N, partials != nullptr);
     if (epi == EPI_MASS_DOT_) h = dot_shape(ctx, p);
@@ -511,31 +523,33 @@ int read_state(bcg_ctx* ctx) {
     return sync(ctx);
 }
 
-// work vectors of a solve; rows: in the row layout (else the plane links too, before any
-// capture of the iteration)
-int alloc_solve(bcg_ctx* ctx, int N, Prec ps, bool rows = false) {
-    if (!rows) RETCK(ensure_plane_links(ctx));
+// work vectors of a solve (of the same size in both layouts)
+int alloc_solve(bcg_ctx* ctx, int N, Prec ps) {
     const size_t n64 = (size_t)nvec(ctx, N) * 16, nsl = store_bytes(ps, N, 3, ctx->Vh);
     for (int s : {WB_B64, WB_Y, WB_X, WB_R64, WB_T64}) RETCK(ensure(ctx, s, n64));
     for (int s : {WB_P0, WB_P1, WB_Q0, WB_Q1, WB_AP, WB_T}) RETCK(ensure(ctx, s, nsl));
     return BCG_OK;
 }
 
+// links in storage ps, in the row layout or the planes
 int ensure_sloppy_links(bcg_ctx* ctx, Prec ps, bool rows = false) {
     if (ps == Prec::FP64) return BCG_OK;
     void** W = rows ? ctx->Wslr : ctx->Wsl;
     Prec& have = rows ? ctx->wslr_prec : ctx->wsl_prec;
     if (W[0] && have == ps) return BCG_OK;
-    if (!rows) RETCK(ensure_plane_links(ctx));
+    have = Prec::FP64;  // none, until both parities are there
     for (int p = 0; p < 2; ++p) {
         if (W[p]) {
             HIPCK(hipStreamSynchronize(ctx->stream));
             HIPCK(hipFree(W[p]));
             W[p] = nullptr;
         }
-        if (hipMalloc(&W[p], store_bytes(ps, ctx->nl, 9, ctx->Vh)) != hipSuccess) {
-            W[p] = nullptr;
+        if (!device_alloc(ctx, &W[p], store_bytes(ps, ctx->nl, 9, ctx->Vh)))
             return fail(ctx, BCG_ERR_NOMEM, "sloppy link allocation failed");
+        if (rows && !ctx->W64r[0]) {  // the row layout made room for this
+            (void)hipFree(W[p]);
+            W[p] = nullptr;
+            return ensure_sloppy_links(ctx, ps);
         }
         Prof pr(ctx, BCG_K_CONVERT);
         if (rows) HIPCK(row_links_from64(ps, ctx->W64r[p], W[p], ctx->nl, ctx->Vh, ctx->stream));
@@ -810,7 +824,7 @@ int bcg_load_links(bcg_ctx* ctx, const void* fat, const void* lng, int on_device
     void* tmp = nullptr;
     if (!on_device) {
         const size_t tot = bytes * (ctx->improved ? 2 : 1);
-        if (hipMalloc(&tmp, tot) != hipSuccess) return fail(ctx, BCG_ERR_NOMEM, "link staging allocation failed");
+        if (!device_alloc(ctx, &tmp, tot)) return fail(ctx, BCG_ERR_NOMEM, "link staging allocation failed");
         HIPCK(hipMemcpyAsync(tmp, fat, bytes, hipMemcpyHostToDevice, ctx->stream));
         dfat = tmp;
         if (ctx->improved) {
@@ -818,18 +832,15 @@ int bcg_load_links(bcg_ctx* ctx, const void* fat, const void* lng, int on_device
             dlng = (char*)tmp + bytes;
         }
     }
-    const bool rows = rows_ever(ctx);
-    int rc = alloc_links(ctx, rows ? ctx->W64r : ctx->W64);
-    if (rc == BCG_OK && rows && ctx->Vh <= NOALLOC_SITES) rc = alloc_links(ctx, ctx->W64);
-    if (rc != BCG_OK) {
+    if (!alloc_links(ctx, ctx->W64)) {
         if (tmp) (void)hipFree(tmp);
-        return rc;
+        return fail(ctx, BCG_ERR_NOMEM, "link allocation failed");
     }
-    for (int p = 0; p < 2; ++p) {
-        if (rows) HIPCK(pack_links_rows(dfat, dlng, ctx->W64r[p], ctx->g, p, ctx->nl, ctx->stream));
-        else HIPCK(pack_links(dfat, dlng, ctx->W64[p], ctx->g, p, ctx->nl, ctx->stream));
-    }
-    ctx->planes = !rows;
+    // both layouts in every load, so that no later call waits for the other one and a graph
+    // that was captured before finds the new links in either
+    alloc_row_links(ctx);
+    for (int p = 0; p < 2; ++p)
+        HIPCK(pack_links(dfat, dlng, ctx->W64[p], ctx->W64r[p], ctx->g, p, ctx->nl, ctx->stream));
     ctx->wsl_prec = ctx->wslr_prec = Prec::FP64;   // sloppy copies are rebuilt from the new links on demand
     for (void** w : {ctx->Wsl, ctx->Wslr})
         for (int p = 0; p < 2; ++p) {
@@ -912,9 +923,9 @@ int bcg_apply_prec(bcg_ctx* ctx, int prec, const void* in, void* out, int nrhs) 
     RETCK(check_ready(ctx));
     const Prec ps = (Prec)prec;
     if (ps == Prec::FP64) return bcg_apply(ctx, in, out, nrhs);
+    RETCK(alloc_solve(ctx, nrhs, ps));
+    RETCK(ensure_sloppy_links(ctx, ps, use_rows(ctx, nrhs)));
     const BlockOps ops(ctx, nrhs);
-    RETCK(alloc_solve(ctx, nrhs, ps, ops.rows));
-    RETCK(ensure_sloppy_links(ctx, ps, ops.rows));
     double2* I64 = Wd(ctx, WB_B64);
     void *P = W(ctx, WB_P0), *T = W(ctx, WB_T), *AP = W(ctx, WB_AP);
     {
@@ -991,10 +1002,10 @@ int bcg_solve(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, int use_guess, 
     const auto t0 = std::chrono::steady_clock::now();
     const int N = nrhs;
     const Prec ps = ctx->sloppy;
-    const BlockOps ops(ctx, N);
-    RETCK(alloc_solve(ctx, N, ps, ops.rows));
+    RETCK(alloc_solve(ctx, N, ps));
     if (ctx->stall_limit > 0) RETCK(ensure(ctx, WB_YBEST, (size_t)nvec(ctx, N) * 16));
-    RETCK(ensure_sloppy_links(ctx, ps, ops.rows));
+    RETCK(ensure_sloppy_links(ctx, ps, use_rows(ctx, N)));
+    const BlockOps ops(ctx, N);
     const int Vh = (int)ctx->Vh;
     const long n = nvec(ctx, N);
     hipStream_t s = ctx->stream;
@@ -1480,8 +1491,8 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
     const int Vh = (int)ctx->Vh;
     const long n = nvec(ctx, N);
     hipStream_t s = ctx->stream;
+    RETCK(alloc_solve(ctx, N, Prec::FP64));
     const BlockOps ops(ctx, N);
-    RETCK(alloc_solve(ctx, N, Prec::FP64, ops.rows));
     double2 *B64 = Wd(ctx, WB_B64), *X = Wd(ctx, WB_Y), *R = Wd(ctx, WB_R64), *T64 = Wd(ctx, WB_T64),
             *Rt = Wd(ctx, WB_X);
     double2 *P = Wd(ctx, WB_P0), *AP = Wd(ctx, WB_AP), *T = Wd(ctx, WB_T);

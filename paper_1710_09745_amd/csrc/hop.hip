@@ -22,41 +22,56 @@
 
 namespace bcg {
 
-__device__ __forceinline__ int lex_of(const Geom& g, int y0, int y1, int y2, int y3) {
-    return y0 + g.L[0] * (y1 + g.L[1] * (y2 + g.L[2] * y3));
-}
-
-// One thread per (output site, folded matrix k): FP64 folded links.  fat/lng:
-// canonical complex128 [4][V][3][3] on the device; lower precisions are made
-// from these by the group conversion below.
+// The folded FP64 links of one parity from the canonical ones, in the plane layout
+// [NL][9][Vh] and, if Wr is given, in the row layout [Vh][9][NL] as well: one read of the
+// links serves both.  A workgroup takes 256 / NL sites; lane k of a site folds matrix k,
+// which the row layout takes from its registers, the planes through LDS (entry q of site t
+// at q * (SITES + 1) + t), so that either side is whole runs.
+// (A load, us, a kernel for each layout / both here: 16^4 121 / 95, 16^3 x 48 432 / 295,
+// 32^3 x 64 4730 / 3110, where the planes alone, by a lane per site and matrix, took 3050.)
+template <int NL>
 __global__ void __launch_bounds__(256)
-k_pack_links(const double2* __restrict__ fat, const double2* __restrict__ lng,
-             double2* __restrict__ W, Geom g, int parity, int nl) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = blockIdx.y;
-    if (i >= g.Vh || k >= nl) return;
-    int x[4];
-    site_coords(g, i, parity, x);
-    const int mu = nl == 16 ? (k >> 2) : (k >> 1);
-    const int j = nl == 16 ? (k & 3) : (k & 1);
-    const int hop = (j & 2) ? 3 : 1;
-    const bool bwd = j & 1;
-    const double2* U = (j & 2) ? lng : fat;
-    const long V = 2L * g.Vh;
-    int y[4] = {x[0], x[1], x[2], x[3]};
-    if (bwd) {
-        int v = y[mu] - hop;
-        while (v < 0) v += g.L[mu];
-        y[mu] = v;
+k_pack_links(const double2* __restrict__ fat, const double2* __restrict__ lng, double2* __restrict__ Wp,
+             double2* __restrict__ Wr, Geom g, int parity) {
+    constexpr int SITES = 256 / NL, E = 9 * NL;
+    __shared__ double2 tile[E * (SITES + 1)];
+    const int s0 = blockIdx.x * SITES, t = threadIdx.x / NL, k = threadIdx.x % NL;
+    const int i = s0 + t;
+    if (i < g.Vh) {
+        int x[4];
+        site_coords(g, i, parity, x);
+        const int mu = hop_mu<NL>(k), d = hop_d<NL>(k);
+        const bool bwd = d < 0, three = d == 3 || d == -3;
+        const double2* U = three ? lng : fat;
+        int y[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            if (bwd && m == mu) {
+                y[m] += d;
+                while (y[m] < 0) y[m] += g.L[m];
+            }
+        const long lex = y[0] + (long)g.L[0] * (y[1] + (long)g.L[1] * (y[2] + (long)g.L[2] * y[3]));
+        const double2* u = U + ((long)mu * 2 * g.Vh + lex) * 9;
+        const double s = (double)eta_sign(x, mu) * (bwd ? -1.0 : 1.0);
+        double2 e[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) e[q] = u[q];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                // forward: W_ab = s U_ab;  backward: W_ab = s conj(U_ba)
+                const double2 v = bwd ? e[3 * b + a] : e[3 * a + b];
+                const double2 w = make_double2(s * v.x, bwd ? -s * v.y : s * v.y);
+                if (Wr != nullptr) Wr[(long)i * E + (3 * a + b) * NL + k] = w;
+                tile[(9 * k + 3 * a + b) * (SITES + 1) + t] = w;
+            }
     }
-    const long src = ((long)mu * V + lex_of(g, y[0], y[1], y[2], y[3])) * 9;
-    const double s = (double)eta_sign(x, mu) * (bwd ? -1.0 : 1.0);
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-            // forward: W_ab = s U_ab;  backward: W_ab = s conj(U_ba)
-            const double2 u = bwd ? U[src + 3 * b + a] : U[src + 3 * a + b];
-            W[((long)k * 9 + 3 * a + b) * g.Vh + i] = make_double2(s * u.x, bwd ? -s * u.y : s * u.y);
-        }
+    __syncthreads();
+    const int ts = threadIdx.x % SITES;
+    if (s0 + ts < g.Vh)
+        for (int r = threadIdx.x / SITES; r < E; r += 256 / SITES)
+            Wp[(long)r * g.Vh + s0 + ts] = tile[r * (SITES + 1) + ts];
 }
 
 // [cols][K][Vh] groups from FP64 into another storage policy
@@ -77,11 +92,15 @@ k_group_from64(const double2* __restrict__ src, typename SD::pair* __restrict__ 
 // ---------------------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------------------
-hipError_t pack_links(const void* fat, const void* lng, void* W, const Geom& g, int parity, int nl,
+hipError_t pack_links(const void* fat, const void* lng, void* Wp, void* Wr, const Geom& g, int parity, int nl,
                       hipStream_t s) {
-    dim3 grid((g.Vh + 255) / 256, nl);
-    hipLaunchKernelGGL(k_pack_links, grid, dim3(256), 0, s, (const double2*)fat, (const double2*)lng,
-                       (double2*)W, g, parity, nl);
+    const dim3 grid((unsigned)(((long)g.Vh * nl + 255) / 256));
+    if (nl == 16)
+        hipLaunchKernelGGL(k_pack_links<16>, grid, dim3(256), 0, s, (const double2*)fat, (const double2*)lng,
+                           (double2*)Wp, (double2*)Wr, g, parity);
+    else
+        hipLaunchKernelGGL(k_pack_links<8>, grid, dim3(256), 0, s, (const double2*)fat, (const double2*)lng,
+                           (double2*)Wp, (double2*)Wr, g, parity);
     return hipGetLastError();
 }
 

@@ -261,63 +261,6 @@ k_hop_gram_rows(const char* __restrict__ W, const char* __restrict__ in, char* _
     G.template finish<NW, HR>(red, partials + (long)blockIdx.x * LD * LD, LD);
 }
 
-// Row-layout FP64 links of one parity from the canonical ones: a row of lanes per
-// site, lane k folded matrix k (as k_pack_links).
-template <int NL>
-__global__ void __launch_bounds__(256)
-k_pack_links_rows(const double2* __restrict__ fat, const double2* __restrict__ lng, double2* __restrict__ W, Geom g,
-                  int parity) {
-    const long t = (long)blockIdx.x * 256 + threadIdx.x;
-    const int i = (int)(t / NL), k = (int)(t % NL);
-    if (i >= g.Vh) return;
-    int x[4];
-    site_coords(g, i, parity, x);
-    const int mu = hop_mu<NL>(k), d = hop_d<NL>(k);
-    const bool bwd = d < 0, three = d == 3 || d == -3;
-    const double2* U = three ? lng : fat;
-    int y[4] = {x[0], x[1], x[2], x[3]};
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-        if (bwd && m == mu) {
-            y[m] += d;
-            while (y[m] < 0) y[m] += g.L[m];
-        }
-    const long lex = y[0] + (long)g.L[0] * (y[1] + (long)g.L[1] * (y[2] + (long)g.L[2] * y[3]));
-    const double2* u = U + ((long)mu * 2 * g.Vh + lex) * 9;
-    const double s = (double)eta_sign(x, mu) * (bwd ? -1.0 : 1.0);
-    double2 e[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) e[q] = u[q];
-    double2* o = W + (long)i * 9 * NL + k;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double2 v = bwd ? e[3 * b + a] : e[3 * a + b];
-            o[(3 * a + b) * NL] = make_double2(s * v.x, bwd ? -s * v.y : s * v.y);
-        }
-}
-
-// FP64 links [Vh][9][NL] -> the plane layout [NL][9][Vh], 16 sites of all 9 NL planes
-// per workgroup through LDS (whole runs on both sides; entry q of site t at q * 17 + t)
-__global__ void __launch_bounds__(256)
-k_row_links_to_planes(const double2* __restrict__ src, double2* __restrict__ dst, int nl, long Vh) {
-    extern __shared__ double2 tile[];  // [9 nl][17]
-    const long s0 = (long)blockIdx.x * 16;
-    const int ne = 9 * nl, ns = Vh - s0 < 16 ? (int)(Vh - s0) : 16;
-    for (int e = threadIdx.x; e < ns * ne; e += 256) {
-        const int t = e / ne, q = e - t * ne;
-        tile[q * 17 + t] = src[s0 * ne + e];
-    }
-    __syncthreads();
-    const int t = threadIdx.x & 15;
-    if (t < ns)
-        for (int r = threadIdx.x >> 4; r < ne; r += 16) {
-            const int k = r / 9, e = r - 9 * k;
-            dst[(long)r * Vh + s0 + t] = tile[(e * nl + k) * 17 + t];
-        }
-}
-
 // row-layout links in another storage from the FP64 ones, one lane per (site, matrix)
 template <typename S>
 __global__ void __launch_bounds__(256)
@@ -355,24 +298,6 @@ k_row_links_from64(const double2* __restrict__ src, char* __restrict__ dst, long
 }
 
 // ---------------------------------------------------------------------------------------------
-hipError_t pack_links_rows(const void* fat, const void* lng, void* W, const Geom& g, int parity, int nl,
-                           hipStream_t s) {
-    const dim3 grid((unsigned)(((long)g.Vh * nl + 255) / 256));
-    if (nl == 16)
-        hipLaunchKernelGGL(k_pack_links_rows<16>, grid, dim3(256), 0, s, (const double2*)fat, (const double2*)lng,
-                           (double2*)W, g, parity);
-    else
-        hipLaunchKernelGGL(k_pack_links_rows<8>, grid, dim3(256), 0, s, (const double2*)fat, (const double2*)lng,
-                           (double2*)W, g, parity);
-    return hipGetLastError();
-}
-
-hipError_t row_links_to_planes(const void* Wr, void* Wp, int nl, long Vh, hipStream_t s) {
-    hipLaunchKernelGGL(k_row_links_to_planes, dim3((unsigned)((Vh + 15) / 16)), dim3(256), (size_t)9 * nl * 17 * 16, s,
-                       (const double2*)Wr, (double2*)Wp, nl, Vh);
-    return hipGetLastError();
-}
-
 hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh, hipStream_t s) {
     const long n = Vh * nl;
     const dim3 grid((unsigned)((n + 255) / 256));

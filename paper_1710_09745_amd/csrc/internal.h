@@ -82,8 +82,9 @@ inline int pad_n(int n) {
 }
 
 // hop.hip ---------------------------------------------------------------------------------------
-// FP64 folded links of one output parity from canonical device links
-hipError_t pack_links(const void* fat, const void* lng, void* W, const Geom& g, int parity, int nl,
+// FP64 folded links of one output parity from canonical device links, in the plane layout
+// and, unless Wr is null, in the row layout (rows.h)
+hipError_t pack_links(const void* fat, const void* lng, void* Wp, void* Wr, const Geom& g, int parity, int nl,
                       hipStream_t s);
 // lower-precision folded links from the FP64 ones
 hipError_t links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh, hipStream_t s);
@@ -120,11 +121,7 @@ bool rows_fit(int N, long Vh);
 // leading dimension of the row kernels' Gram partials
 inline int row_ld(int N) { return N <= 8 ? 8 : pad_n(N); }
 RowOrder row_order(const Geom& g, int N);
-// FP64 row-layout links of one parity from the canonical ones; from those the FP64 plane
-// layout, and other storages
-hipError_t pack_links_rows(const void* fat, const void* lng, void* W, const Geom& g, int parity, int nl,
-                           hipStream_t s);
-hipError_t row_links_to_planes(const void* Wr, void* Wp, int nl, long Vh, hipStream_t s);
+// row-layout links in another storage from the FP64 ones
 hipError_t row_links_from64(Prec pd, const void* W64, void* Wd, int nl, long Vh, hipStream_t s);
 // out = D_{p,1-p} in, or with ctr: out = m2 ctr - D_{p,1-p} in
 // (canon, FP64: out in the canonical layout; dots, FP64 with ctr: also Re ctr^H out of each column and block of sites, [row_blocks][N])
