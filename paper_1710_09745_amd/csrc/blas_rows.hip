@@ -106,6 +106,19 @@ __device__ __forceinline__ void row_product(C2<R> acc[3], const C2<R> v[3], bool
     if (HR || (T8 && last)) row_product_m<HR, 8>(acc, v, m);
     else row_product_m<HR, HR ? 8 : 16>(acc, v, m);
 }
+// Arithmetic of the passes' products and sums on NT tiles: that of the storage, but FP64 for
+// FP32 storage on two tiles, with one rounding as a result is stored: sums over 17 to 32
+// columns in FP32 leave errors of 2e-7 in the iterates, which with FP64 sums are those of the
+// stored numbers alone.  (An iteration, us, FP32 / FP64 sums: 16^3 x 48, N = 32 526 / 560,
+// 24^4, N = 24 716 / 761; with the plane kernels, whose products are FP64, 778 and 1138.)
+template <typename S, int NT> struct PassReal { using type = typename S::real; };
+template <> struct PassReal<F32, 2> { using type = double; };
+template <typename S, typename R> __device__ __forceinline__ void row_get(const RowRaw<S>& raw, C2<R> o[3]) {
+    C2<typename S::real> v[3];
+    raw.get(v);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) o[c] = C2<R>{(R)v[c].re, (R)v[c].im};
+}
 // Waves of a Gram workgroup: four from three tiles on, whose accumulators need more
 // than the 256 registers a lane has in a workgroup of eight.
 constexpr int row_gram_nw(int nt) { return nt <= 2 ? ROW_NW : 4; }
@@ -173,7 +186,7 @@ template <typename S, int NT, bool HR, bool T8, bool GR>
 __global__ void __launch_bounds__(64 * ROW_NW)
 k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* __restrict__ beta, int N, int Vh,
               RowOrder ord, int nb, int ld, double2* __restrict__ partials, const int* __restrict__ halt) {
-    using R = typename S::real;
+    using R = typename PassReal<S, NT>::type;
     constexpr int NP = HR ? 8 : 16 * NT;
     extern __shared__ unsigned char lds[];
     C2<R>* cf = reinterpret_cast<C2<R>*>(lds);  // [NP][NP], zero outside N x N
@@ -208,8 +221,8 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
             C2<R> av[NT][3], qv[NT][3];
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                a[t].get(av[t]);
-                q[t].get(qv[t]);
+                row_get<S>(a[t], av[t]);
+                row_get<S>(q[t], qv[t]);
             }
             const RowLane<S, NT, HR> M = L;
             sb = row_turn(++it, blockIdx.x, gridDim.x, ROW_NW / 4, w >> 2, nb, ord);
@@ -256,12 +269,12 @@ k_pass_a_rows(char* __restrict__ Q, const char* __restrict__ AP, const double2* 
                     RowRaw<S> ar;
                     ar.load(ra, L.template off<S>(lt, N), L.template cs<S>(lt, N));
                     C2<R> av[3];
-                    ar.get(av);
+                    row_get<S>(ar, av);
                     const C2<R>* m = cf + lt * 16 * NP + t * 16 + L.cl;
                     row_product<HR, T8>(acc, av, lt == NT - 1, [&](int l) { return m[l * NP]; });
                 }
                 C2<R> qv[3];
-                qr.get(qv);
+                row_get<S>(qr, qv);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     qv[c].re -= acc[c].re;
@@ -287,7 +300,7 @@ __global__ void __launch_bounds__(64 * ROW_NW)
 k_pass_b_rows(double2* __restrict__ X, const char* Qt, const char* P, char* Qn, char* Pn,
               const double2* __restrict__ betaC, const double2* __restrict__ Sinv, const double2* __restrict__ SH, int N,
               int Vh, RowOrder ord, int nb, const SolveState* __restrict__ stt) {
-    using R = typename S::real;
+    using R = typename PassReal<S, NT>::type;
     constexpr int TW = HR ? 8 : 16, NP = TW * NT, TE = TW * TW, NUP = NT * (NT + 1) / 2;
     extern __shared__ unsigned char lds[];
     C2<double>* cx = reinterpret_cast<C2<double>*>(lds);         // [NP][NP]
@@ -343,12 +356,18 @@ k_pass_b_rows(double2* __restrict__ X, const char* Qt, const char* P, char* Qn, 
         for (int c = 0; c < 3; ++c) {
             x[c].re += xa[c].re;
             x[c].im += xa[c].im;
-            pa[c].re += qa[c].re;
-            pa[c].im += qa[c].im;
         }
         row_store_nt(X, ox, L.template cs<F64>(jt, N), x);
         if (!full) return;
-        row_store<S, R>(Qn, o, L.template cs<S>(jt, N), qa);
+        C2<R> qs[3] = {qa[0], qa[1], qa[2]};
+        row_store_rt<S, R>(Qn, o, L.template cs<S>(jt, N), qs, true);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            // with sums finer than the storage, P' is formed from Q' as stored
+            const C2<R> q = std::is_same<R, typename S::real>::value ? qa[c] : qs[c];
+            pa[c].re += q.re;
+            pa[c].im += q.im;
+        }
         row_store<S, R>(Pn, o, L.template cs<S>(jt, N), pa);
     };
     if constexpr (NT <= 2) {
@@ -368,8 +387,8 @@ k_pass_b_rows(double2* __restrict__ X, const char* Qt, const char* P, char* Qn, 
             C2<R> pv[NT][3], qv[NT][3];
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                p[t].get(pv[t]);
-                q[t].get(qv[t]);
+                row_get<S>(p[t], pv[t]);
+                row_get<S>(q[t], qv[t]);
             }
 #pragma unroll
             for (int jt = 0; jt < NT; ++jt) {
@@ -398,8 +417,8 @@ k_pass_b_rows(double2* __restrict__ X, const char* Qt, const char* P, char* Qn, 
                     pr.load(rp, o, L.template cs<S>(lt, N));
                     if (lt <= jt) qr.load(rq, o, L.template cs<S>(lt, N));
                     C2<R> pv[3], qv[3];
-                    pr.get(pv);
-                    qr.get(qv);
+                    row_get<S>(pr, pv);
+                    row_get<S>(qr, qv);
                     tile(lt, jt, pv, qv, xa, pa, qa);
                 }
                 store(jt, xr, xa, pa, qa);
@@ -528,13 +547,18 @@ hipError_t launch_gram_rows(Prec prec, const void* A, const void* B, int N, int 
 
 bool pass_a_rows_gram(int N) { return N <= 32; }
 
+// bytes of a coefficient in the arithmetic of the passes
+template <typename S> static size_t pass_coef_bytes(int N) {
+    return N > 16 && N <= 32 ? sizeof(C2<typename PassReal<S, 2>::type>) : sizeof(C2<typename S::real>);
+}
+
 template <typename S>
 static void pass_a_rows_go(void* Q, const void* AP, const double2* beta, int N, int Vh, const RowOrder& o,
                            double2* part, const int* halt, hipStream_t s) {
     const int nb = row_blocks(N, Vh), ld = row_ld(N);
     const dim3 grid(row_grid(nb, o, GRAM_BLOCKS)), blk(64 * ROW_NW);
     const int np = N <= 8 ? 8 : (N + 15) / 16 * 16;
-    const size_t cf = (size_t)np * np * sizeof(C2<typename S::real>), red = ROW_NW * 512 * sizeof(double);
+    const size_t cf = (size_t)np * np * pass_coef_bytes<S>(N), red = ROW_NW * 512 * sizeof(double);
     const size_t lds = pass_a_rows_gram(N) && red > cf ? red : cf;
 #define GO(NT, HR, T8, GR)                                                                                         \
     hipLaunchKernelGGL((k_pass_a_rows<S, NT, HR, T8, GR>), grid, blk, lds, s, (char*)Q, (const char*)AP, beta, N, \
@@ -568,7 +592,7 @@ hipError_t launch_pass_a_rows(Prec prec, void* Q, const void* AP, const double2*
 template <typename S>
 static size_t pass_b_rows_lds(int N) {
     const int tw = N <= 8 ? 8 : 16, nt = N <= 8 ? 1 : (N + 15) / 16;
-    return (size_t)nt * nt * tw * tw * sizeof(C2<double>) + (size_t)nt * (nt + 1) * tw * tw * sizeof(C2<typename S::real>);
+    return (size_t)nt * nt * tw * tw * sizeof(C2<double>) + (size_t)nt * (nt + 1) * tw * tw * pass_coef_bytes<S>(N);
 }
 
 template <typename S>
