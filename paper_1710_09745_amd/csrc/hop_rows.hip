@@ -103,23 +103,40 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
     };
     RowRaw<S> v[D][NT];
     static_for<D>([&](auto k) { fetch(v[k.value], k); });
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) acc[t][a] = c2<R>(0, 0);
+    // The sum over directions in chains of G, so that a number takes part in no more
+    // roundings than in four chains of NL / 4 directions added in pairs (error of A x against
+    // extended precision, FP64: one chain of 6 NL multiply-adds 3.8e-16, the lane-split plane
+    // kernel's four 1.9e-16, these 1.9e-16; FP32 storage 2.1e-7, 1.1e-7, 1.1e-7; the time of
+    // both hops within 2 %).  Two chains in the 16-bit formats, whose storage leaves 2.8e-5
+    // and more whatever the chains: the vector unit is busy throughout there (24^4, N = 16,
+    // A x: two 302 us, six 328 us).
+    constexpr int G = S::scaled ? NL / 2 : (NL == 16 ? 3 : 1);
+    C2<R> part[NT][3];
     static_for<NL>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
+        C2<R>(*sum)[3] = k < G ? acc : part;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
+            if constexpr (k % G == 0)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) sum[t][a] = c2<R>(0, 0);
             C2<R> u[3];
             v[k % D][t].get(u);
             if constexpr (HR) {
-                row_matvec<k, 0x3>(acc[t], la.w, u);
-                row_matvec<k, 0xc>(acc[t], lb.w, u);
+                row_matvec<k, 0x3>(sum[t], la.w, u);
+                row_matvec<k, 0xc>(sum[t], lb.w, u);
             } else {
-                row_matvec<k, 0xf>(acc[t], la.w, u);
+                row_matvec<k, 0xf>(sum[t], la.w, u);
             }
+            if constexpr (k >= G && (k % G == G - 1 || k == NL - 1))
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    acc[t][a].re += part[t][a].re;
+                    acc[t][a].im += part[t][a].im;
+                    // here, not sunk into the branch of the store with `part` kept for it
+                    asm volatile("" : "+v"(acc[t][a].re), "+v"(acc[t][a].im));
+                }
         }
         if constexpr (k + D < NL) fetch(v[k % D], std::integral_constant<int, k + D>{});
     });
@@ -377,9 +394,13 @@ static void hop_rows_go(const void* W, const void* in, void* out, const void* ct
             GO2(HRV, NTV, DV, WV, ROWS_PLAIN);                            \
         }                                                                 \
     } while (0)
-    if (N <= 8) GO(true, 1, F ? 4 : 8, F ? 3 : 4);
-    else if (N <= 16) GO(false, 1, F ? 4 : 8, 4);
-    else GO(false, 2, F ? 2 : 4, 4);
+    // FP64 on more than one tile: two tiles leave registers for one direction in flight at
+    // four waves per SIMD, and up to 16^4 sites one tile with four in flight is as fast or
+    // faster (an application, us, one tile / two: 8^4, N = 24 19.6 / 25.9, 16^4, N = 24 125 /
+    // 126, N = 32 156 / 161, 16^3 x 48, N = 24 425 / 350, 24^4, N = 32 945 / 861)
+    if (N <= 8) GO(true, 1, F ? 4 : 8, F ? 2 : 4);
+    else if (N <= 16 || (F && g.Vh <= 32768)) GO(false, 1, F ? 4 : 8, F ? 3 : 4);
+    else GO(false, 2, F ? 1 : 4, 4);
 #undef GO
 #undef GO2
 }

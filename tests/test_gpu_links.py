@@ -105,6 +105,7 @@ def test_links_in_one_layout_where_memory_is_short():
         assert rel(short.apply(x[:n]), ref[:n]) <= 1e-12
     del blocks
     short.close()
+    free()
     ctx.load_links(fat, lng)  # room again: both layouts
     assert torch.equal(ctx.apply(x[:8]), ref)
     ctx.close()
