@@ -1587,11 +1587,10 @@ int bcg_solve_pseudo(bcg_ctx* ctx, const void* B, void* Xout, int nrhs, bcg_stat
             if (ops.rows) RETCK(hop_rows(ctx, Prec::FP64, 0, T, AP, P, N, halt, dots));
             else RETCK(ops.hop1(Prec::FP64, 0, T, AP, P, halt));
             Prof pr(ctx, BCG_K_CG_VEC);
-            HIPCK(ops.rows ? launch_pb_dot_sum(dots, N, Vh, ctx->nparts, st, s)
-                           : launch_pb_dot(P, AP, N, Vh, ctx->nparts, st, s));
-            HIPCK(launch_pb_alpha(ctx->nparts, N, Vh, ops.rows, st, s));
-            HIPCK(launch_pb_update1(R, AP, N, Vh, ops.rows, ctx->nparts, st, s));
-            HIPCK(launch_pb_beta(ctx->nparts, N, Vh, st, s));
+            if (!ops.rows) HIPCK(launch_pb_dot(P, AP, N, Vh, ctx->nparts, st, s));
+            HIPCK(launch_pb_alpha(ops.rows ? dots : ctx->nparts, ctx->nparts, N, Vh, ops.rows, st, s));
+            HIPCK(launch_pb_update1(X, R, P, AP, N, Vh, ops.rows, ctx->nparts, st, s));
+            HIPCK(launch_pb_beta(ctx->nparts, N, Vh, ops.rows, st, s));
             HIPCK(launch_pb_update2(X, P, R, N, Vh, ops.rows, st, s));
         }
     }

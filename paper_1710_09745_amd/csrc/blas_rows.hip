@@ -483,22 +483,26 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
     }
 }
 
-// per-column sums of |V|^2 over each workgroup's rows (FP64): partials[b * N + j]
-__global__ void __launch_bounds__(256)
+// per-column sums of |V|^2 over each workgroup's rows (FP64): partials[b * N + j].  As many
+// threads as a workgroup holds: the partials, and with them the workgroups, are a 256th of
+// the sites.
+constexpr int NORM_THREADS = 1024;
+__global__ void __launch_bounds__(NORM_THREADS)
 k_colnorm2_rows(const double2* __restrict__ V, int N, int cp, long rows, double* __restrict__ partials) {
-    __shared__ double red[256];
-    const int j = threadIdx.x & (cp - 1), rpw = 256 / cp;
+    __shared__ double red[NORM_THREADS / 64][64];
+    const int j = threadIdx.x & (cp - 1), rpw = NORM_THREADS / cp;
     double s = 0.0;
     if (j < N)
         for (long r = (long)blockIdx.x * rpw + threadIdx.x / cp; r < rows; r += (long)gridDim.x * rpw) {
             const double2 v = V[r * N + j];
             s += v.x * v.x + v.y * v.y;
         }
-    red[threadIdx.x] = s;
+    for (int off = 32; off >= cp; off >>= 1) s += __shfl_xor(s, off, 64);  // cp: a power of two up to 64
+    red[threadIdx.x >> 6][threadIdx.x & 63] = s;
     __syncthreads();
     if (threadIdx.x < cp && j < N) {
         double t = 0.0;
-        for (int q = 0; q < rpw; ++q) t += red[q * cp + j];
+        for (int w = 0; w < NORM_THREADS / 64; ++w) t += red[w][j];
         partials[(long)blockIdx.x * N + j] = t;
     }
 }
@@ -671,7 +675,7 @@ hipError_t launch_bmul_rows(Prec px, const void* X, Prec py, const void* Z, void
 // partials as launch_colnorm2 (the same count, reduced by launch_colnorm_reduce)
 hipError_t launch_colnorm2_rows(const double2* V, int N, int Vh, double* partials, hipStream_t s) {
     const int g = (Vh + 255) / 256;
-    hipLaunchKernelGGL(k_colnorm2_rows, dim3(g < NORM_BLOCKS ? g : NORM_BLOCKS), dim3(256), 0, s, V, N, pad_n(N),
+    hipLaunchKernelGGL(k_colnorm2_rows, dim3(g < NORM_BLOCKS ? g : NORM_BLOCKS), dim3(NORM_THREADS), 0, s, V, N, pad_n(N),
                        3L * Vh, partials);
     return hipGetLastError();
 }

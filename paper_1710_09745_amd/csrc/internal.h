@@ -267,14 +267,14 @@ struct PbState {
     int col_iters[64];
 };
 // (rows: blocks in the row layout, else planes)
-// partials of P^H AP per column, from both blocks (planes) or from the hop's block sums
+// planes: partials of P^H AP per column, as launch_pb_alpha's dots
 hipError_t launch_pb_dot(const double2* P, const double2* AP, int N, int Vh, double* partials, const PbState* st,
                          hipStream_t s);
-hipError_t launch_pb_dot_sum(const double* dots, int N, int Vh, double* partials, const PbState* st, hipStream_t s);
-hipError_t launch_pb_alpha(const double* partials, int N, int Vh, bool rows, PbState* st, hipStream_t s);
-hipError_t launch_pb_update1(double2* R, const double2* AP, int N, int Vh, bool rows, double* partials,
+// dots: those partials, or (rows) the block sums of the hop; partials: scratch
+hipError_t launch_pb_alpha(const double* dots, double* partials, int N, int Vh, bool rows, PbState* st, hipStream_t s);
+hipError_t launch_pb_update1(double2* X, double2* R, const double2* P, const double2* AP, int N, int Vh, bool rows, double* partials,
                              const PbState* st, hipStream_t s);
-hipError_t launch_pb_beta(const double* partials, int N, int Vh, PbState* st, hipStream_t s);
+hipError_t launch_pb_beta(const double* partials, int N, int Vh, bool rows, PbState* st, hipStream_t s);
 hipError_t launch_pb_update2(double2* X, double2* P, const double2* R, int N, int Vh, bool rows, const PbState* st,
                              hipStream_t s);
 // row layout: R and P take the true residual Rt on the columns with restart[j] != 0 (device flags)
