@@ -96,13 +96,13 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
         RowRaw<F64> a, b;
         a.load(ru1, (unsigned)i * ss + co[t], cs);
         b.load(ru2, (unsigned)i * ss + co[t], cs);
-        const C2<double> zero{0.0, 0.0};  // lanes past the last column add nothing
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            u1[t][q] = c < N ? a.v[q] : zero;
-            u2[t][q] = c < N ? b.v[q] : zero;
+            u1[t][q] = a.v[q];
+            u2[t][q] = b.v[q];
         }
     }
+    const bool last = (NT - 1) * 16 + row_lane_col<HR>(lane) < N;  // a column of the last tile
     // step s: direction s / NT (mu = direction mod 4, hop 1 then 3), column tile s % NT
     auto fetch = [&](RowRaw<F64>& a, RowRaw<F64>& b, auto sc) {
         constexpr int dir = decltype(sc)::value / NT, t = decltype(sc)::value % NT;
@@ -126,14 +126,16 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
         if constexpr (t == 0)
 #pragma unroll
             for (int e = 0; e < 9; ++e) acc[e] = C2<double>{0.0, 0.0};
+        if (t < NT - 1 || last) {  // lanes past the last column add nothing
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+            for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                // u v^H: (a, b) = u_a conj(v_b) = conj(v_b) u_a
-                cmac_conj(acc[3 * a + b], v1[s & 1].v[b], u1[t][a]);
-                cmac_conj(acc[3 * a + b], v2[s & 1].v[b], u2[t][a]);
-            }
+                for (int b = 0; b < 3; ++b) {
+                    // u v^H: (a, b) = u_a conj(v_b) = conj(v_b) u_a
+                    cmac_conj(acc[3 * a + b], v1[s & 1].v[b], u1[t][a]);
+                    cmac_conj(acc[3 * a + b], v2[s & 1].v[b], u2[t][a]);
+                }
+        }
         if constexpr (t == NT - 1) {
 #pragma unroll
             for (int e = 0; e < 9; ++e) pw[lane * 9 + e] = acc[e];
@@ -162,8 +164,14 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
                         const long ls = xs[0] + (long)st[1] * xs[1] + (long)st[2] * xs[2] + (long)st[3] * xs[3];
                         const double sg = (double)eta_sign(xs, mu) * (p == 0 ? 1.0 : -1.0);
                         typedef double pair_t __attribute__((ext_vector_type(2)));
-                        __builtin_nontemporal_store(pair_t{sg * r.re, sg * r.im},
-                                                    reinterpret_cast<pair_t*>(out + ((long)mu * 2 * g.Vh + ls) * 9 + e));
+                        const pair_t v{sg * r.re, sg * r.im};
+                        pair_t* o = reinterpret_cast<pair_t*>(out + ((long)mu * 2 * g.Vh + ls) * 9 + e);
+                        // Half rows store 16 entries of two links, then the last two: parts of
+                        // lines that L2 puts together unless they carry the streaming hint (us
+                        // with / without: 16^4, N = 5 122 / 103, 16^3 x 32, N = 8 247 / 222; a
+                        // whole row's, N = 16: 332 / 356)
+                        if constexpr (HR) *o = v;
+                        else __builtin_nontemporal_store(v, o);
                     }
                 }
             }
