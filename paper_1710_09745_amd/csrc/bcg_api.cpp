@@ -423,7 +423,8 @@ struct BlockOps {
     int N;
     bool rows;
     RowOrder ord;
-    BlockOps(bcg_ctx* c, int n) : ctx(c), N(n), rows(use_rows(c, n)), ord(row_order(c->g, n)) {}
+    BlockOps(bcg_ctx* c, int n) : BlockOps(c, n, use_rows(c, n)) {}
+    BlockOps(bcg_ctx* c, int n, bool in_rows) : ctx(c), N(n), rows(in_rows), ord(row_order(c->g, n)) {}
     int Vh() const { return (int)ctx->Vh; }
     int from_canon(const void* src, double2* dst) const {
         HIPCK(rows ? launch_canon_to_rows((const double2*)src, dst, N, Vh(), ctx->stream)
@@ -501,6 +502,10 @@ struct BlockOps {
             HIPCK(launch_gram_fold(ctx->partials, n, row_ld(N), ctx->partials + n * e, &n, halt, ctx->stream));
         }
         return reduce(ctx, part, n, nullptr, 0, 0.0, N, out, halt, row_ld(N));
+    }
+    // Y = X in another storage (planes: with the identity in M_ID)
+    int convert(Prec px, const void* X, Prec py, void* Y) const {
+        return bmul(px, X, py, nullptr, Y, rows ? nullptr : M(ctx, M_ID), nullptr);
     }
     int bmul(Prec px, const void* X, Prec py, const void* Z, void* Y, const double2* M, const int* skip) const {
         HIPCK(rows ? launch_bmul_rows(px, X, py, Z, Y, M, N, Vh(), ord, skip, ctx->stream)
@@ -924,21 +929,29 @@ int bcg_apply_prec(bcg_ctx* ctx, int prec, const void* in, void* out, int nrhs) 
     const Prec ps = (Prec)prec;
     if (ps == Prec::FP64) return bcg_apply(ctx, in, out, nrhs);
     RETCK(alloc_solve(ctx, nrhs, ps));
-    RETCK(ensure_sloppy_links(ctx, ps, use_rows(ctx, nrhs)));
-    const BlockOps ops(ctx, nrhs);
+    // 16-bit storage on 5 or 6 columns above 32768 sites: the half-row hops, whose vector unit
+    // works through both halves of every row, take longer than the planes' (fix16, us, rows /
+    // planes: 16^3 x 48, N = 5 114 / 96, N = 7 124 / 114, 24^3 x 48, N = 5 341 / 308, 16^4,
+    // N = 5 53 / 58); an iteration makes up for it in its other kernels (16^3 x 48, N = 5 155 /
+    // 152 us, N = 6 157 / 161, 20^4, N = 5 132 / 143)
+    auto in_rows = [&] {
+        return use_rows(ctx, nrhs) && !(pd_bytes(ps) == 4 && nrhs <= 6 && ctx->Vh > 32768);
+    };
+    RETCK(ensure_sloppy_links(ctx, ps, in_rows()));
+    const BlockOps ops(ctx, nrhs, in_rows());
     double2* I64 = Wd(ctx, WB_B64);
     void *P = W(ctx, WB_P0), *T = W(ctx, WB_T), *AP = W(ctx, WB_AP);
     {
         Prof pr(ctx, BCG_K_CONVERT);
         RETCK(ops.from_canon(in, I64));
-        HIPCK(launch_identity(M(ctx, M_ID), nrhs, ctx->stream));
-        RETCK(ops.bmul(Prec::FP64, I64, ps, nullptr, P, M(ctx, M_ID), nullptr));
+        if (!ops.rows) HIPCK(launch_identity(M(ctx, M_ID), nrhs, ctx->stream));
+        RETCK(ops.convert(Prec::FP64, I64, ps, P));
     }
     RETCK(ops.hop1(ps, 1, P, T, nullptr, nullptr));
     RETCK(ops.hop1(ps, 0, T, AP, P, nullptr));
     {
         Prof pr(ctx, BCG_K_CONVERT);
-        RETCK(ops.bmul(ps, AP, Prec::FP64, nullptr, I64, M(ctx, M_ID), nullptr));
+        RETCK(ops.convert(ps, AP, Prec::FP64, I64));
     }
     return ops.to_canon(I64, out);
 }

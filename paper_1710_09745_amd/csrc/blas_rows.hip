@@ -427,7 +427,8 @@ k_pass_b_rows(double2* __restrict__ X, const char* Qt, const char* P, char* Qn, 
     }
 }
 
-// Y <- Z + X M in FP64 arithmetic (Z may be NULL), all buffers distinct
+// Y <- Z + X M in FP64 arithmetic (Z may be NULL; M NULL: the identity, X in another
+// storage), all buffers distinct
 template <typename SX, typename SY, bool HR>
 __global__ void __launch_bounds__(64 * ROW_NW)
 k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __restrict__ Y,
@@ -438,7 +439,7 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nt = HR ? 1 : (N + 15) / 16, np = HR ? 8 : 16 * nt;
-    for (int l = threadIdx.x / np; l < np; l += 64 * ROW_NW / np) {
+    for (int l = threadIdx.x / np; l < np && M != nullptr; l += 64 * ROW_NW / np) {
         const int j = threadIdx.x % np;
         if (threadIdx.x >= (64 * ROW_NW / np) * np) break;
         const double2 b = (l < N && j < N) ? M[l * MAXN + j] : make_double2(0.0, 0.0);
@@ -454,14 +455,16 @@ k_bmul_rows(const char* __restrict__ X, const char* __restrict__ Z, char* __rest
         for (int t = 0; t < nt; ++t) {
             C2<double> acc[3] = {};
 #pragma unroll 1
-            for (int lt = 0; lt < nt; ++lt) {
+            for (int lt = M != nullptr ? 0 : t; lt < (M != nullptr ? nt : t + 1); ++lt) {
                 RowRaw<SX> xr;
                 xr.load(rx, L.template off<SX>(lt, N), L.template cs<SX>(lt, N));
-                C2<typename SX::real> xv[3];
-                xr.get(xv);
                 C2<double> xd[3];
+                row_get<SX>(xr, xd);
+                if (M == nullptr) {
 #pragma unroll
-                for (int c = 0; c < 3; ++c) xd[c] = C2<double>{(double)xv[c].re, (double)xv[c].im};
+                    for (int c = 0; c < 3; ++c) acc[c] = xd[c];
+                    break;
+                }
                 const C2<double>* m = cf + lt * 16 * np + t * 16 + L.cl;
                 row_product<HR, false>(acc, xd, false, [&](int l) { return m[l * np]; });
             }
@@ -641,7 +644,7 @@ static void bmul_rows_go(const void* X, const void* Z, void* Y, const double2* M
                          const int* skip, hipStream_t s) {
     const int nb = row_blocks(N, Vh), np = N <= 8 ? 8 : (N + 15) / 16 * 16;
     const dim3 grid(row_grid(nb, o, 2048)), blk(64 * ROW_NW);
-    const size_t lds = (size_t)np * np * sizeof(C2<double>);
+    const size_t lds = M != nullptr ? (size_t)np * np * sizeof(C2<double>) : 0;
     if (N <= 8)
         hipLaunchKernelGGL((k_bmul_rows<SX, SY, true>), grid, blk, lds, s, (const char*)X, (const char*)Z, (char*)Y, M,
                            N, Vh, o, nb, skip);

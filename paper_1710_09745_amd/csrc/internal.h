@@ -153,7 +153,7 @@ hipError_t launch_pass_a_rows(Prec prec, void* Q, const void* AP, const double2*
 hipError_t launch_pass_b_rows(Prec prec, double2* X, const void* Qt, const void* P, void* Qn, void* Pn,
                               const double2* betaC, const double2* Sinv, const double2* SH, int N, int Vh,
                               const RowOrder& o, const SolveState* st, hipStream_t s);
-// px, py: FP64, or one lower precision
+// px, py: FP64, or one lower precision; M null: the identity
 hipError_t launch_bmul_rows(Prec px, const void* X, Prec py, const void* Z, void* Y, const double2* M, int N, int Vh,
                             const RowOrder& o, const int* skip, hipStream_t s);
 hipError_t launch_colnorm2_rows(const double2* V, int N, int Vh, double* partials, hipStream_t s);
