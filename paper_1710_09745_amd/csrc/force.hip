@@ -89,6 +89,8 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
     const unsigned cs = row_cs<F64>(N, 0), ss = row_ss<F64>(N);
     unsigned co[NT];
     C2<double> u1[NT][3], u2[NT][3];
+    const bool last = (NT - 1) * 16 + row_lane_col<HR>(lane) < N;  // a column of the last tile
+    auto keep = [&](C2<double>& z) { z = C2<double>{last ? z.re : 0.0, last ? z.im : 0.0}; };
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int c = t * 16 + row_lane_col<HR>(lane);
@@ -100,9 +102,9 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
         for (int q = 0; q < 3; ++q) {
             u1[t][q] = a.v[q];
             u2[t][q] = b.v[q];
+            if (t == NT - 1) keep(u1[t][q]), keep(u2[t][q]);
         }
     }
-    const bool last = (NT - 1) * 16 + row_lane_col<HR>(lane) < N;  // a column of the last tile
     // step s: direction s / NT (mu = direction mod 4, hop 1 then 3), column tile s % NT
     auto fetch = [&](RowRaw<F64>& a, RowRaw<F64>& b, auto sc) {
         constexpr int dir = decltype(sc)::value / NT, t = decltype(sc)::value % NT;
@@ -126,16 +128,17 @@ k_link_force_rows(const char* __restrict__ X, const char* __restrict__ Lam, cons
         if constexpr (t == 0)
 #pragma unroll
             for (int e = 0; e < 9; ++e) acc[e] = C2<double>{0.0, 0.0};
-        if (t < NT - 1 || last) {  // lanes past the last column add nothing
+        if constexpr (t == NT - 1)  // lanes past the last column add nothing
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
+            for (int b = 0; b < 3; ++b) keep(v1[s & 1].v[b]), keep(v2[s & 1].v[b]);
 #pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    // u v^H: (a, b) = u_a conj(v_b) = conj(v_b) u_a
-                    cmac_conj(acc[3 * a + b], v1[s & 1].v[b], u1[t][a]);
-                    cmac_conj(acc[3 * a + b], v2[s & 1].v[b], u2[t][a]);
-                }
-        }
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                // u v^H: (a, b) = u_a conj(v_b) = conj(v_b) u_a
+                cmac_conj(acc[3 * a + b], v1[s & 1].v[b], u1[t][a]);
+                cmac_conj(acc[3 * a + b], v2[s & 1].v[b], u2[t][a]);
+            }
         if constexpr (t == NT - 1) {
 #pragma unroll
             for (int e = 0; e < 9; ++e) pw[lane * 9 + e] = acc[e];

@@ -40,6 +40,23 @@ template <typename S, int NL, bool NT> struct RowLinks {
     }
 };
 
+// Directions at which the sum over them starts another chain.  The lengths, 2 3 3 4 4 (naive
+// operator 1 1 2 2 2), give fewer roundings of large sums than four chains of NL / 4 added in
+// pairs, the plane kernel's (error of A x against extended precision, FP64: one chain of 6 NL
+// multiply-adds 3.8e-16, the lane-split plane kernel 1.9e-16, these 1.9e-16; FP32 storage
+// 2.1e-7, 1.1e-7, 1.1e-7).  Two chains in the 16-bit formats, whose storage leaves 2.8e-5 and
+// more whatever the chains: the vector unit is busy throughout there (24^4, N = 16, A x: two
+// chains 302 us, six 328 us).
+template <typename S, int NL> __host__ __device__ constexpr bool chain_start(int k) {
+    if (S::scaled) return k == NL / 2;
+    return NL == 16 ? (k == 2 || k == 5 || k == 8 || k == 12) : (k == 1 || k == 2 || k == 4 || k == 6);
+}
+template <typename S, int NL> __host__ __device__ constexpr int chain_second() {
+    int k = 1;
+    while (!chain_start<S, NL>(k)) ++k;
+    return k;
+}
+
 // The hop at one block of sites (four waves) and the NT column tiles from column ct0 on:
 // acc = D in, or with MASS acc = m2 * ctr - D in and z = ctr, at the lane's site and
 // columns.  D directions are in flight at a time.  Two tiles share the links, the site's
@@ -103,22 +120,16 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
     };
     RowRaw<S> v[D][NT];
     static_for<D>([&](auto k) { fetch(v[k.value], k); });
-    // The sum over directions in chains of G, so that a number takes part in no more
-    // roundings than in four chains of NL / 4 directions added in pairs (error of A x against
-    // extended precision, FP64: one chain of 6 NL multiply-adds 3.8e-16, the lane-split plane
-    // kernel's four 1.9e-16, these 1.9e-16; FP32 storage 2.1e-7, 1.1e-7, 1.1e-7; the time of
-    // both hops within 2 %).  Two chains in the 16-bit formats, whose storage leaves 2.8e-5
-    // and more whatever the chains: the vector unit is busy throughout there (24^4, N = 16,
-    // A x: two 302 us, six 328 us).
-    constexpr int G = S::scaled ? NL / 2 : (NL == 16 ? 3 : 1);
+    // The sum over directions in chains (chain_start), added as they end
     C2<R> part[NT][3];
     static_for<NL>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        C2<R>(*sum)[3] = k < G ? acc : part;
+        constexpr bool first = k < chain_second<S, NL>(), start = k == 0 || chain_start<S, NL>(k);
+        C2<R>(*sum)[3] = first ? acc : part;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            if constexpr (k % G == 0)
+            if constexpr (start)
 #pragma unroll
                 for (int a = 0; a < 3; ++a) sum[t][a] = c2<R>(0, 0);
             C2<R> u[3];
@@ -129,7 +140,7 @@ __device__ __forceinline__ void hop_rows_block(const char* __restrict__ W, const
             } else {
                 row_matvec<k, 0xf>(sum[t], la.w, u);
             }
-            if constexpr (k >= G && (k % G == G - 1 || k == NL - 1))
+            if constexpr (!first && (k == NL - 1 || chain_start<S, NL>(k + 1)))
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     acc[t][a].re += part[t][a].re;
@@ -181,15 +192,12 @@ k_hop_rows(const char* __restrict__ W, const char* __restrict__ in, char* __rest
     __shared__ C2<R> tile[EPI == ROWS_CANON ? NT * TW * (RW + 1) : 1];
     if (halt != nullptr && *halt) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int sb, ct;
-    if (ord.on) {
-        const int q = blockIdx.x >> 3;
-        ct = q % nct;
-        sb = row_block((q / nct) * 8 + (blockIdx.x & 7), ord);
-    } else {
-        sb = blockIdx.x / nct;
-        ct = blockIdx.x - sb * nct;
-    }
+    // the tiles of a site block eight workgroups apart, on one XCD (an odd rest of blocks:
+    // next to each other)
+    const int nb = gridDim.x / nct, whole = (nb & ~7) * nct, q = blockIdx.x >> 3, rest = (int)blockIdx.x - whole;
+    const int ct = rest < 0 ? q % nct : rest % nct;
+    int sb = rest < 0 ? (q / nct) * 8 + (blockIdx.x & 7) : (nb & ~7) + rest / nct;
+    if (ord.on) sb = row_block(sb, ord);
     auto tiles = [&](auto ntc) {
         constexpr int T = decltype(ntc)::value;
         C2<R> acc[T][3], z[T][3];
@@ -394,13 +402,16 @@ static void hop_rows_go(const void* W, const void* in, void* out, const void* ct
             GO2(HRV, NTV, DV, WV, ROWS_PLAIN);                            \
         }                                                                 \
     } while (0)
-    // FP64 on more than one tile: two tiles leave registers for one direction in flight at
-    // four waves per SIMD, and up to 16^4 sites one tile with four in flight is as fast or
-    // faster (an application, us, one tile / two: 8^4, N = 24 19.6 / 25.9, 16^4, N = 24 125 /
-    // 126, N = 32 156 / 161, 16^3 x 48, N = 24 425 / 350, 24^4, N = 32 945 / 861)
+    // FP64 on more than one tile: two at a time with three directions in flight at two waves
+    // per SIMD, but one at a time (four directions, three waves) where the third tile would be
+    // left alone and up to 8192 sites, whose workgroups are few (an application, us, one /
+    // two: 16^3 x 48, N = 40 654 / 768, N = 64 1152 / 963, N = 28 511 / 388, 24^4, N = 32 942 /
+    // 794; 8^4, N = 24 20 / 25; two at three or four waves with two directions or one: 4 to 13 %
+    // longer than these)
+    const bool one = N <= 16 || (F && ((N > 32 && N <= 48) || g.Vh <= 8192));
     if (N <= 8) GO(true, 1, F ? 4 : 8, F ? 2 : 4);
-    else if (N <= 16 || (F && g.Vh <= 32768)) GO(false, 1, F ? 4 : 8, F ? 3 : 4);
-    else GO(false, 2, F ? 1 : 4, 4);
+    else if (one) GO(false, 1, F ? 4 : 8, F ? 3 : 4);
+    else GO(false, 2, F ? 3 : 4, F ? 2 : 4);
 #undef GO
 #undef GO2
 }
