@@ -60,15 +60,16 @@ def model_bytes_per_site(kernel, N, prec="fp64", nl=16, aliased_gram=None):
     return None
 
 
-# source file of each timed kernel; its counters also depend on the shared headers
-# and on the host code that picks its launch shape
-KERNEL_SOURCE = {"hop_oe": "hop.hip", "hop_eo": "hop.hip", "pass_a": "blas.hip", "pass_b": "blas.hip",
-                 "gram": "blas.hip"}
+# source files of each timed kernel (plane and row layout); its counters also depend on
+# the shared headers and on the host code that picks its launch shape
+HOP_SOURCES, PASS_SOURCES = ["hop.hip", "hop_rows.hip"], ["blas.hip", "blas_rows.hip"]
+KERNEL_SOURCE = {"hop_oe": HOP_SOURCES, "hop_eo": HOP_SOURCES, "pass_a": PASS_SOURCES, "pass_b": PASS_SOURCES,
+                 "gram": PASS_SOURCES}
 
 
 def kernel_source_hash(kernel):
     h = hashlib.sha256()
-    files = sorted(f for f in os.listdir(CSRC) if f.endswith(".h")) + [KERNEL_SOURCE[kernel], "bcg_api.cpp"]
+    files = sorted(f for f in os.listdir(CSRC) if f.endswith(".h")) + KERNEL_SOURCE[kernel] + ["bcg_api.cpp"]
     for f in files:
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(f.encode())

@@ -300,7 +300,8 @@ int bcg_set_stability(bcg_ctx *ctx, int ru_window, int stall_limit, int qr_passe
  *                         N > 8, 2: on the vector ALUs
  *   BCG_OPT_SMALL_THREADS threads (64, 256, 1024) of the one-workgroup N x N
  *                         kernels, used when N^2 <= 4 x threads; 0 (default):
- *                         the kernels on rows of lanes for N <= 32, else 1024
+ *                         the kernels on rows of lanes for N <= 32 (one and two
+ *                         columns only where they sum Gram partials), else 1024
  *   BCG_OPT_SITE_ORDER    1: workgroups walk the lattice so that XCD x takes the
  *                         x-th eighth of every time slice and all XCDs sweep the
  *                         slices together, 2: plain lexicographic order

@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -756,7 +757,7 @@ int bcg_create(bcg_ctx** out, const int dims[4], int improved, void* hip_stream)
         void** p;
         size_t bytes;
     };
-    auto carve = [](const std::vector<Part>& parts, auto alloc, void** block) {
+    auto carve = [](std::initializer_list<Part> parts, auto alloc, void** block) {
         size_t total = 0;
         for (const Part& t : parts) total += (t.bytes + 255) & ~(size_t)255;
         if (alloc(block, total) != hipSuccess) {

@@ -115,7 +115,12 @@ enum { EPI_PLAIN_ = 0, EPI_MASS_ = 1, EPI_MASS_DOT_ = 2 };
 // on a lattice so small that the number of launches counts (us per block CG iteration,
 // FP64, N = 4, rows against planes: 41 / 53 at 4^4, 45 / 56 at 8^2 x 12^2, 61 / 67 at
 // 16^3 x 8, 93 / 87 at 16^4; an application, N = 2: 19 / 21, then 29 / 25 at 12^4; one
-// column is never faster in rows)
+// column is never faster in rows).  From 5 columns on, time of a block CG iteration on planes
+// over rows, lattices of 1296 to 1048576 sites of a parity, both operators: FP64 1.05 (17
+// columns, 8^4) to 1.7, FP32 1.05 to 1.9 up to 48 columns and 0.95 (naive 16^4) to 1.06 at 56
+// to 64, whose plane passes are on the FP32 matrix cores, 16-bit 0.96 (5 columns, 16^3 x 48)
+// and 1.0 to 2.2 from 6; of an application 1.1 to 2.4, of the link force 0.95 (naive 16^4, 5
+// columns) and 1.05 to 3.4, of pseudo-block CG 1.0 to 1.9
 constexpr long ROWS_SMALL_SITES = 8192;
 bool rows_fit(int N, long Vh);
 // leading dimension of the row kernels' Gram partials
@@ -169,11 +174,12 @@ hipError_t launch_gram(Prec prec, const void* A, const void* B, int N, int Vh, d
 // out[i*64 + j] = sum_b partials[b][i*NB + j]  (fixed order)
 // number of partials launch_gram writes
 int gram_parts(int N, int Vh, bool mfma);
-// out[i*64 + j] = sum_b pa[b][i*NB + j] + alpha * sum_b pb[b][i*NB + j]  (fixed order; pb may be NULL)
-// ld: leading dimension of the partials (0: pad_n(N))
-// sums of a fixed number of partials each, *folded of them, into out (other memory)
+// sums of a fixed number of the P partials each (leading dimension ld), *folded of them, into
+// out (other memory)
 hipError_t launch_gram_fold(const double2* part, int P, int ld, double2* out, int* folded, const int* halt,
                             hipStream_t s);
+// out[i*64 + j] = sum_b pa[b][i*NB + j] + alpha * sum_b pb[b][i*NB + j]  (fixed order; pb may be NULL)
+// ld: leading dimension of the partials (0: pad_n(N))
 hipError_t launch_gram_reduce(const double2* pa, int na, const double2* pb, int nb, double alpha, int N,
                               double2* out, const int* halt, hipStream_t s, int ld = 0);
 // LDS bytes of a fused Gram epilogue of the streaming passes (0: does not fit, use launch_gram)
@@ -300,11 +306,11 @@ hipError_t launch_small_init(const double2* H, double2* C, double2* Cinv, SolveS
 hipError_t launch_sstep_coef(const double2* Gv, const double2* Gvv, const double2* Ga, const double2* Wp,
                              const double2* Pv, double2* Bk, double2* alpha, double2* nalpha, int* status, int K,
                              int N, int first, hipStream_t s);
-// beta = G^{-1}, betaC = beta C.  parts > 0 (small_sums_parts only): G is that many Gram
-// partials of leading dimension row_ld(N), which the kernel sums itself
 // whether the kernels of N columns sum `parts` Gram partials (leading dimension row_ld(N))
 // themselves rather than leave it to launch_gram_reduce
 bool small_sums_parts(int N, int parts, int req);
+// beta = G^{-1}, betaC = beta C.  parts > 0 (small_sums_parts only): G is that many Gram
+// partials of leading dimension row_ld(N), which the kernel sums itself
 hipError_t launch_small1(const double2* G, const double2* C, double2* beta, double2* betaC,
                          SolveState* st, int N, int req, int parts, hipStream_t s);
 // residual test, S from H = S^H S, Sinv, S^H, C <- S C; sets pb_mode / halt

@@ -667,8 +667,11 @@ template <int NN> __device__ __forceinline__ void herm_column(const Z2* t, int j
     for (int i = 0; i < NN; ++i) A[i] = herm_entry<NN>(t, i, j);
 }
 
-// 1 / d and 1 / sqrt(d) for a positive normal d: the hardware estimate and two Newton
-// steps (the pivots are a serial chain, and the IEEE division is twice as long)
+// 1 / d and 1 / sqrt(d) for a positive d: the hardware estimate and two Newton steps, whose
+// residual is one fused multiply-add (the pivots are a serial chain, and the IEEE division is
+// twice as long: a solve at 4^4 and 8^4 1 to 2 % longer).  Errors over 4e6 pivots, in units of
+// 2^-53, worst and root mean square: 1.00 and 0.44 as the division's, and 1.24 and 0.48 where
+// the division by the square root has 1.49 and 0.60.
 __device__ __forceinline__ double rcp_nr(double d) {
     double x = __builtin_amdgcn_rcp(d);
     x = fma(x, fma(-d, x, 1.0), x);
