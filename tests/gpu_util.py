@@ -1,4 +1,6 @@
 """Helpers shared by the GPU parity tests: contexts on cuda:0 and seeded inputs."""
+import time
+
 import numpy as np
 import torch
 
@@ -97,3 +99,21 @@ def config_inputs_cached(config, nrhs):
     c = synth.CONFIGS[config]
     B = synth.rhs(synth.make_rng(synth.seed_for(config, 1)), nrhs, c["dims"])
     return fat, lng, B
+
+
+def best_times(calls, rounds=10, repeats=1):
+    """Shortest time in seconds of each call (by its key) over rounds that take the calls in
+    turn, so that a clock that changes meets all of them."""
+    best = {k: float("inf") for k in calls}
+    for f in calls.values():
+        f()
+    for _ in range(rounds):
+        for k, f in calls.items():
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(repeats):
+                f()
+            torch.cuda.synchronize()
+            best[k] = min(best[k], time.perf_counter() - t)
+    print(f"[times] {best}", flush=True)
+    return best

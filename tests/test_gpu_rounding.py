@@ -1,14 +1,11 @@
 """Rounding of the operator in the row layout, against its definition in extended precision:
 no larger than in the lane-split kernel of the plane layout, which sums four chains."""
-import time
-
 import numpy as np
 import pytest
-import torch
 
 import oracle
 
-from gpu_util import context, emulated_sloppy_apply, inputs, site_scaled_err, to_dev
+from gpu_util import best_times, context, emulated_sloppy_apply, inputs, site_scaled_err, to_dev
 from test_gpu_operator import SLOPPY_TOL
 
 pytestmark = pytest.mark.gpu
@@ -82,20 +79,8 @@ def test_sloppy_apply_takes_no_longer_than_planes():
     dims, n = (16, 16, 16, 48), 5
     fat, lng, B = inputs(dims, True, n, 23200)
     x = to_dev(B)
-    best = {}
-    for planes in (0, 1):
-        ctx = context(dims, True, fat, lng, 0.05)
-        ctx.set_option("site_order", planes)
-        ctx.apply_prec("fix16", x)
-        times = []
-        for _ in range(8):
-            torch.cuda.synchronize()
-            t = time.perf_counter()
-            for _ in range(50):
-                ctx.apply_prec("fix16", x)
-            torch.cuda.synchronize()
-            times.append(time.perf_counter() - t)
-        best[planes] = min(times)
-        ctx.close()
-    print(best)
-    assert best[0] <= 1.08 * best[1]
+    default, planes = (context(dims, True, fat, lng, 0.05) for _ in range(2))
+    planes.set_option("site_order", 1)
+    t = best_times({"default": lambda: default.apply_prec("fix16", x),
+                    "planes": lambda: planes.apply_prec("fix16", x)}, repeats=50)
+    assert t["default"] <= 1.1 * t["planes"]
